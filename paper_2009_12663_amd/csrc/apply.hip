@@ -24,13 +24,16 @@
 
 namespace {
 
-__global__ void reduce_partials(int64_t count, int nchunks, const double* __restrict__ part,
-                                double* __restrict__ Z) {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= count) return;
-    double s = 0.0;
-    for (int ch = 0; ch < nchunks; ++ch) s += part[(int64_t)ch * count + e];
-    Z[e] = s;
+__global__ void __launch_bounds__(SUM_THREADS) reduce_partials(int64_t count, int nchunks,
+                                                               const double* __restrict__ part,
+                                                               double* __restrict__ Z) {
+    __shared__ double sh[SUM_DEPTH][SUM_ENTRIES];
+    const int64_t e = blockIdx.x * (int64_t)SUM_ENTRIES + threadIdx.x % SUM_ENTRIES;
+    const bool live = e < count;
+    const double t = ordered_sum(
+        0, nchunks, sh, [&](int ch) { return live ? part[(int64_t)ch * count + e] : 0.0; },
+        [](double sum, double v, int) { return sum + v; });
+    if (threadIdx.x < SUM_ENTRIES && e < count) Z[e] = t;
 }
 
 // One 64-lane wave per probe column j.
@@ -462,7 +465,7 @@ int apply_generic(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, c
     const int64_t count = (int64_t)twok * c;
     prof_end(h);
     prof_begin(h, "apply_reduce");
-    hipLaunchKernelGGL(reduce_partials, dim3(ceil_div(count, 256)), dim3(256), 0, h->stream, count, nchunks, part, Z);
+    if (int rc2 = sum_partials(h->stream, count, nchunks, part, Z)) return rc2;
     prof_end(h);
     if (int rc2 = apply_small_solve(h, c, Z, P, T)) return rc2;
     prof_begin(h, diff ? "hdiff_gemm2" : "apply_gemm2");
@@ -515,7 +518,7 @@ int apply_streamed(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff) 
         if (rc != BFGS_OK) return rc;
     }
     const int64_t count = (int64_t)twok * c;
-    hipLaunchKernelGGL(reduce_partials, dim3(ceil_div(count, 256)), dim3(256), 0, h->stream, count, used, part, Z);
+    if ((rc = sum_partials(h->stream, count, used, part, Z)) != BFGS_OK) return rc;
     if ((rc = apply_small_solve(h, c, Z, P, T)) != BFGS_OK) return rc;
     ProfScope ps(h, diff ? "hdiff_stream_pass2" : "apply_stream_pass2");
     rc = stream_slices(h, k, [&](int, int64_t r0, int64_t rows, const void* Sst, const void* Yst) {
@@ -560,8 +563,28 @@ __global__ void __launch_bounds__(256, 2) batch_pass1(const PersistProblem* __re
     }
 }
 
-// One workgroup per (problem, block of SB_COLS columns): the fixed-order sum of that
-// block's pass-1 partials into Z, then the small solve of the block.
+// Z of every problem: the fixed-order sums of its pass-1 partials, one workgroup per
+// (problem, SUM_ENTRIES entries), as reduce_partials forms them.
+__global__ void __launch_bounds__(SUM_THREADS) batch_sum(const PersistProblem* __restrict__ pr, int nprob) {
+    __shared__ double sh[SUM_DEPTH][SUM_ENTRIES];
+    int lo = 0, hi = nprob - 1;   // last problem whose first block is <= this one
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (pr[mid].firstsum <= (int)blockIdx.x) lo = mid;
+        else hi = mid - 1;
+    }
+    const PersistProblem& q = pr[lo];
+    const int64_t count = (int64_t)2 * q.k * q.c;
+    const int64_t e = (int64_t)((int)blockIdx.x - q.firstsum) * SUM_ENTRIES + threadIdx.x % SUM_ENTRIES;
+    const bool live = e < count;
+    const double* part = q.part;
+    const double t = ordered_sum(
+        0, q.nchunks, sh, [&](int ch) { return live ? part[(int64_t)ch * count + e] : 0.0; },
+        [](double sum, double v, int) { return sum + v; });
+    if (threadIdx.x < SUM_ENTRIES && e < count) q.Z[e] = t;
+}
+
+// One workgroup per (problem, block of SB_COLS columns): the small solve of the block.
 __global__ void __launch_bounds__(256) batch_solve(const PersistProblem* __restrict__ pr, int nprob) {
     int blk = blockIdx.x, p = 0;
     while (p < nprob && blk >= (pr[p].c + SB_COLS - 1) / SB_COLS) {
@@ -570,16 +593,6 @@ __global__ void __launch_bounds__(256) batch_solve(const PersistProblem* __restr
     }
     if (p >= nprob) return;   // whole workgroup
     const PersistProblem& q = pr[p];
-    const int twok = 2 * q.k, j0 = blk * SB_COLS, nj = min(SB_COLS, q.c - j0);
-    const int64_t count = (int64_t)twok * q.c;
-    for (int e = threadIdx.x; e < twok * nj; e += blockDim.x) {
-        const int64_t idx = (int64_t)j0 * twok + e;
-        double sacc = 0.0;
-        for (int ch = 0; ch < q.nchunks; ++ch) sacc += q.part[(int64_t)ch * count + idx];
-        q.Z[idx] = sacc;
-    }
-    __threadfence_block();
-    __syncthreads();
     small_solve_block(q.k, q.kmax, q.c, q.Rm, q.Rinv, q.RinvT, q.YHY, q.Z, q.P, q.P + (size_t)q.k * q.c, q.status,
                       blk);
 }
@@ -624,7 +637,7 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
             return (double)hs[a]->n * hs[a]->k * ncols[a] > (double)hs[b]->n * hs[b]->k * ncols[b];
         });
         std::vector<PersistProblem> host(nprob);
-        int t1 = 0, t2 = 0, tsolve = 0;
+        int t1 = 0, tsum = 0, t2 = 0, tsolve = 0;
         for (int r = 0; r < nprob; ++r) {
             const int i = order[r];
             bfgsuq_ctx* h = hs[i];
@@ -661,8 +674,10 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
             q.YHY = h->YHY;
             q.status = h->status;
             q.first1 = t1;
+            q.firstsum = tsum;
             q.first2 = t2;
             t1 += q.nchunks * q.ptiles * q.ctiles;
+            tsum += ceil_div((int64_t)twok * c, SUM_ENTRIES);
             t2 += ceil_div(q.n, (int64_t)FT) * q.ctiles;
             tsolve += ceil_div(c, SB_COLS);
         }
@@ -683,6 +698,7 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
                                 hipMemcpyHostToDevice, st));
         slot->nprob = nprob;
         slot->items1 = t1;
+        slot->sum_blocks = tsum;
         slot->items2 = t2;
         slot->solve_blocks = tsolve;
     }
@@ -694,6 +710,7 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
     hipLaunchKernelGGL(batch_reset, dim3(1), dim3(64), 0, st, slot->head);
     hipLaunchKernelGGL((batch_pass1<Ts, Th, Ts>), dim3(g1), dim3(256), 0, st, slot->prob, nprob, slot->items1,
                        slot->head);
+    hipLaunchKernelGGL(batch_sum, dim3(slot->sum_blocks), dim3(SUM_THREADS), 0, st, slot->prob, nprob);
     hipLaunchKernelGGL(batch_solve, dim3(slot->solve_blocks), dim3(256), 0, st, slot->prob, nprob);
     hipLaunchKernelGGL((batch_pass2<Ts, Th, Th, Ts>), dim3(g2), dim3(256), 0, st, slot->prob, nprob, slot->items2,
                        slot->head + 1);
@@ -711,6 +728,12 @@ int batch_apply_persistent(bfgsuq_ctx* const* hs, int nprob, const void* const* 
     if (s0 == BFGS_F64) return batch_persistent_impl<double, double>(hs, nprob, V, ncols, out, st, slot, upload, wg_per_cu);
     if (s0 == BFGS_F32) return batch_persistent_impl<float, float>(hs, nprob, V, ncols, out, st, slot, upload, wg_per_cu);
     return BFGS_ERR_ARG;
+}
+
+int sum_partials(hipStream_t st, int64_t count, int nchunks, const double* part, double* out) {
+    hipLaunchKernelGGL(reduce_partials, dim3(ceil_div(count, SUM_ENTRIES)), dim3(SUM_THREADS), 0, st, count, nchunks,
+                       part, out);
+    return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
 }
 
 int apply_small_solve(bfgsuq_ctx* h, int c, const double* Z, double* P, double* T) {

@@ -199,6 +199,48 @@ __device__ __forceinline__ void set_status(int32_t* status, int32_t code) {
     if (status[0] == 0) status[0] = code;
 }
 
+// Sums in index order, fed by a whole workgroup.  An entry's terms are added one after
+// the other (the result does not depend on the launch shape, and the rSVD's columns at
+// numerically zero eigenvalues, which are rounding noise, stay what they were), but
+// SUM_SEGS threads per entry fetch them: a batch of SUM_DEPTH terms of SUM_ENTRIES
+// consecutive entries goes through LDS while the next is in flight.  With one thread
+// fetching and adding, the loads queued behind one another: 300-420 us for 1000-2000
+// partials of 200-9000 entries, 15-35 us in this form.
+constexpr int SUM_ENTRIES = 64, SUM_SEGS = 16, SUM_THREADS = SUM_ENTRIES * SUM_SEGS, SUM_DEPTH = 4 * SUM_SEGS;
+
+// load(t) gives term t of this thread's entry (threadIdx.x % SUM_ENTRIES; 0 for an entry
+// that does not exist); add(sum, v, t) the sum with term t, lo <= t < hi.  Called by a
+// whole workgroup of SUM_THREADS; the sum is returned to the first SUM_ENTRIES threads.
+template <typename Load, typename Add>
+__device__ __forceinline__ double ordered_sum(int lo, int hi, double (*sh)[SUM_ENTRIES], Load load, Add add) {
+    const int x = threadIdx.x % SUM_ENTRIES, s = threadIdx.x / SUM_ENTRIES;
+    double v[4], sum = 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = lo + s + SUM_SEGS * u < hi ? load(lo + s + SUM_SEGS * u) : 0.0;
+    for (int b = lo; b < hi; b += SUM_DEPTH) {
+        __syncthreads();   // the previous batch has been added
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sh[s + SUM_SEGS * u][x] = v[u];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int t = b + SUM_DEPTH + s + SUM_SEGS * u;
+            v[u] = t < hi ? load(t) : 0.0;
+        }
+        if (s != 0) continue;
+        if (hi - b >= SUM_DEPTH) {
+#pragma unroll 16
+            for (int t = 0; t < SUM_DEPTH; ++t) sum = add(sum, sh[t][x], b + t);
+        } else {
+            for (int t = 0; t < hi - b; ++t) sum = add(sum, sh[t][x], b + t);
+        }
+    }
+    return sum;
+}
+
+// out[e] = sum over ch of part[ch * count + e], e < count (apply.hip).
+int sum_partials(hipStream_t st, int64_t count, int nchunks, const double* part, double* out);
+
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
@@ -272,7 +314,7 @@ int apply_small_solve(bfgsuq_ctx* h, int c, const double* Z, double* P, double* 
 // One problem of a persistent batched apply (device copy read by the pass kernels).
 struct PersistProblem {
     int64_t n, ld, rows_per_chunk;
-    int k, kmax, c, ptiles, ctiles, nchunks, first1, first2;
+    int k, kmax, c, ptiles, ctiles, nchunks, first1, firstsum, first2;
     const void *S, *Y, *h0, *V;
     void* out;
     double *part, *Z, *P;
@@ -286,12 +328,12 @@ struct PersistSlot {
     PersistProblem* prob = nullptr;
     size_t cap = 0;
     unsigned* head = nullptr;
-    int nprob = 0, items1 = 0, items2 = 0, solve_blocks = 0;
+    int nprob = 0, items1 = 0, sum_blocks = 0, items2 = 0, solve_blocks = 0;
 };
 
 // Apply B_k of every problem to its block (float32 or float64 storage, all of one
-// type, 1 <= k <= 256): four launches on st in all (queue reset, pass 1 of every
-// problem, the small solves, pass 2).  upload = false reuses the slot's descriptors
+// type, 1 <= k <= 256): five launches on st in all (queue reset, pass 1 of every
+// problem, the sums of its partials, the small solves, pass 2).  upload = false reuses the slot's descriptors
 // (a graph capture after an eager call with the same arguments).  wg_per_cu sets the
 // persistent grid (workgroups per compute unit).
 int batch_apply_persistent(bfgsuq_ctx* const* hs, int nprob, const void* const* V, const int32_t* ncols,

@@ -50,14 +50,6 @@ __global__ void set_identity(double* __restrict__ M, int c) {
         M[e] = (e / c == e % c) ? 1.0 : 0.0;
 }
 
-__global__ void sum_chunks(int64_t count, int nchunks, const double* __restrict__ part, double* __restrict__ out) {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= count) return;
-    double s = 0.0;
-    for (int ch = 0; ch < nchunks; ++ch) s += part[(int64_t)ch * count + e];
-    out[e] = s;
-}
-
 // ---------------------------------------------------------------------------
 // Small float64 steps, one workgroup of 256 threads.  Matrices live in global
 // memory (at most 256 x 256 doubles, cache resident).
@@ -1006,7 +998,7 @@ int qr_two_blocks(bfgsuq_ctx* h, int c, double* E, double* Q, int nchunks, int64
         hipLaunchKernelGGL((qtx_mfma<double, double>), dim3(nchunks, ceil_div(c1, MT_TILE), ceil_div(c2, MT_TILE)),
                            dim3(256), 0, h->stream, n, c1, c2, Q, E2, part, rows_per_chunk);
         double* dst = pass == 0 ? R12 : Rk;
-        hipLaunchKernelGGL(sum_chunks, dim3(ceil_div(cnt, 256)), dim3(256), 0, h->stream, cnt, nchunks, part, dst);
+        if ((rc = sum_partials(h->stream, cnt, nchunks, part, dst)) != BFGS_OK) return rc;
         hipLaunchKernelGGL((basis_mfma<double, double, true>), dim3((unsigned)ceil_div(n, (int64_t)MT_TILE),
                            ceil_div(c2, MT_TILE)), dim3(256), 0, h->stream, n, c1, c2, Q, dst, E2);
         if (pass == 1) hipLaunchKernelGGL(add_into, dim3(ceil_div(cnt, 256)), dim3(256), 0, h->stream, cnt, Rk, R12);
@@ -1020,7 +1012,7 @@ int qr_two_blocks(bfgsuq_ctx* h, int c, double* E, double* Q, int nchunks, int64
     double* Rn1 = Rb + 5 * cc;
     hipLaunchKernelGGL((qtx_mfma<double, double>), dim3(nchunks, ceil_div(c1, MT_TILE), ceil_div(c2, MT_TILE)),
                        dim3(256), 0, h->stream, n, c1, c2, Q, Q2, part, rows_per_chunk);
-    hipLaunchKernelGGL(sum_chunks, dim3(ceil_div(cnt, 256)), dim3(256), 0, h->stream, cnt, nchunks, part, P);
+    if ((rc = sum_partials(h->stream, cnt, nchunks, part, P)) != BFGS_OK) return rc;
     hipLaunchKernelGGL((basis_mfma<double, double, true>), dim3((unsigned)ceil_div(n, (int64_t)MT_TILE),
                        ceil_div(c2, MT_TILE)), dim3(256), 0, h->stream, n, c1, c2, Q, P, Q2);
     hipLaunchKernelGGL(add_p_times_r, dim3(ceil_div(cnt, 256)), dim3(256), 0, h->stream, c1, c2, P, R22, R12);
@@ -1196,8 +1188,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
         const int nblk = ceil_div(c, MT_TILE);
         hipLaunchKernelGGL((qtx_mfma<TQ, TE>), dim3(nchunks, nblk, nblk), dim3(256), 0, h->stream, n, c, c, Q, Efree,
                            part, rows_per_chunk);
-        hipLaunchKernelGGL(sum_chunks, dim3(ceil_div((int64_t)cc, 256)), dim3(256), 0, h->stream, (int64_t)cc, nchunks,
-                           part, Tm);
+        if ((rc = sum_partials(h->stream, (int64_t)cc, nchunks, part, Tm)) != BFGS_OK) return rc;
         hipLaunchKernelGGL(symmetrise, dim3(ceil_div((int64_t)cc, 256)), dim3(256), 0, h->stream, c, Tm, Om);
     } else {
         ProfScope ps(h, "proj_QtX");
@@ -1218,8 +1209,8 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
             hipLaunchKernelGGL((qtx_mfma<TQ, TS>), dim3(nchunks, nblk, nblk), dim3(256), 0, h->stream, n, c, c, Qp, X,
                                part, rows_per_chunk);
         }
-        hipLaunchKernelGGL(sum_chunks, dim3(ceil_div((int64_t)cc, 256)), dim3(256), 0, h->stream, (int64_t)cc,
-                           bf16_path ? qx_chunks : nchunks, part, Tm);
+        if ((rc = sum_partials(h->stream, (int64_t)cc, bf16_path ? qx_chunks : nchunks, part, Tm)) != BFGS_OK)
+            return rc;
     }
     if (!two_pass) {
         ProfScope ps(h, "omega_lu");
