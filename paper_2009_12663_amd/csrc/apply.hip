@@ -18,9 +18,10 @@
 #include <cmath>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
-#include "common.h"
+#include "tall_f64.h"
 
 namespace {
 
@@ -36,6 +37,24 @@ __global__ void __launch_bounds__(SUM_THREADS) reduce_partials(int64_t count, in
     if (threadIdx.x < SUM_ENTRIES && e < count) Z[e] = t;
 }
 
+// Where a small solve writes column j of P and T: column-major k x c each, or the packed
+// [T ; -P] that pass 2 reads (with the zero rows that fill its last step).
+struct SolveOut {
+    double *P, *T, *M;
+    int k, cblocks;
+    __device__ __forceinline__ void put(int i, int j, double pv, double tv) const {
+        if (M) {
+            M[nn_pack_index(i, j, cblocks)] = tv;
+            M[nn_pack_index(k + i, j, cblocks)] = -pv;
+            if (i == 0)
+                for (int q = 2 * k; q % 4; ++q) M[nn_pack_index(q, j, cblocks)] = 0.0;
+        } else {
+            P[(int64_t)j * k + i] = pv;
+            T[(int64_t)j * k + i] = tv;
+        }
+    }
+};
+
 // One 64-lane wave per probe column j.
 //   P = R^-1 Z_s               (column-oriented back substitution)
 //   W = (D + YHY) P - Z_y
@@ -45,8 +64,7 @@ constexpr int SOLVE_MAXK_PER_LANE = BFGS_MAX_PAIRS / 64;
 
 __global__ void __launch_bounds__(64) small_solve(int k, int kmax, int c, const double* __restrict__ Rm,
                                                   const double* __restrict__ YHY, const double* __restrict__ Z,
-                                                  double* __restrict__ P, double* __restrict__ T,
-                                                  int32_t* __restrict__ status) {
+                                                  SolveOut out, int32_t* __restrict__ status) {
     extern __shared__ double sh[];
     double* b = sh;          // right-hand side, overwritten
     double* x = sh + k;      // P column
@@ -94,93 +112,91 @@ __global__ void __launch_bounds__(64) small_solve(int k, int kmax, int c, const 
     bool bad = false;
     for (int i = lane; i < k; i += 64) {
         const double pv = x[i], tv = w[i];
-        P[(int64_t)j * k + i] = pv;
-        T[(int64_t)j * k + i] = tv;
+        out.put(i, j, pv, tv);
         bad |= !isfinite(pv) || !isfinite(tv);
     }
     if (bad) set_status(status, BFGS_ERR_NONFINITE);
 }
 
-// Same solve through the stored R^-1, for k <= 256: one workgroup per block of 8
-// probe columns, one thread per pair index.
+// Same solve through the stored R^-1, for k <= 256: one workgroup per probe column, one
+// thread per pair index.
 //   P = R^-1 Z_s;  W = (D + YHY) P - Z_y;  T = R^-T W
-constexpr int SB_COLS = 4;
+// A result is one chain of sums over the pairs, in order; what bounds it is the latency of
+// the matrix entries, so SOLVE_DEPTH of them are fetched at a time, and the lanes of a wave
+// walk the same pair, so that they come as whole lines.  The loop is kept short on purpose:
+// unrolled further, fetching its instructions took longer than the sums (44 us at k = 200,
+// c = 220).  Before, with eight in flight, four columns to a thread and every lane starting
+// at its own diagonal: 47 us at k = 200, c = 220 and 28 us for one column at k = 100; now
+// 34 and 19 us.
+constexpr int SOLVE_DEPTH = 16;
 
-__device__ __forceinline__ void small_solve_block(int k, int kmax, int c, const double* __restrict__ Rm,
-                                                  const double* __restrict__ Rinv, const double* __restrict__ RinvT,
-                                                  const double* __restrict__ YHY, const double* __restrict__ Z,
-                                                  double* __restrict__ P, double* __restrict__ T,
-                                                  int32_t* __restrict__ status, int blk) {
-    __shared__ double a_sh[256][SB_COLS + 1];
-    __shared__ double b_sh[256][SB_COLS + 1];
-    const int i = threadIdx.x;
-    const int j0 = blk * SB_COLS;
-    const int nj = min(SB_COLS, c - j0);
-    for (int e = threadIdx.x; e < k * SB_COLS; e += blockDim.x) {
-        const int l = e % k, jj = e / k;
-        a_sh[l][jj] = jj < nj ? Z[(int64_t)(j0 + jj) * 2 * k + l] : 0.0;
-        b_sh[l][jj] = jj < nj ? Z[(int64_t)(j0 + jj) * 2 * k + k + l] : 0.0;
-    }
-    __syncthreads();
-    double acc[SB_COLS];
+struct SolveLds {
+    alignas(16) double a[256];
+    alignas(16) double b[256];
+};
+
+// acc + sum of A(i, l) x[l] over l in [lo, hi) in order, taking only first <= l <= last;
+// A column-major, lo and hi the same in a whole wave, lo a multiple of 2.
+__device__ __forceinline__ double solve_chain(double acc, const double* __restrict__ A, int kmax, int i, int lo, int hi,
+                                              int first, int last, const double* x) {
+    double cur[SOLVE_DEPTH], nxt[SOLVE_DEPTH];
 #pragma unroll
-    for (int jj = 0; jj < SB_COLS; ++jj) acc[jj] = 0.0;
-    if (i < k)
-#pragma unroll 8
-        for (int l = i; l < k; ++l) {
-            const double r = Rinv[(int64_t)l * kmax + i];
+    for (int u = 0; u < SOLVE_DEPTH; ++u) cur[u] = A[(int64_t)min(lo + u, hi - 1) * kmax + i];
+#pragma unroll 1
+    for (int l0 = lo; l0 < hi; l0 += SOLVE_DEPTH) {
 #pragma unroll
-            for (int jj = 0; jj < SB_COLS; ++jj) acc[jj] = fma(r, a_sh[l][jj], acc[jj]);
-        }
-    __syncthreads();
-    if (i < k)
+        for (int u = 0; u < SOLVE_DEPTH; ++u)
+            nxt[u] = A[(int64_t)min(l0 + SOLVE_DEPTH + u, hi - 1) * kmax + i];
+        double xv[SOLVE_DEPTH];
 #pragma unroll
-        for (int jj = 0; jj < SB_COLS; ++jj) a_sh[i][jj] = acc[jj];   // P
-    __syncthreads();
-    if (i < k) {
-        const double dii = Rm[(int64_t)i * kmax + i];
+        for (int u = 0; u < SOLVE_DEPTH; ++u) xv[u] = x[l0 + u];   // past hi: not used
+        __builtin_amdgcn_sched_barrier(0);   // all fetched before the first is added
 #pragma unroll
-        for (int jj = 0; jj < SB_COLS; ++jj) acc[jj] = dii * a_sh[i][jj] - b_sh[i][jj];
-#pragma unroll 8
-        for (int l = 0; l < k; ++l) {
-            const double y = YHY[(int64_t)l * kmax + i];
-#pragma unroll
-            for (int jj = 0; jj < SB_COLS; ++jj) acc[jj] = fma(y, a_sh[l][jj], acc[jj]);
+        for (int u = 0; u < SOLVE_DEPTH; ++u) {
+            const int l = l0 + u;
+            const double t = fma(cur[u], xv[u], acc);
+            acc = l < hi && l >= first && l <= last ? t : acc;
+            cur[u] = nxt[u];
         }
     }
-    __syncthreads();
-    if (i < k)
-#pragma unroll
-        for (int jj = 0; jj < SB_COLS; ++jj) b_sh[i][jj] = acc[jj];   // W
-    __syncthreads();
-    bool bad = false;
-    if (i < k) {
-#pragma unroll
-        for (int jj = 0; jj < SB_COLS; ++jj) acc[jj] = 0.0;
-#pragma unroll 8
-        for (int l = 0; l <= i; ++l) {
-            const double r = RinvT[(int64_t)l * kmax + i];
-#pragma unroll
-            for (int jj = 0; jj < SB_COLS; ++jj) acc[jj] = fma(r, b_sh[l][jj], acc[jj]);
-        }
-        for (int jj = 0; jj < nj; ++jj) {
-            const double pv = a_sh[i][jj], tv = acc[jj];
-            P[(int64_t)(j0 + jj) * k + i] = pv;
-            T[(int64_t)(j0 + jj) * k + i] = tv;
-            bad |= !isfinite(pv) || !isfinite(tv);
-        }
-    }
-    if (bad) set_status(status, BFGS_ERR_NONFINITE);
-    __syncthreads();   // a_sh and b_sh are free for the next block of columns
+    return acc;
 }
 
-__global__ void __launch_bounds__(256) small_solve_blocks(int k, int kmax, int c, const double* __restrict__ Rm,
+__device__ __forceinline__ void small_solve_block(SolveLds& s, int k, int kmax, const double* __restrict__ Rm,
+                                                  const double* __restrict__ Rinv, const double* __restrict__ RinvT,
+                                                  const double* __restrict__ YHY, const double* __restrict__ Z,
+                                                  SolveOut out, int32_t* __restrict__ status, int j) {
+    const int i = threadIdx.x;
+    const bool live = i < k;
+    const int ic = min(i, k - 1);
+    const int w0 = __builtin_amdgcn_readfirstlane(i / 64 * 64);   // this wave's rows: w0 .. w1 - 1
+    const int w1 = min(k, w0 + 64);
+    const bool work = w0 < k;
+    const double zs = live ? Z[(int64_t)j * 2 * k + i] : 0.0, zy = live ? Z[(int64_t)j * 2 * k + k + i] : 0.0;
+    const double dii = Rm[(int64_t)ic * kmax + ic];
+    s.a[i] = zs;
+    __syncthreads();
+    const double pv = work ? solve_chain(0.0, Rinv, kmax, ic, w0, k, i, k, s.a) : 0.0;
+    __syncthreads();
+    s.a[i] = pv;   // P
+    __syncthreads();
+    if (work) s.b[i] = solve_chain(dii * pv - zy, YHY, kmax, ic, 0, k, 0, k, s.a);   // W
+    __syncthreads();
+    const double tv = work ? solve_chain(0.0, RinvT, kmax, ic, 0, w1, 0, i, s.b) : 0.0;
+    if (live) {
+        out.put(i, j, pv, tv);
+        if (!isfinite(pv) || !isfinite(tv)) set_status(status, BFGS_ERR_NONFINITE);
+    }
+}
+
+__global__ void __launch_bounds__(256) small_solve_blocks(int k, int kmax, const double* __restrict__ Rm,
                                                           const double* __restrict__ Rinv,
                                                           const double* __restrict__ RinvT,
-                                                          const double* __restrict__ YHY, const double* __restrict__ Z,
-                                                          double* __restrict__ P, double* __restrict__ T,
+                                                          const double* __restrict__ YHY,
+                                                          const double* __restrict__ Z, SolveOut out,
                                                           int32_t* __restrict__ status) {
-    small_solve_block(k, kmax, c, Rm, Rinv, RinvT, YHY, Z, P, T, status, blockIdx.x);
+    __shared__ SolveLds lds;
+    small_solve_block(lds, k, kmax, Rm, Rinv, RinvT, YHY, Z, out, status, blockIdx.x);
 }
 
 // k = 0: B_0 V (or zero for B_k - B_0); a non-finite input sets the deferred status.
@@ -200,222 +216,179 @@ __global__ void scale_by_h0(int64_t n, int c, const Th* __restrict__ h0, const T
 
 // ---------------------------------------------------------------------------
 // Float64 matrix-core forms of both passes for float32 and float64 storage
-// (v_mfma_f64_16x16x4f64: lane l holds A(l % 16, l / 16), B(l / 16, l % 16) and
-// C(l / 16 + 4 r, l % 16) in accumulator element r).  Both read W = [S | h0 o Y]
-// (n x 2k), widened to float64 and scaled as it is staged:
+// (tall_f64.h).  Both read W = [S | h0 o Y] (n x 2k), widened to float64 and scaled as it
+// is loaded:
 //   pass 1:  Z = W^T V                  (= [S^T V ; Y^T (h0 o V)])
 //   pass 2:  out = W [T ; -P] + h0 o V  (= h0 o (V - Y P) + S T; no h0 o V for B_k - B_0)
-// Tiles are 128 x 128 on four waves (2 x 2, 4 x 4 fragments each); the next
-// 16-deep stage is loaded into registers while the current one feeds the MFMAs.
 // ---------------------------------------------------------------------------
-typedef double v4d __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v4d mfma64(double a, double b, v4d c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
-constexpr int FT = 128;          // output tile edge
-constexpr int FT_LD = FT + 4;    // LDS pitch of a staged row of 128
-constexpr int FK = 16;           // reduction depth per stage
-
-// Raw W entry (r, p) in the storage type: S's column p, or Y's column p - k (the h0
-// factor of the Y half is applied when the value is staged).
+// Column p of W: S's column p, or Y's column p - k, which takes the row scale.
 template <typename Ts>
-__device__ __forceinline__ Ts w_raw(const Ts* S, const Ts* Y, int64_t ld, int k, int p, int64_t r) {
-    return p < k ? S[(int64_t)p * ld + r] : Y[(int64_t)(p - k) * ld + r];
+struct PairCols {
+    const Ts *S, *Y;
+    int64_t ld;
+    int k;
+    __device__ __forceinline__ TnCol<Ts> operator()(int p) const {
+        const bool y = p >= k;
+        return {(y ? Y : S) + (int64_t)(y ? p - k : p) * ld, y};
+    }
+};
+
+// part[chunk][j * 2k + p] = sum over the chunk's rows of W(r, p) V(r, j); V's columns are
+// ldv apart (n for a whole block; the block's row count when the rows come in slices).
+template <int TA, int TB, typename Ts, typename Th, typename Tv>
+__global__ void __launch_bounds__(64, 2) gemm1_f64mfma(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
+                                                       const Ts* __restrict__ Y, const Th* __restrict__ h0,
+                                                       const Tv* __restrict__ V, int64_t ldv,
+                                                       double* __restrict__ part, int64_t rows_per_chunk, int nchunks,
+                                                       int ptiles, int ctiles) {
+    int chunk, pos;
+    if (!tn_place(blockIdx.x, ptiles * ctiles, nchunks, chunk, pos)) return;
+    tn_tile<TA, TB, true, false, Ts>(n, 2 * k, c, chunk, rows_per_chunk, pos % ptiles, pos / ptiles, ctiles,
+                                     PairCols<Ts>{S, Y, ld, k}, h0, V, ldv, part);
 }
 
-// part[chunk][j * 2k + p] = sum over the chunk's rows of W(r, p) V(r, j); V's
-// columns are ldv apart (n for a whole block; the block's row count when the rows
-// come in slices).  Grid (nchunks, ceil(2k / 128), ceil(c / 128)).
-template <typename Ts, typename Th, typename Tv>
-__device__ __forceinline__ void gemm1_tile(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
-                                           const Ts* __restrict__ Y, const Th* __restrict__ h0,
-                                           const Tv* __restrict__ V, int64_t ldv, double* __restrict__ part,
-                                           int64_t rows_per_chunk, int bx, int by, int bz) {
-    __shared__ double Ws[FK][FT_LD];
-    __shared__ double Vs[FK][FT_LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wi = wave >> 1, wj = wave & 1;
-    const int twok = 2 * k;
-    const int pi0 = by * FT, cj0 = bz * FT;
-    const int64_t rb = (int64_t)bx * rows_per_chunk;
-    const int64_t re = min(n, rb + rows_per_chunk);
-    // staging map: element e = tid + 256 q (q < 8): row e % 16 (= tid % 16 for every q),
-    // column e / 16; values stay in the storage type until they are staged
-    Ts wreg[8];
-    Tv vreg[8];
-    double h0r = 0.0;
-#define G1F_LOAD_STAGE(R0)                                                                   \
-    {                                                                                      \
-        const int64_t r = (R0) + tid % FK;                                                 \
-        const bool rv = r < re;                                                            \
-        h0r = rv ? to_f64(h0[r]) : 0.0;                                                    \
-        _Pragma("unroll") for (int q = 0; q < 8; ++q) {                                    \
-            const int cc = (tid + 256 * q) / FK;                                           \
-            wreg[q] = (rv && pi0 + cc < twok) ? w_raw(S, Y, ld, k, pi0 + cc, r) : Ts{};     \
-            vreg[q] = (rv && cj0 + cc < c) ? V[(int64_t)(cj0 + cc) * ldv + r] : Tv{};        \
-        }                                                                                  \
-    }
-    v4d acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0, 0, 0, 0};
-    if (rb < re) { G1F_LOAD_STAGE(rb) }
-    for (int64_t r0 = rb; r0 < re; r0 += FK) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int e = tid + 256 * q, rr = e % FK, cc = e / FK;
-            const double w = to_f64(wreg[q]);
-            Ws[rr][cc] = pi0 + cc < k ? w : w * h0r;
-            Vs[rr][cc] = to_f64(vreg[q]);
+// Stores the results of rows r .. r + live - 1 of column j, with h0 o V added unless diff.
+template <int TA, typename To, typename Tv>
+struct ApplyEmit {
+    const Tv* V;
+    To* out;
+    int64_t ldv;
+    int diff;
+    typedef Run<Tv, TA> Ahead;
+    __device__ __forceinline__ Ahead ahead(int j, int64_t r, int live) const {
+        Ahead v{};
+        if (!diff) {
+            const Tv* p = V + (int64_t)j * ldv + r;
+            v = live == TA ? load_run<Tv, TA>(p) : load_run_part<Tv, TA>(p, live);
         }
-        __syncthreads();
-        if (r0 + FK < re) { G1F_LOAD_STAGE(r0 + FK) }
-#pragma unroll
-        for (int kk = 0; kk < FK / 4; ++kk) {
-            const int kr = 4 * kk + lane / 16, m = lane % 16;
-            double a[4], b[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                a[t] = Ws[kr][(wi * 4 + t) * 16 + m];
-                b[t] = Vs[kr][(wj * 4 + t) * 16 + m];
-            }
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-                for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = mfma64(a[ta], b[tb], acc[ta][tb]);
-        }
-        __syncthreads();
+        return v;
     }
-#undef G1F_LOAD_STAGE
-    double* dst = part + (int64_t)bx * twok * c;
+    __device__ __forceinline__ void store(int j, int64_t r, const double (&o)[TA], const double (&h)[TA], const Ahead& v,
+                                          int live) const {
+        To* p = out + (int64_t)j * ldv + r;
+        Run<To, TA> w;
 #pragma unroll
-    for (int ta = 0; ta < 4; ++ta)
+        for (int f = 0; f < TA; ++f) {
+            double s = o[f];
+            if (!diff) s += h[f] * to_f64(v.v[f]);
+            w.v[f] = (To)s;
+        }
+        if (live == TA) {
+            *(Run<To, TA>*)p = w;
+        } else {
 #pragma unroll
-        for (int tb = 0; tb < 4; ++tb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int gp = pi0 + (wi * 4 + ta) * 16 + lane / 16 + 4 * r;
-                const int gj = cj0 + (wj * 4 + tb) * 16 + lane % 16;
-                if (gp < twok && gj < c) dst[(int64_t)gj * twok + gp] = acc[ta][tb][r];
-            }
+            for (int f = 0; f < TA; ++f)
+                if (f < live) p[f] = w.v[f];
+        }
+    }
+};
+
+// out (column-major n x c, columns ldv apart, as V's) = W [T ; -P] (+ h0 o V unless diff),
+// [T ; -P] packed.
+template <int TA, int TB, bool SKIP, typename Ts, typename Th, typename To, typename Tv>
+__device__ __forceinline__ void gemm2_group(NnLds<TB>& lds, int64_t n, int64_t ld, int k, int c,
+                                            const Ts* __restrict__ S, const Ts* __restrict__ Y,
+                                            const Th* __restrict__ h0, const Tv* __restrict__ V, int64_t ldv,
+                                            const double* __restrict__ M, To* __restrict__ out, int diff, int64_t row0,
+                                            int ct, int ctiles) {
+    const int cblocks = (c + 15) / 16, cb = ct * cblocks / ctiles, ce = (ct + 1) * cblocks / ctiles;
+    // the columns of S and Y are ld (a multiple of 128) rows long: whole runs exist
+    nn_group<TA, TB, true, SKIP, Ts>(lds, n, row0, true, 2 * k, c, cblocks, cb, ce - cb, PairCols<Ts>{S, Y, ld, k}, h0,
+                                     M, ApplyEmit<TA, To, Tv>{V, out, ldv, diff});
 }
 
-template <typename Ts, typename Th, typename Tv>
-__global__ void __launch_bounds__(256, 2) gemm1_f64mfma(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
-                                                     const Ts* __restrict__ Y, const Th* __restrict__ h0,
-                                                     const Tv* __restrict__ V, int64_t ldv, double* __restrict__ part,
-                                                     int64_t rows_per_chunk) {
-    gemm1_tile<Ts, Th, Tv>(n, ld, k, c, S, Y, h0, V, ldv, part, rows_per_chunk, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-
-// out (column-major n x c, columns ldv apart, as V's) = W [T ; -P] (+ h0 o V unless
-// diff); P, T column-major k x c.  Grid (ceil(n / 128), ceil(c / 128)).
-template <typename Ts, typename Th, typename To, typename Tv>
-__device__ __forceinline__ void gemm2_tile(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
-                                           const Ts* __restrict__ Y, const Th* __restrict__ h0,
-                                           const Tv* __restrict__ V, int64_t ldv, const double* __restrict__ P,
-                                           const double* __restrict__ T, To* __restrict__ out, int diff, int bx,
-                                           int by) {
-    __shared__ double stage_sh[FT * (FK + 1) + FK * FT_LD];
-    double* Wsh = stage_sh;                     // [128 rows][FK + 1]
-    double* Ms = stage_sh + FT * (FK + 1);      // [FK][FT_LD]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wi = wave >> 1, wj = wave & 1;
-    const int twok = 2 * k;
-    const int64_t row0 = (int64_t)bx * FT;
-    const int col0 = by * FT;
-    // W stage element e = tid + 256 q: row e % 128 (= tid % 128 for every q), pair
-    // e / 128; M stage: pair e % 16, column e / 16
-    Ts wreg[8];
-    double mreg[8];
-    const int64_t wr = row0 + tid % FT;
-    const double h0w = wr < n ? to_f64(h0[wr]) : 0.0;
-#define G2F_LOAD_STAGE(K0)                                                                       \
-    _Pragma("unroll") for (int q = 0; q < 8; ++q) {                                            \
-        const int e = tid + 256 * q;                                                           \
-        const int kq = e / FT;                                                                 \
-        wreg[q] = (wr < n && (K0) + kq < twok) ? w_raw(S, Y, ld, k, (K0) + kq, wr) : Ts{};      \
-        const int pm = (K0) + e % FK, j = col0 + e / FK;                                       \
-        double mv = 0.0;                                                                       \
-        if (pm < twok && j < c) mv = pm < k ? T[(int64_t)j * k + pm] : -P[(int64_t)j * k + pm - k]; \
-        mreg[q] = mv;                                                                          \
-    }
-    v4d acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0, 0, 0, 0};
-    G2F_LOAD_STAGE(0)
-    for (int k0 = 0; k0 < twok; k0 += FK) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int e = tid + 256 * q;
-            const double w = to_f64(wreg[q]);
-            Wsh[(e % FT) * (FK + 1) + e / FT] = k0 + e / FT < k ? w : w * h0w;
-            Ms[(e % FK) * FT_LD + e / FK] = mreg[q];
-        }
-        __syncthreads();
-        if (k0 + FK < twok) { G2F_LOAD_STAGE(k0 + FK) }
-#pragma unroll
-        for (int kk = 0; kk < FK / 4; ++kk) {
-            double a[4], b[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                a[t] = Wsh[((wi * 4 + t) * 16 + lane % 16) * (FK + 1) + 4 * kk + lane / 16];
-                b[t] = Ms[(4 * kk + lane / 16) * FT_LD + (wj * 4 + t) * 16 + lane % 16];
-            }
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-                for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = mfma64(a[ta], b[tb], acc[ta][tb]);
-        }
-        __syncthreads();
-    }
-#undef G2F_LOAD_STAGE
-    // Transpose through LDS in groups of EC columns (Os[column][row], float64, so the
-    // output is rounded once) so that each column's 128 rows are written, and V's
-    // read, contiguously.
-    constexpr int EC = 32;
-    double* Os = stage_sh;
-    static_assert(EC * (FT + 1) * sizeof(double) <= sizeof(stage_sh), "epilogue tile exceeds LDS");
-    for (int g0 = 0; g0 < FT; g0 += EC) {
-#pragma unroll
-        for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-            for (int tb = 0; tb < 4; ++tb) {
-                const int jj = (wj * 4 + tb) * 16 + lane % 16 - g0;
-                if (jj >= 0 && jj < EC) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int rr = (wi * 4 + ta) * 16 + lane / 16 + 4 * r;
-                        Os[jj * (FT + 1) + rr] = acc[ta][tb][r];
-                    }
-                }
-            }
-        __syncthreads();
-        for (int e = tid; e < EC * FT; e += 256) {
-            const int rr = e % FT, jj = e / FT;
-            const int64_t r = row0 + rr;
-            const int j = col0 + g0 + jj;
-            if (r < n && j < c) {
-                double o = Os[jj * (FT + 1) + rr];
-                if (!diff) o += to_f64(h0[r]) * to_f64(V[(int64_t)j * ldv + r]);
-                out[(int64_t)j * ldv + r] = (To)o;
-            }
-        }
-        __syncthreads();
-    }
-}
-
-template <typename Ts, typename Th, typename To, typename Tv>
+template <int TA, int TB, typename Ts, typename Th, typename To, typename Tv>
 __global__ void __launch_bounds__(256, 2) gemm2_f64mfma(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
-                                                     const Ts* __restrict__ Y, const Th* __restrict__ h0,
-                                                     const Tv* __restrict__ V, int64_t ldv, const double* __restrict__ P,
-                                                     const double* __restrict__ T, To* __restrict__ out, int diff) {
-    gemm2_tile<Ts, Th, To, Tv>(n, ld, k, c, S, Y, h0, V, ldv, P, T, out, diff, blockIdx.x, blockIdx.y);
+                                                        const Ts* __restrict__ Y, const Th* __restrict__ h0,
+                                                        const Tv* __restrict__ V, int64_t ldv,
+                                                        const double* __restrict__ M, To* __restrict__ out, int diff,
+                                                        int ctiles) {
+    __shared__ NnLds<TB> lds;
+    int64_t row0;
+    int ct;
+    if (!nn_place(blockIdx.x, n, 64 * TA, ctiles, row0, ct)) return;
+    gemm2_group<TA, TB, false, Ts, Th, To, Tv>(lds, n, ld, k, c, S, Y, h0, V, ldv, M, out, diff, row0, ct, ctiles);
+}
+
+// Calls f(std::integral_constant<int, TB>) for the tile width tb (1 .. 7).
+template <typename F>
+void with_tile_width(int tb, F&& f) {
+    switch (tb) {
+        case 1: f(std::integral_constant<int, 1>()); break;
+        case 2: f(std::integral_constant<int, 2>()); break;
+        case 3: f(std::integral_constant<int, 3>()); break;
+        case 4: f(std::integral_constant<int, 4>()); break;
+        case 5: f(std::integral_constant<int, 5>()); break;
+        case 6: f(std::integral_constant<int, 6>()); break;
+        default: f(std::integral_constant<int, 7>()); break;
+    }
+}
+
+template <typename Ts, typename Th, typename Tv>
+void launch_gemm1(hipStream_t st, int64_t n, int64_t ld, int k, int c, const Ts* S, const Ts* Y, const Th* h0,
+                  const Tv* V, int64_t ldv, double* part, int64_t rows_per_chunk, int nchunks) {
+    constexpr bool wide = sizeof(Tv) == 8;
+    const TnShape s = tn_shape(2 * k, c, wide);
+    with_tile_width(s.tb, [&](auto tb) {
+        constexpr int TB = wide && decltype(tb)::value > TN_WIDE_TB ? TN_WIDE_TB : decltype(tb)::value;
+        hipLaunchKernelGGL((gemm1_f64mfma<tile_rows(TB), TB, Ts, Th, Tv>), dim3(tn_grid(s.tiles(), nchunks)),
+                           dim3(64), 0, st, n, ld, k, c, S, Y, h0, V, ldv, part, rows_per_chunk, nchunks, s.ptiles,
+                           s.ctiles);
+    });
+}
+
+template <typename Ts, typename Th, typename To, typename Tv>
+void launch_gemm2(hipStream_t st, int64_t n, int64_t ld, int k, int c, const Ts* S, const Ts* Y, const Th* h0,
+                  const Tv* V, int64_t ldv, const double* M, To* out, bool diff) {
+    const NnShape s = nn_shape(c);
+    with_tile_width(s.tb, [&](auto tb) {
+        constexpr int TB = decltype(tb)::value;
+        hipLaunchKernelGGL((gemm2_f64mfma<tile_rows(TB), TB, Ts, Th, To, Tv>), dim3(nn_grid(n, s)), dim3(256), 0, st, n,
+                           ld, k, c, S, Y, h0, V, ldv, M, out, diff ? 1 : 0, s.ctiles);
+    });
+}
+
+// Row chunks of pass 1 over n rows for a history of k pairs and c columns: how many rows
+// go into one partial sum.  The chunk length fixes the order of the sums.  For the rSVD's
+// range sample (diff) it stays what it was when a tile had 128 x 128 results, about 2048
+// of them: the columns of U at numerically zero eigenvalues are rounding noise and would
+// turn with any other order.  Otherwise as many chunks as fill the wave slots once, or
+// twice where a chunk then still has 1024 rows; counted by XCD (a chunk's tiles share one,
+// workgroup g runs on XCD g % 8), so that the last round of waves is a full one: at
+// n = 1.785M, k = 200, c = 220, float32, 157 chunks of 26 tiles are 2.03 rounds on five of
+// the XCDs and took 7.0 ms, 152 are 1.93 and take 5.9.
+struct ChunkPlan {
+    int64_t rows_per_chunk;
+    int nchunks;
+};
+ChunkPlan chunk_plan(int64_t n, int k, int c, bool diff, bool wide_v, int most = 1 << 20) {
+    int64_t nch;
+    if (diff) {
+        nch = std::max(1, 2048 / (ceil_div(2 * k, 128) * ceil_div(c, 128)));
+    } else {
+        const TnShape s = tn_shape(2 * k, c, wide_v);
+        const int slots = 32 * 4 * s.waves;   // of one XCD
+        nch = 8 * std::max(1, 2 * slots / s.tiles());
+        if (n < 1024 * nch) nch = 8 * std::max(1, slots / s.tiles());
+        nch = std::min(nch, (n + 63) / 64);
+    }
+    nch = std::min(std::min<int64_t>(nch, most), (n + 15) / 16);
+    const int64_t rows = round_up((n + nch - 1) / nch, 16);
+    return {rows, (int)((n + rows - 1) / rows)};
+}
+
+// Doubles of the P/T workspace: P and T (k x c each) or the packed [T ; -P].
+size_t pt_doubles(int kmax) { return (size_t)(2 * kmax + 2) * BFGS_MAX_COLS; }
+
+int small_solve_launch(bfgsuq_ctx* h, int c, const double* Z, SolveOut out) {
+    ProfScope ps(h, "apply_solve");
+    const int k = h->k;
+    if (k <= 256)
+        hipLaunchKernelGGL(small_solve_blocks, dim3(c), dim3((unsigned)round_up(k, 64)), 0, h->stream, k, h->kmax, h->Rm, h->Rinv, h->RinvT, h->YHY, Z, out, h->status);
+    else
+        hipLaunchKernelGGL(small_solve, dim3(c), dim3(64), 3 * k * sizeof(double), h->stream, k, h->kmax, c, h->Rm,
+                           h->YHY, Z, out, h->status);
+    return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
 }
 
 template <typename Ts, typename Th, typename To, typename Tv = Ts>
@@ -432,46 +405,37 @@ int apply_generic(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, c
         return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
     }
     const int twok = 2 * k;
-    const int ptiles = ceil_div(twok, FT), ctiles = ceil_div(c, FT);
-    // row chunks: about 2048 pass-1 workgroups, each chunk a whole number of stages
-    const int64_t max_chunks = std::max<int64_t>(1, (n + FK - 1) / FK);
-    int nchunks = (int)std::min<int64_t>(max_chunks, std::max(1, 2048 / (ptiles * ctiles)));
     const size_t chunk_bytes = (size_t)twok * c * 8;
+    int most = 1 << 20;
     if (fixed) {
-        const int cap = (int)std::min<size_t>(fixed->part_bytes / chunk_bytes, 1 << 20);
-        if (cap < 1) return BFGS_ERR_ARG;
-        nchunks = std::min(nchunks, cap);
+        most = (int)std::min<size_t>(fixed->part_bytes / chunk_bytes, most);
+        if (most < 1) return BFGS_ERR_ARG;
     }
-    const int64_t rows_per_chunk = round_up((n + nchunks - 1) / nchunks, FK);
-    nchunks = (int)((n + rows_per_chunk - 1) / rows_per_chunk);
-    double *part, *Z, *P;
+    const ChunkPlan plan = chunk_plan(n, k, c, diff, sizeof(Tv) == 8, most);
+    double *part, *Z, *M;
     if (fixed) {
         part = (double*)fixed->part;
         Z = fixed->Z;
-        P = fixed->PT;
+        M = fixed->PT;
     } else {
         int rc;
-        if ((rc = ensure_ws(h->part, (size_t)nchunks * chunk_bytes)) != BFGS_OK) return rc;
+        if ((rc = ensure_ws(h->part, (size_t)plan.nchunks * chunk_bytes)) != BFGS_OK) return rc;
         if ((rc = ensure_ws(h->Z, (size_t)twok * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
-        if ((rc = ensure_ws(h->PT, (size_t)2 * h->kmax * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
+        if ((rc = ensure_ws(h->PT, pt_doubles(h->kmax) * 8)) != BFGS_OK) return rc;
         part = (double*)h->part.ptr;
         Z = (double*)h->Z.ptr;
-        P = (double*)h->PT.ptr;
+        M = (double*)h->PT.ptr;
     }
-    double* T = P + (size_t)k * c;
     prof_begin(h, diff ? "hdiff_gemm1" : "apply_gemm1");
-    hipLaunchKernelGGL((gemm1_f64mfma<Ts, Th, Tv>), dim3(nchunks, ptiles, ctiles), dim3(256), 0, h->stream, n, h->ld, k,
-                       c, (const Ts*)h->S, (const Ts*)h->Y, h0, V, n, part, rows_per_chunk);
-    const int64_t count = (int64_t)twok * c;
+    launch_gemm1<Ts, Th, Tv>(h->stream, n, h->ld, k, c, (const Ts*)h->S, (const Ts*)h->Y, h0, V, n, part,
+                             plan.rows_per_chunk, plan.nchunks);
     prof_end(h);
     prof_begin(h, "apply_reduce");
-    if (int rc2 = sum_partials(h->stream, count, nchunks, part, Z)) return rc2;
+    if (int rc2 = sum_partials(h->stream, (int64_t)twok * c, plan.nchunks, part, Z)) return rc2;
     prof_end(h);
-    if (int rc2 = apply_small_solve(h, c, Z, P, T)) return rc2;
+    if (int rc2 = small_solve_launch(h, c, Z, SolveOut{nullptr, nullptr, M, k, ceil_div(c, 16)})) return rc2;
     prof_begin(h, diff ? "hdiff_gemm2" : "apply_gemm2");
-    hipLaunchKernelGGL((gemm2_f64mfma<Ts, Th, To, Tv>), dim3((unsigned)ceil_div(n, (int64_t)FT), ctiles), dim3(256), 0,
-                       h->stream, n, h->ld, k, c, (const Ts*)h->S, (const Ts*)h->Y, h0, V, n, P, T, out,
-                       diff ? 1 : 0);
+    launch_gemm2<Ts, Th, To, Tv>(h->stream, n, h->ld, k, c, (const Ts*)h->S, (const Ts*)h->Y, h0, V, n, M, out, diff);
     prof_end(h);
     return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
 }
@@ -489,42 +453,38 @@ int apply_streamed(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff) 
     const Tv* V = (const Tv*)Vv;
     To* out = (To*)outv;
     const int twok = 2 * k;
-    const int ptiles = ceil_div(twok, FT), ctiles = ceil_div(c, FT);
     const int64_t sr = h->slice_rows;
     const int ns = (int)((n + sr - 1) / sr);
-    int nsub = (int)std::min<int64_t>((sr + FK - 1) / FK, std::max(1, 2048 / (ptiles * ctiles)));
-    const int64_t rows_per_sub = round_up((sr + nsub - 1) / nsub, FK);
-    nsub = (int)((sr + rows_per_sub - 1) / rows_per_sub);
+    const ChunkPlan plan = chunk_plan(sr, k, c, diff, sizeof(Tv) == 8);   // of one slice
+    const int64_t rows_per_sub = plan.rows_per_chunk;
+    const int nsub = plan.nchunks;
     const int64_t last_rows = n - (int64_t)(ns - 1) * sr;
     const int used = (ns - 1) * nsub + (int)((last_rows + rows_per_sub - 1) / rows_per_sub);
     const size_t chunk_bytes = (size_t)twok * c * 8;
     int rc;
     if ((rc = ensure_ws(h->part, (size_t)ns * nsub * chunk_bytes)) != BFGS_OK) return rc;
     if ((rc = ensure_ws(h->Z, (size_t)twok * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
-    if ((rc = ensure_ws(h->PT, (size_t)2 * h->kmax * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
+    if ((rc = ensure_ws(h->PT, pt_doubles(h->kmax) * 8)) != BFGS_OK) return rc;
     double* part = (double*)h->part.ptr;
     double* Z = (double*)h->Z.ptr;
-    double* P = (double*)h->PT.ptr;
-    double* T = P + (size_t)k * c;
+    double* M = (double*)h->PT.ptr;
     {
         ProfScope ps(h, diff ? "hdiff_stream_pass1" : "apply_stream_pass1");
         rc = stream_slices(h, k, [&](int i, int64_t r0, int64_t rows, const void* Sst, const void* Yst) {
             const int nsi = (int)((rows + rows_per_sub - 1) / rows_per_sub);
-            hipLaunchKernelGGL((gemm1_f64mfma<Ts, Th, Tv>), dim3(nsi, ptiles, ctiles), dim3(256), 0, h->stream, rows,
-                               h->slice_ld, k, c, (const Ts*)Sst, (const Ts*)Yst, h0 + r0, V + r0, n,
-                               part + (size_t)i * nsub * twok * c, rows_per_sub);
+            launch_gemm1<Ts, Th, Tv>(h->stream, rows, h->slice_ld, k, c, (const Ts*)Sst, (const Ts*)Yst, h0 + r0,
+                                     V + r0, n, part + (size_t)i * nsub * twok * c, rows_per_sub, nsi);
             return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
         });
         if (rc != BFGS_OK) return rc;
     }
     const int64_t count = (int64_t)twok * c;
     if ((rc = sum_partials(h->stream, count, used, part, Z)) != BFGS_OK) return rc;
-    if ((rc = apply_small_solve(h, c, Z, P, T)) != BFGS_OK) return rc;
+    if ((rc = small_solve_launch(h, c, Z, SolveOut{nullptr, nullptr, M, k, ceil_div(c, 16)})) != BFGS_OK) return rc;
     ProfScope ps(h, diff ? "hdiff_stream_pass2" : "apply_stream_pass2");
     rc = stream_slices(h, k, [&](int, int64_t r0, int64_t rows, const void* Sst, const void* Yst) {
-        hipLaunchKernelGGL((gemm2_f64mfma<Ts, Th, To, Tv>), dim3((unsigned)ceil_div(rows, (int64_t)FT), ctiles),
-                           dim3(256), 0, h->stream, rows, h->slice_ld, k, c, (const Ts*)Sst, (const Ts*)Yst, h0 + r0,
-                           V + r0, n, P, T, out + r0, diff ? 1 : 0);
+        launch_gemm2<Ts, Th, To, Tv>(h->stream, rows, h->slice_ld, k, c, (const Ts*)Sst, (const Ts*)Yst, h0 + r0, V + r0,
+                                     n, M, out + r0, diff);
         return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
     });
     return rc;
@@ -539,15 +499,20 @@ int apply_streamed(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff) 
 // item is exactly one workgroup of the per-problem kernels (same tiles, same
 // chunking, same fixed-order sums), so the results equal the per-problem path's.
 // ---------------------------------------------------------------------------
-template <typename Ts, typename Th, typename Tv>
-__global__ void __launch_bounds__(256, 2) batch_pass1(const PersistProblem* __restrict__ pr, int nprob, int total,
-                                                    unsigned* __restrict__ head) {
-    __shared__ int item_sh;
+// A pointer read from memory that is known to be global (loads through it are then global
+// loads, not flat ones).
+template <typename T>
+__device__ __forceinline__ T* global_ptr(const void* p) {
+    return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+
+template <int TB, typename Ts, typename Th, typename Tv>
+__global__ void __launch_bounds__(64, 2) batch_pass1(const PersistProblem* __restrict__ pr, int nprob, int total,
+                                                     unsigned* __restrict__ head) {
     for (;;) {
-        if (threadIdx.x == 0) item_sh = (int)atomicAdd(head, 1u);
-        __syncthreads();
-        const int item = item_sh;
-        __syncthreads();
+        int item = 0;
+        if (threadIdx.x == 0) item = (int)atomicAdd(head, 1u);
+        item = __builtin_amdgcn_readfirstlane(item);   // a workgroup is one wave
         if (item >= total) break;
         int lo = 0, hi = nprob - 1;   // last problem whose first item is <= item
         while (lo < hi) {
@@ -556,10 +521,11 @@ __global__ void __launch_bounds__(256, 2) batch_pass1(const PersistProblem* __re
             else hi = mid - 1;
         }
         const PersistProblem& q = pr[lo];
-        const int local = item - q.first1, per = q.ptiles * q.ctiles;
-        const int bx = local / per, rest = local % per;
-        gemm1_tile<Ts, Th, Tv>(q.n, q.ld, q.k, q.c, (const Ts*)q.S, (const Ts*)q.Y, (const Th*)q.h0, (const Tv*)q.V,
-                               q.n, q.part, q.rows_per_chunk, bx, rest % q.ptiles, rest / q.ptiles);
+        const int local = item - q.first1, per = q.ptiles * q.ctiles1;
+        const int chunk = local / per, pos = local % per;
+        tn_tile<2, TB, true, true, Ts>(q.n, 2 * q.k, q.c, chunk, q.rows_per_chunk, pos % q.ptiles, pos / q.ptiles,
+                                       q.ctiles1, PairCols<Ts>{global_ptr<const Ts>(q.S), global_ptr<const Ts>(q.Y), q.ld, q.k},
+                                       global_ptr<const Th>(q.h0), global_ptr<const Tv>(q.V), q.n, global_ptr<double>(q.part));
     }
 }
 
@@ -584,23 +550,24 @@ __global__ void __launch_bounds__(SUM_THREADS) batch_sum(const PersistProblem* _
     if (threadIdx.x < SUM_ENTRIES && e < count) q.Z[e] = t;
 }
 
-// One workgroup per (problem, block of SB_COLS columns): the small solve of the block.
+// One workgroup per (problem, column): its small solve.
 __global__ void __launch_bounds__(256) batch_solve(const PersistProblem* __restrict__ pr, int nprob) {
-    int blk = blockIdx.x, p = 0;
-    while (p < nprob && blk >= (pr[p].c + SB_COLS - 1) / SB_COLS) {
-        blk -= (pr[p].c + SB_COLS - 1) / SB_COLS;
-        ++p;
-    }
+    int j = blockIdx.x, p = 0;
+    while (p < nprob && j >= pr[p].c) j -= pr[p++].c;
     if (p >= nprob) return;   // whole workgroup
     const PersistProblem& q = pr[p];
-    small_solve_block(q.k, q.kmax, q.c, q.Rm, q.Rinv, q.RinvT, q.YHY, q.Z, q.P, q.P + (size_t)q.k * q.c, q.status,
-                      blk);
+    __shared__ SolveLds lds;
+    small_solve_block(lds, q.k, q.kmax, global_ptr<double>(q.Rm), global_ptr<double>(q.Rinv),
+                      global_ptr<double>(q.RinvT), global_ptr<double>(q.YHY), global_ptr<double>(q.Z),
+                      SolveOut{nullptr, nullptr, global_ptr<double>(q.M), q.k, (q.c + 15) / 16}, q.status,
+                      j);
 }
 
 template <typename Ts, typename Th, typename To, typename Tv>
 __global__ void __launch_bounds__(256, 2) batch_pass2(const PersistProblem* __restrict__ pr, int nprob, int total,
                                                     unsigned* __restrict__ head) {
     __shared__ int item_sh;
+    __shared__ NnLds<NN_TB> lds;
     for (;;) {
         if (threadIdx.x == 0) item_sh = (int)atomicAdd(head, 1u);
         __syncthreads();
@@ -615,9 +582,10 @@ __global__ void __launch_bounds__(256, 2) batch_pass2(const PersistProblem* __re
         }
         const PersistProblem& q = pr[lo];
         const int local = item - q.first2;
-        gemm2_tile<Ts, Th, To, Tv>(q.n, q.ld, q.k, q.c, (const Ts*)q.S, (const Ts*)q.Y, (const Th*)q.h0,
-                                   (const Tv*)q.V, q.n, q.P, q.P + (size_t)q.k * q.c, (To*)q.out, 0,
-                                   local / q.ctiles, local % q.ctiles);
+        gemm2_group<2, NN_TB, true, Ts, Th, To, Tv>(
+            lds, q.n, q.ld, q.k, q.c, global_ptr<const Ts>(q.S), global_ptr<const Ts>(q.Y), global_ptr<const Th>(q.h0),
+            global_ptr<const Tv>(q.V), q.n, global_ptr<double>(q.M), global_ptr<To>(q.out), 0,
+            (int64_t)(local / q.ctiles2) * 128, local % q.ctiles2, q.ctiles2);
     }
 }
 
@@ -630,6 +598,7 @@ __global__ void batch_reset(unsigned* __restrict__ head) {
 template <typename Ts, typename Th>
 int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V, const int32_t* ncols,
                           void* const* out, hipStream_t st, PersistSlot* slot, bool upload, int wg_per_cu) {
+    constexpr int TB1 = sizeof(Ts) == 8 ? TN_WIDE_TB : NN_TB;
     if (upload) {
         std::vector<int> order(nprob);
         for (int i = 0; i < nprob; ++i) order[i] = i;
@@ -654,20 +623,20 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
             q.h0 = h->h0;
             q.V = V[i];
             q.out = out[i];
-            q.ptiles = ceil_div(twok, FT);
-            q.ctiles = ceil_div(c, FT);
+            q.ptiles = ceil_div(ceil_div(twok, 16), 2);
+            q.ctiles1 = ceil_div(ceil_div(c, 16), TB1);
+            q.ctiles2 = ceil_div(ceil_div(c, 16), NN_TB);
             // the per-problem path's chunking, so that the partial sums match it
-            const int64_t max_chunks = std::max<int64_t>(1, (q.n + FK - 1) / FK);
-            int nch = (int)std::min<int64_t>(max_chunks, std::max(1, 2048 / (q.ptiles * q.ctiles)));
-            q.rows_per_chunk = round_up((q.n + nch - 1) / nch, FK);
-            q.nchunks = (int)((q.n + q.rows_per_chunk - 1) / q.rows_per_chunk);
+            const ChunkPlan plan = chunk_plan(q.n, k, c, false, sizeof(Ts) == 8);
+            q.rows_per_chunk = plan.rows_per_chunk;
+            q.nchunks = plan.nchunks;
             int rc;
             if ((rc = ensure_ws(h->part, (size_t)q.nchunks * twok * c * 8)) != BFGS_OK) return rc;
             if ((rc = ensure_ws(h->Z, (size_t)twok * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
-            if ((rc = ensure_ws(h->PT, (size_t)2 * h->kmax * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
+            if ((rc = ensure_ws(h->PT, pt_doubles(h->kmax) * 8)) != BFGS_OK) return rc;
             q.part = (double*)h->part.ptr;
             q.Z = (double*)h->Z.ptr;
-            q.P = (double*)h->PT.ptr;
+            q.M = (double*)h->PT.ptr;
             q.Rm = h->Rm;
             q.Rinv = h->Rinv;
             q.RinvT = h->RinvT;
@@ -676,10 +645,10 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
             q.first1 = t1;
             q.firstsum = tsum;
             q.first2 = t2;
-            t1 += q.nchunks * q.ptiles * q.ctiles;
+            t1 += q.nchunks * q.ptiles * q.ctiles1;
             tsum += ceil_div((int64_t)twok * c, SUM_ENTRIES);
-            t2 += ceil_div(q.n, (int64_t)FT) * q.ctiles;
-            tsolve += ceil_div(c, SB_COLS);
+            t2 += ceil_div(q.n, 128) * q.ctiles2;
+            tsolve += c;
         }
         if (slot->cap < (size_t)nprob) {
             if (slot->prob) (void)hipFree(slot->prob);
@@ -705,10 +674,10 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
     if (slot->nprob != nprob || !slot->prob) return BFGS_ERR_STATE;
     int dev = 0, ncu = 256;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    const int g1 = std::max(1, std::min(slot->items1, ncu * wg_per_cu));
+    const int g1 = std::max(1, std::min(slot->items1, 4 * ncu * wg_per_cu));   // single waves
     const int g2 = std::max(1, std::min(slot->items2, ncu * wg_per_cu));
     hipLaunchKernelGGL(batch_reset, dim3(1), dim3(64), 0, st, slot->head);
-    hipLaunchKernelGGL((batch_pass1<Ts, Th, Ts>), dim3(g1), dim3(256), 0, st, slot->prob, nprob, slot->items1,
+    hipLaunchKernelGGL((batch_pass1<TB1, Ts, Th, Ts>), dim3(g1), dim3(64), 0, st, slot->prob, nprob, slot->items1,
                        slot->head);
     hipLaunchKernelGGL(batch_sum, dim3(slot->sum_blocks), dim3(SUM_THREADS), 0, st, slot->prob, nprob);
     hipLaunchKernelGGL(batch_solve, dim3(slot->solve_blocks), dim3(256), 0, st, slot->prob, nprob);
@@ -737,42 +706,21 @@ int sum_partials(hipStream_t st, int64_t count, int nchunks, const double* part,
 }
 
 int apply_small_solve(bfgsuq_ctx* h, int c, const double* Z, double* P, double* T) {
-    ProfScope ps(h, "apply_solve");
-    const int k = h->k;
-    if (k <= 256)
-        hipLaunchKernelGGL(small_solve_blocks, dim3(ceil_div(c, SB_COLS)), dim3(256), 0, h->stream, k, h->kmax, c,
-                           h->Rm, h->Rinv, h->RinvT, h->YHY, Z, P, T, h->status);
-    else
-        hipLaunchKernelGGL(small_solve, dim3(c), dim3(64), 3 * k * sizeof(double), h->stream, k, h->kmax, c, h->Rm,
-                           h->YHY, Z, P, T, h->status);
-    return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
+    return small_solve_launch(h, c, Z, SolveOut{P, T, nullptr, h->k, 0});
 }
 
-int apply_diff_float_block(bfgsuq_ctx* h, const void* V, bool v64, int32_t ncols, void* out, bool out64) {
-    // (B_k - B_0) V for a float32 or float64 block V (a basis, not a probe block in the
-    // storage type) on the float64 matrix cores, whatever the storage
-    if (h->streamed) {
-#define ADS(TS, TH)                                                                                      \
-    if (v64 && out64) return apply_streamed<TS, TH, double, double>(h, V, ncols, out, true);           \
-    if (v64) return apply_streamed<TS, TH, float, double>(h, V, ncols, out, true);                     \
-    if (out64) return apply_streamed<TS, TH, double, float>(h, V, ncols, out, true);                   \
-    return apply_streamed<TS, TH, float, float>(h, V, ncols, out, true);
-        if (h->storage == BFGS_F64) { ADS(double, double) }
-        if (h->storage == BFGS_F32) { ADS(float, float) }
-#undef ADS
-        return BFGS_ERR_ARG;
-    }
-#define ADF(TS, TH)                                                                                      \
-    if (v64 && out64) return apply_generic<TS, TH, double, double>(h, V, ncols, out, true, nullptr);   \
-    if (v64) return apply_generic<TS, TH, float, double>(h, V, ncols, out, true, nullptr);             \
-    if (out64) return apply_generic<TS, TH, double, float>(h, V, ncols, out, true, nullptr);           \
-    return apply_generic<TS, TH, float, float>(h, V, ncols, out, true, nullptr);
-    switch (h->storage) {
-        case BFGS_F64: { ADF(double, double) }
-        case BFGS_F32: { ADF(float, float) }
-        case BFGS_BF16: { ADF(bf16_t, float) }
-    }
-#undef ADF
+int apply_diff_float_block(bfgsuq_ctx* h, const void* V, bool f64, int32_t ncols, void* out) {
+    // (B_k - B_0) V for a block of the type in which the rSVD keeps Q, not a probe block in the
+    // storage type (float64 for float32 and float64 storage, float32 for bfloat16), on the
+    // float64 matrix cores
+    if (h->storage == BFGS_F64 && f64)
+        return h->streamed ? apply_streamed<double, double, double, double>(h, V, ncols, out, true)
+                           : apply_generic<double, double, double, double>(h, V, ncols, out, true, nullptr);
+    if (h->storage == BFGS_F32 && f64)
+        return h->streamed ? apply_streamed<float, float, double, double>(h, V, ncols, out, true)
+                           : apply_generic<float, float, double, double>(h, V, ncols, out, true, nullptr);
+    if (h->storage == BFGS_BF16 && !f64 && !h->streamed)
+        return apply_generic<bf16_t, float, float, float>(h, V, ncols, out, true, nullptr);
     return BFGS_ERR_ARG;
 }
 

@@ -265,9 +265,10 @@ size_t apply_small16_bytes(int kmax);
 // the storage's result type.
 int apply_block(bfgsuq_ctx* h, const void* V, int32_t ncols, void* out, bool diff, bool out64 = false,
                 const ApplyWs* fixed = nullptr);
-// (B_k - B_0) V for a float32 or float64 block (float64 matrix cores, any storage);
-// out float64 or float32.
-int apply_diff_float_block(bfgsuq_ctx* h, const void* V, bool v64, int32_t ncols, void* out, bool out64);
+// (B_k - B_0) V for a block and a result of the type in which the rSVD keeps Q: float64
+// (f64; float32 and float64 storage) or float32 (bfloat16 storage), on the float64 matrix
+// cores.
+int apply_diff_float_block(bfgsuq_ctx* h, const void* V, bool f64, int32_t ncols, void* out);
 // rSVD variants (flags of bfgs_rsvd_ex)
 int rsvd_run(bfgsuq_ctx* h, int32_t rank, int32_t oversample, uint64_t seed, void* U, double* Sigma,
              uint32_t flags = 0);
@@ -314,10 +315,10 @@ int apply_small_solve(bfgsuq_ctx* h, int c, const double* Z, double* P, double* 
 // One problem of a persistent batched apply (device copy read by the pass kernels).
 struct PersistProblem {
     int64_t n, ld, rows_per_chunk;
-    int k, kmax, c, ptiles, ctiles, nchunks, first1, firstsum, first2;
+    int k, kmax, c, ptiles, ctiles1, ctiles2, nchunks, first1, firstsum, first2;
     const void *S, *Y, *h0, *V;
     void* out;
-    double *part, *Z, *P;
+    double *part, *Z, *M;
     const double *Rm, *Rinv, *RinvT, *YHY;
     int32_t* status;
 };

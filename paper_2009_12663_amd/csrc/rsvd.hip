@@ -1183,7 +1183,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
             scale_rows_copy(h, c, Q, Qs, -1);
             V2 = Qs;
         }
-        if ((rc = apply_diff_float_block(h, V2, sizeof(TQ) == 8, c, Efree, sizeof(TE) == 8)) != BFGS_OK) return rc;
+        if ((rc = apply_diff_float_block(h, V2, sizeof(TQ) == 8, c, Efree)) != BFGS_OK) return rc;
         if (precond) scale_rows_launch(h, c, Efree, -1);
         const int nblk = ceil_div(c, MT_TILE);
         hipLaunchKernelGGL((qtx_mfma<TQ, TE>), dim3(nchunks, nblk, nblk), dim3(256), 0, h->stream, n, c, c, Q, Efree,
