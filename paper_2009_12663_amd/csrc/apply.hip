@@ -21,7 +21,7 @@
 #include <type_traits>
 #include <vector>
 
-#include "tall_f64.h"
+#include "stream_f64.h"
 
 namespace {
 
@@ -199,6 +199,46 @@ __global__ void __launch_bounds__(256) small_solve_blocks(int k, int kmax, const
     small_solve_block(lds, k, kmax, Rm, Rinv, RinvT, YHY, Z, out, status, blockIdx.x);
 }
 
+// The solve of a few columns: as above, with each sum dealt to FEW_SEGS waves per 64 rows
+// (contiguous quarters of the pairs) and added through LDS in a fixed order, since with the
+// chip otherwise idle the length of a chain is all that counts: one column at k = 100
+// takes 19 us as above, 15 in this form.  (More threads lose it again to the instructions
+// they all issue on one CU; touching the matrices ahead changes nothing.)
+constexpr int FEW_SEGS = 4;
+
+__global__ void __launch_bounds__(256 * FEW_SEGS) small_solve_few(int k, int kmax, const double* __restrict__ Rm,
+                                                                  const double* __restrict__ Rinv,
+                                                                  const double* __restrict__ RinvT,
+                                                                  const double* __restrict__ YHY,
+                                                                  const double* __restrict__ Z, SolveOut out,
+                                                                  int32_t* __restrict__ status) {
+    __shared__ double red[FEW_SEGS][256], x[256 + 64];
+    const int rows = blockDim.x / FEW_SEGS;                        // k rounded up to 64
+    const int seg = __builtin_amdgcn_readfirstlane(threadIdx.x / rows), i = threadIdx.x - seg * rows;
+    const int j = blockIdx.x, ic = min(i, k - 1);
+    const int q = (k + 2 * FEW_SEGS - 1) / (2 * FEW_SEGS) * 2;     // pairs of a segment, even
+    const int lo = min(k, seg * q), hi = min(k, lo + q);
+    const double zy = Z[(int64_t)j * 2 * k + k + ic], dii = Rm[(int64_t)ic * kmax + ic];
+    if (seg == 0) x[i] = i < k ? Z[(int64_t)j * 2 * k + i] : 0.0;
+    __syncthreads();
+    auto step = [&](const double* A, int first, int last) {
+        red[seg][i] = lo < hi ? solve_chain(0.0, A, kmax, ic, lo, hi, first, last, x) : 0.0;
+        __syncthreads();
+        return (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
+    };
+    const double pv = step(Rinv, i, k);          // P
+    if (seg == 0) x[i] = pv;
+    __syncthreads();
+    const double wv = step(YHY, 0, k) + fma(dii, pv, -zy);   // W
+    if (seg == 0) x[i] = wv;
+    __syncthreads();
+    const double tv = step(RinvT, 0, i);         // T
+    if (seg == 0 && i < k) {
+        out.put(i, j, pv, tv);
+        if (!isfinite(pv) || !isfinite(tv)) set_status(status, BFGS_ERR_NONFINITE);
+    }
+}
+
 // k = 0: B_0 V (or zero for B_k - B_0); a non-finite input sets the deferred status.
 template <typename Th, typename Tv, typename To>
 __global__ void scale_by_h0(int64_t n, int c, const Th* __restrict__ h0, const Tv* __restrict__ V,
@@ -324,6 +364,14 @@ void with_tile_width(int tb, F&& f) {
     }
 }
 
+// The same for up to STREAM_COLS columns (1, 2 or 4 of them computed).
+template <typename F>
+void with_few_columns(int c, F&& f) {
+    if (c == 1) f(std::integral_constant<int, 1>());
+    else if (c == 2) f(std::integral_constant<int, 2>());
+    else f(std::integral_constant<int, STREAM_COLS>());
+}
+
 template <typename Ts, typename Th, typename Tv>
 void launch_gemm1(hipStream_t st, int64_t n, int64_t ld, int k, int c, const Ts* S, const Ts* Y, const Th* h0,
                   const Tv* V, int64_t ldv, double* part, int64_t rows_per_chunk, int nchunks) {
@@ -391,6 +439,63 @@ int small_solve_launch(bfgsuq_ctx* h, int c, const double* Z, SolveOut out) {
     return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
 }
 
+// A few columns (c <= STREAM_COLS): both passes on the vector unit (stream_f64.h).  Row
+// chunks of pass 1: as many as keep 16 waves a CU busy, of at least 1024 rows, so that the
+// sum of the partials stays short; a single chunk writes Z itself.
+template <typename Ts, typename Th, typename To, typename Tv>
+int apply_few(bfgsuq_ctx* h, const Tv* V, int c, To* out, bool diff, const ApplyWs* fixed) {
+    const int64_t n = h->n;
+    const int k = h->k, groups = ceil_div(k, STREAM_PAIRS);
+    const Th* h0 = (const Th*)h->h0;
+    const Ts *S = (const Ts*)h->S, *Y = (const Ts*)h->Y;
+    const size_t chunk_bytes = (size_t)2 * k * c * 8;
+    int64_t nch = std::min<int64_t>(8 * std::max(1, 512 / (2 * groups)), (n + 1023) / 1024);
+    if (fixed) nch = std::min<int64_t>(nch, (int64_t)(fixed->part_bytes / chunk_bytes));
+    const int64_t rows = round_up((n + nch - 1) / nch, 256);
+    const int nchunks = (int)((n + rows - 1) / rows);
+    double *part, *Z, *P;
+    if (fixed) {
+        part = (double*)fixed->part;
+        Z = fixed->Z;
+        P = fixed->PT;
+    } else {
+        int rc;
+        if ((rc = ensure_ws(h->part, (size_t)nchunks * chunk_bytes)) != BFGS_OK) return rc;
+        if ((rc = ensure_ws(h->Z, (size_t)2 * k * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
+        if ((rc = ensure_ws(h->PT, pt_doubles(h->kmax) * 8)) != BFGS_OK) return rc;
+        part = (double*)h->part.ptr;
+        Z = (double*)h->Z.ptr;
+        P = (double*)h->PT.ptr;
+    }
+    double* T = P + (size_t)k * c;
+    {
+        ProfScope ps(h, diff ? "hdiff_gemm1" : "apply_gemm1");
+        with_few_columns(c, [&](auto cc) {
+            hipLaunchKernelGGL((stream_pass1<decltype(cc)::value, Ts, Th, Tv>), dim3(tn_grid(2 * groups, nchunks)),
+                               dim3(64), 0, h->stream, n, h->ld, k, c, S, Y, h0, V, nchunks > 1 ? part : Z, rows, nchunks,
+                               groups);
+        });
+    }
+    if (nchunks > 1) {
+        ProfScope ps(h, "apply_reduce");
+        if (int rc = sum_partials(h->stream, (int64_t)2 * k * c, nchunks, part, Z)) return rc;
+    }
+    if (k <= 256) {
+        ProfScope ps(h, "apply_solve");
+        hipLaunchKernelGGL(small_solve_few, dim3(c), dim3((unsigned)(FEW_SEGS * round_up(k, 64))), 0, h->stream, k,
+                           h->kmax, h->Rm, h->Rinv, h->RinvT, h->YHY, Z, SolveOut{P, T, nullptr, k, 0}, h->status);
+    } else if (int rc = apply_small_solve(h, c, Z, P, T)) {
+        return rc;
+    }
+    ProfScope ps(h, diff ? "hdiff_gemm2" : "apply_gemm2");
+    with_few_columns(c, [&](auto cc) {
+        hipLaunchKernelGGL((stream_pass2<decltype(cc)::value, Ts, Th, To, Tv>),
+                           dim3((unsigned)ceil_div(n, 64 * stream_rows<Ts>())), dim3(256), 0, h->stream, n, h->ld, k, c,
+                           S, Y, h0, V, P, T, out, diff ? 1 : 0);
+    });
+    return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
+}
+
 template <typename Ts, typename Th, typename To, typename Tv = Ts>
 int apply_generic(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, const ApplyWs* fixed) {
     const int64_t n = h->n;
@@ -404,6 +509,7 @@ int apply_generic(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, c
                            diff ? 1 : 0, h->status);
         return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
     }
+    if (c <= STREAM_COLS) return apply_few<Ts, Th, To, Tv>(h, V, c, out, diff, fixed);
     const int twok = 2 * k;
     const size_t chunk_bytes = (size_t)twok * c * 8;
     int most = 1 << 20;
@@ -693,7 +799,7 @@ int batch_apply_persistent(bfgsuq_ctx* const* hs, int nprob, const void* const* 
     if (nprob < 1) return BFGS_ERR_ARG;
     const bfgs_dtype s0 = hs[0]->storage;
     for (int i = 0; i < nprob; ++i)
-        if (hs[i]->storage != s0 || hs[i]->streamed || hs[i]->k < 1 || hs[i]->k > 256) return BFGS_ERR_ARG;
+        if (ncols[i] <= STREAM_COLS || hs[i]->storage != s0 || hs[i]->streamed || hs[i]->k < 1 || hs[i]->k > 256) return BFGS_ERR_ARG;
     if (s0 == BFGS_F64) return batch_persistent_impl<double, double>(hs, nprob, V, ncols, out, st, slot, upload, wg_per_cu);
     if (s0 == BFGS_F32) return batch_persistent_impl<float, float>(hs, nprob, V, ncols, out, st, slot, upload, wg_per_cu);
     return BFGS_ERR_ARG;
@@ -708,6 +814,8 @@ int sum_partials(hipStream_t st, int64_t count, int nchunks, const double* part,
 int apply_small_solve(bfgsuq_ctx* h, int c, const double* Z, double* P, double* T) {
     return small_solve_launch(h, c, Z, SolveOut{P, T, nullptr, h->k, 0});
 }
+
+bool apply_takes_tiles(int ncols) { return ncols > STREAM_COLS; }
 
 int apply_diff_float_block(bfgsuq_ctx* h, const void* V, bool f64, int32_t ncols, void* out) {
     // (B_k - B_0) V for a block of the type in which the rSVD keeps Q, not a probe block in the

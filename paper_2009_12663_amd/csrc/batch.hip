@@ -1,7 +1,7 @@
 // Batched form: many independent inversions (uneven n and k) driven together.
 //
 // A batch owns one handle per problem.  With float32 or float64 storage (and
-// 1 <= k <= 256 everywhere) the apply of all problems is five launches in all:
+// 1 <= k <= 256 and more than a few columns everywhere) the apply of all problems is five launches in all:
 // persistent pass kernels take (problem, tile) items from a work queue, longest
 // problems first (batch_apply_persistent).  Otherwise, and for the rSVD, problems
 // are spread over a small set of side streams forked from the caller's stream with
@@ -69,11 +69,13 @@ int joined(bfgsuq_batch* b, hipStream_t root, F&& fn) {
     return rc;
 }
 
-bool persistent_ok(const bfgsuq_batch* b) {
+bool persistent_ok(const bfgsuq_batch* b, const int32_t* ncols) {
     const bfgs_dtype s0 = b->h[0]->storage;
     if (s0 != BFGS_F32 && s0 != BFGS_F64) return false;
-    for (const bfgsuq_ctx* h : b->h)
-        if (h->storage != s0 || h->streamed || h->k < 1 || h->k > 256) return false;
+    for (int i = 0; i < b->nprob; ++i) {
+        const bfgsuq_ctx* h = b->h[i];
+        if (h->storage != s0 || h->streamed || h->k < 1 || h->k > 256 || !apply_takes_tiles(ncols[i])) return false;
+    }
     return true;
 }
 
@@ -82,7 +84,7 @@ bool persistent_ok(const bfgsuq_batch* b) {
 // forked after it orders the side streams behind it.
 int batch_apply(bfgsuq_batch* b, hipStream_t root, const void* const* V, const int32_t* ncols, void* const* out,
                 int slot, bool upload, bool capture = false) {
-    if (persistent_ok(b)) {
+    if (persistent_ok(b, ncols)) {
         auto launch = [&] {
             return batch_apply_persistent(b->h.data(), b->nprob, V, ncols, out, root, &b->pslot[slot], upload,
                                           b->wg_per_cu);
@@ -322,7 +324,7 @@ int bfgs_batch_autotune(bfgs_batch_t b, const void* const* V, const int32_t* nco
                                      U ? U[i] : nullptr, Sigma ? Sigma[i] : nullptr);
         if (rc != BFGS_OK) return rc;
     }
-    if (persistent_ok(b)) {
+    if (persistent_ok(b, ncols)) {
         // the persistent grid: workgroups per compute unit
         const int cand[] = {1, 2, 4};
         float best = 1e30f;
@@ -365,7 +367,7 @@ int bfgs_batch_graph_build(bfgs_batch_t b, const void* const* V, const int32_t* 
     // One eager pass sizes every workspace (and fills the graph's persistent
     // descriptors), so nothing is allocated or copied while capturing.
     int rc = bfgs_batch_apply_Hinv(b, V, ncols, out);
-    if (rc == BFGS_OK && persistent_ok(b)) rc = batch_apply(b, b->main, V, ncols, out, 1, true);
+    if (rc == BFGS_OK && persistent_ok(b, ncols)) rc = batch_apply(b, b->main, V, ncols, out, 1, true);
     if (rc == BFGS_OK) rc = bfgs_batch_rsvd(b, rank, oversample, seed, U, Sigma);
     if (rc != BFGS_OK) return rc;
     BFGS_HIP(hipStreamSynchronize(b->main));

@@ -332,8 +332,11 @@ struct PersistSlot {
     int nprob = 0, items1 = 0, sum_blocks = 0, items2 = 0, solve_blocks = 0;
 };
 
+// Whether the float64 apply of that many columns runs in tiles (which the persistent form
+// deals out), not on the few-column path.
+bool apply_takes_tiles(int ncols);
 // Apply B_k of every problem to its block (float32 or float64 storage, all of one
-// type, 1 <= k <= 256): five launches on st in all (queue reset, pass 1 of every
+// type, 1 <= k <= 256, blocks that run in tiles): five launches on st in all (queue reset, pass 1 of every
 // problem, the sums of its partials, the small solves, pass 2).  upload = false reuses the slot's descriptors
 // (a graph capture after an eager call with the same arguments).  wg_per_cu sets the
 // persistent grid (workgroups per compute unit).

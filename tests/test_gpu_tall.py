@@ -58,3 +58,46 @@ def test_tile_edges(storage, nx, nz, k, c):
         assert err <= TOL[storage]
     assert H.get_status() == 0
     B.close()
+
+
+# n around the 128- and 256-row runs, pairs around the groups of 8 and the four segments of
+# the solve, k past the stored inverse's 256, every column count of the few-column path
+FEW = [(1, 1, 1), (5, 5, 2), (17, 5, 7), (11, 31, 8), (29, 3, 9), (43, 16, 33), (61, 28, 64), (37, 37, 65), (53, 41, 129),
+       (43, 61, 257)]
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("nx,nz,k", FEW)
+def test_few_columns(storage, nx, nz, k):
+    """One to five columns: the streaming passes (up to four) and the tiles beside them, the
+    allocation-free form, and a batch of them against the per-problem results."""
+    import ctypes
+
+    import paper_2009_12663_amd as P
+    precond = (nx + nz) % 2 == 0
+    prob, S, Y, h0 = make_pairs("secant", nx, nz, k, seed=nz + 3 * k, precond=precond)
+    n = prob.n
+    h0g = None if h0 is None else gpu_input(h0, storage)
+    B = P.BfgsBatch([n, n], [k, k], [h0g, h0g], storage)
+    Sg, Yg = gpu_input(S, storage), gpu_input(Y, storage)
+    assert B.push_pairs([Sg, Sg], [Yg, Yg]) == 0
+    H = B.problems[0]
+    h = oracle_h0(storage, S, Y, h0)
+    print(f"\n[few {storage}] n={n} k={k} diagonal={precond}", flush=True)
+    for c in range(1, min(5, n) + 1):
+        V = gpu_input(wq.normal_block(n, c, seed=c), storage)
+        for diff in (False, True):
+            out = H.apply_Hdiff(V) if diff else H.apply_Hinv(V)
+            want = recursion.apply_hk(h, oracle_input(S, storage), oracle_input(Y, storage),
+                                      oracle_input(V.double().cpu(), storage), subtract_b0=diff)
+            err = col_max_rel(out.double().cpu().numpy(), want)
+            print(f"  c={c} diff={diff} elementwise {err:.2e}", flush=True)
+            assert err <= TOL[storage]
+        ref = H.apply_Hinv(V)
+        fixed = torch.empty_like(ref)
+        assert H.L.bfgs_apply_Hinv_noalloc(H.h, ctypes.c_void_p(V.data_ptr()), c, ctypes.c_void_p(fixed.data_ptr())) == 0
+        both = B.apply_Hinv([V, V])
+        torch.cuda.synchronize()
+        assert torch.equal(fixed, ref) and torch.equal(both[0], ref) and torch.equal(both[1], ref)
+    assert H.get_status() == 0
+    B.close()
