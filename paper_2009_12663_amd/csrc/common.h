@@ -343,6 +343,9 @@ bool apply_takes_tiles(int ncols);
 int batch_apply_persistent(bfgsuq_ctx* const* hs, int nprob, const void* const* V, const int32_t* ncols,
                            void* const* out, hipStream_t st, PersistSlot* slot, bool upload, int wg_per_cu);
 int push_enqueue(bfgsuq_ctx* h, const void* s, const void* y, bfgs_dtype in_dtype);
+// push_enqueue for a pair already in column k of S and Y (float64 or float32 storage,
+// device-resident).
+int push_stored(bfgsuq_ctx* h);
 int push_finish(bfgsuq_ctx* h);
 // Forget the oldest pair (float32/float64 storage, device-resident history).
 int pop_oldest(bfgsuq_ctx* h);

@@ -13,8 +13,16 @@
 // s = alpha p, y = A s = alpha A p (formed from A p, not by differencing
 // gradients), m += s, g += y, then (s, y) is pushed.  Dot products are fixed-order
 // block reductions in float64, so a run is deterministic.
+//
+// What bounds an iteration on all but the largest models is the launches and the one wait
+// for the pair's check, so the kernels between them are few: the smoothing (both passes
+// through LDS), the coupling with both dot products, and one that takes the step, stores
+// the pair and sums g^T g (q = -p is kept instead of p).  30 iterations at
+// n = 90,000, float64: 4.1 ms with 20 launches and two waits an iteration, now 3.0 with 11
+// and one.
 #include <cmath>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -38,15 +46,16 @@ int blocks_for(int64_t n) {
     return (int)(g > 4096 ? 4096 : (g < 1 ? 1 : g));
 }
 
-__global__ void stencil_x(int64_t nx, int64_t rows, int half, const double* __restrict__ w, const double* __restrict__ x,
+template <typename T>
+__global__ void stencil_x(int64_t nx, int64_t rows, int half, const double* __restrict__ w, const T* __restrict__ x,
                           double* __restrict__ out) {
     const int64_t total = rows * nx;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
         const int64_t ix = e % nx;
-        const double* src = x + (e - ix);
+        const T* src = x + (e - ix);
         double s = 0.0;
         const int lo = (int)max((int64_t)-half, -ix), hi = (int)min((int64_t)half, nx - 1 - ix);
-        for (int t = lo; t <= hi; ++t) s = fma(w[t + half], src[ix + t], s);
+        for (int t = lo; t <= hi; ++t) s = fma(w[t + half], (double)src[ix + t], s);
         out[e] = s;
     }
 }
@@ -64,20 +73,108 @@ __global__ void stencil_z(int64_t nx, int64_t nz, int64_t nparam, int half, cons
     }
 }
 
+// Both passes of the smoother on one field through LDS: a tile of 32 x 32 points with its
+// half-width halo (zero outside the grid), four neighbouring outputs to a thread in the x
+// pass and one in the z pass.  Sums run over the taps in order, as in stencil_x and
+// stencil_z, which serve wider smoothers.  A small grid's tiles are far fewer than the CUs,
+// so a tile's own latency counts: 300 x 100 x 3 points, half 20: 9 us, 19 for
+// the two stencils.
+constexpr int SM_T = 32, SM_HALF = 20, SM_IN = SM_T + 2 * SM_HALF, SM_PITCH = SM_IN + 1;
+
+template <typename T>
+__global__ void __launch_bounds__(SM_T* SM_T) smooth_tile(int64_t nx, int64_t nz, int half,
+                                                          const double* __restrict__ w, const T* __restrict__ x,
+                                                          double* __restrict__ out) {
+    __shared__ double in[SM_IN][SM_PITCH];
+    __shared__ double xs[SM_IN][SM_T];
+    __shared__ double ws[2 * SM_HALF + 1];
+    const int64_t x0 = (int64_t)blockIdx.x * SM_T, z0 = (int64_t)blockIdx.y * SM_T;
+    const T* src = x + (int64_t)blockIdx.z * nz * nx;
+    const int ext = SM_T + 2 * half, taps = 2 * half + 1;
+    if ((int)threadIdx.x < taps) ws[threadIdx.x] = w[threadIdx.x];
+#pragma unroll
+    for (int q = 0; q < (SM_IN * SM_IN + SM_T * SM_T - 1) / (SM_T * SM_T); ++q) {
+        const int e = threadIdx.x + q * SM_T * SM_T, iz = e / ext, ix = e % ext;
+        const int64_t gz = z0 + iz - half, gx = x0 + ix - half;
+        const bool there = iz < ext && gz >= 0 && gz < nz && gx >= 0 && gx < nx;
+        const double v = there ? (double)src[gz * nx + gx] : 0.0;
+        if (iz < ext) in[iz][ix] = v;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < ext * (SM_T / 4); e += SM_T * SM_T) {
+        const int iz = e / (SM_T / 4), o = e % (SM_T / 4) * 4;
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+        double a0 = in[iz][o], a1 = in[iz][o + 1], a2 = in[iz][o + 2];
+#pragma unroll 8
+        for (int t = 0; t < taps; ++t) {
+            const double a3 = in[iz][o + 3 + t], wt = ws[t];
+            s0 = fma(wt, a0, s0);
+            s1 = fma(wt, a1, s1);
+            s2 = fma(wt, a2, s2);
+            s3 = fma(wt, a3, s3);
+            a0 = a1;
+            a1 = a2;
+            a2 = a3;
+        }
+        xs[iz][o] = s0;
+        xs[iz][o + 1] = s1;
+        xs[iz][o + 2] = s2;
+        xs[iz][o + 3] = s3;
+    }
+    __syncthreads();
+    const int ix = threadIdx.x % SM_T, iz = threadIdx.x / SM_T;
+    double sum = 0.0;
+#pragma unroll 8
+    for (int t = 0; t < taps; ++t) sum = fma(ws[t], xs[iz + t][ix], sum);
+    if (x0 + ix < nx && z0 + iz < nz) out[(int64_t)blockIdx.z * nz * nx + (z0 + iz) * nx + x0 + ix] = sum;
+}
+
+// Sum of v over a workgroup of 256, in thread 0.
+__device__ __forceinline__ double block_sum256(double v, double* sh) {
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    for (int off = 128; off > 0; off >>= 1) {
+        if ((int)threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
+        __syncthreads();
+    }
+    const double t = sh[0];
+    __syncthreads();
+    return t;
+}
+
 // y = D o x + (1 - c) g + c sum_q g_q, g the smoothed fields (coupling P applied per point).
-__global__ void couple(int64_t npt, int nparam, double c, const double* __restrict__ D, const double* __restrict__ x,
-                       const double* __restrict__ g, double* __restrict__ y) {
+// DOTS: also the workgroup's part of r^T x (dots[block]) and x^T y (dots[blocks + block]).
+template <typename T, bool DOTS>
+__global__ void __launch_bounds__(256) couple(int64_t npt, int nparam, double c, const double* __restrict__ D,
+                                              const T* __restrict__ x, const double* __restrict__ g,
+                                              double* __restrict__ y, const double* __restrict__ r,
+                                              double* __restrict__ dots) {
+    __shared__ double sh[256];
+    double rx = 0.0, xy = 0.0;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < npt; e += (int64_t)gridDim.x * blockDim.x) {
         double sum = 0.0;
         for (int p = 0; p < nparam; ++p) sum += g[(int64_t)p * npt + e];
         for (int p = 0; p < nparam; ++p) {
             const int64_t i = (int64_t)p * npt + e;
-            y[i] = fma(D[i], x[i], fma(1.0 - c, g[i], c * sum));
+            const double xe = (double)x[i];
+            const double ye = fma(D[i], xe, fma(1.0 - c, g[i], c * sum));
+            y[i] = ye;
+            if (DOTS) {
+                rx = fma(r[i], xe, rx);
+                xy = fma(xe, ye, xy);
+            }
         }
+    }
+    if (!DOTS) return;
+    rx = block_sum256(rx, sh);
+    xy = block_sum256(xy, sh);
+    if (threadIdx.x == 0) {
+        dots[blockIdx.x] = rx;
+        dots[gridDim.x + blockIdx.x] = xy;
     }
 }
 
-// Fixed-order dot products: per-block partials, then one block sums them in order.
+// A fixed-order dot product's parts, one to a workgroup.
 __global__ void dot_partial(int64_t n, const double* __restrict__ a, const double* __restrict__ b,
                             double* __restrict__ part) {
     __shared__ double sh[256];
@@ -93,32 +190,45 @@ __global__ void dot_partial(int64_t n, const double* __restrict__ a, const doubl
     if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-__global__ void dot_final(int nb, const double* __restrict__ part, double* __restrict__ out) {
+// The step from q = -p, Aq = A q and the parts of g^T q and q^T A q (couple): alpha =
+// damping g^T q / q^T A q, s = -alpha q, y = -alpha A q, m += s, g += y; s and y go to the
+// pair's columns in the storage type (one rounding), and gg[block] is the workgroup's part
+// of the new g^T g.  Every workgroup sums the parts itself, in the same order.
+template <typename T, typename Ts>
+__global__ void __launch_bounds__(256) line_step(int64_t n, int nb, const double* __restrict__ dots, double damping,
+                                                 const T* __restrict__ q, const double* __restrict__ Aq,
+                                                 Ts* __restrict__ s, Ts* __restrict__ y, double* __restrict__ m,
+                                                 double* __restrict__ g, double* __restrict__ gg) {
     __shared__ double sh[256];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) s += part[i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
-        __syncthreads();
+    double gq = 0.0, qAq = 0.0;
+    for (int b = threadIdx.x; b < nb; b += 256) {
+        gq += dots[b];
+        qAq += dots[nb + b];
     }
-    if (threadIdx.x == 0) out[0] = sh[0];
+    gq = block_sum256(gq, sh);
+    qAq = block_sum256(qAq, sh);
+    const double alpha = damping * (gq / qAq);
+    double sum = 0.0;
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+        const double se = -alpha * (double)q[e], ye = -alpha * Aq[e];
+        s[e] = from_f64<Ts>(se);
+        y[e] = from_f64<Ts>(ye);
+        m[e] += se;
+        const double ge = g[e] + ye;
+        g[e] = ge;
+        sum = fma(ge, ge, sum);
+    }
+    sum = block_sum256(sum, sh);
+    if (threadIdx.x == 0) gg[blockIdx.x] = sum;
 }
 
-// alpha = -(g^T p) / (p^T A p) from the two dots in sc[0], sc[1]; s = alpha p, y = alpha A p,
-// m += s, g += y.
-__global__ void line_step(int64_t n, const double* __restrict__ sc, const double* __restrict__ p,
-                          const double* __restrict__ Ap, double* __restrict__ s, double* __restrict__ y,
-                          double* __restrict__ m, double* __restrict__ g, double damping) {
-    const double alpha = damping * (-sc[0] / sc[1]);
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const double se = alpha * p[e], ye = alpha * Ap[e];
-        s[e] = se;
-        y[e] = ye;
-        m[e] += se;
-        g[e] += ye;
-    }
+// out[0] (host memory) = the sum of nb parts.
+__global__ void __launch_bounds__(256) sum_to_host(int nb, const double* __restrict__ part, double* __restrict__ out) {
+    __shared__ double sh[256];
+    double t = 0.0;
+    for (int b = threadIdx.x; b < nb; b += 256) t += part[b];
+    t = block_sum256(t, sh);
+    if (threadIdx.x == 0) out[0] = t;
 }
 
 __global__ void negate_to(int64_t n, const double* __restrict__ x, double* __restrict__ out) {
@@ -126,28 +236,35 @@ __global__ void negate_to(int64_t n, const double* __restrict__ x, double* __res
         out[e] = -x[e];
 }
 
-template <typename Ti, typename To>
-__global__ void convert(int64_t n, const Ti* __restrict__ x, To* __restrict__ out, double scale) {
+__global__ void to_f32(int64_t n, const double* __restrict__ x, float* __restrict__ out) {
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
-        out[e] = (To)(scale * (double)x[e]);
+        out[e] = (float)x[e];
 }
 
-int gridop_apply_impl(bfgsuq_gridop* op, const double* x, double* y, hipStream_t st) {
-    const int64_t n = op->n;
-    double* tx = op->tmp;
+// y = A x; with r also the workgroups' parts of r^T x and x^T y (kRedBlocks each in dots).
+template <typename T>
+int gridop_apply_impl(bfgsuq_gridop* op, const T* x, double* y, hipStream_t st, const double* r = nullptr,
+                      double* dots = nullptr) {
+    const int64_t n = op->n, npt = op->nx * op->nz;
     double* tz = op->tmp + n;
-    hipLaunchKernelGGL(stencil_x, dim3(blocks_for(n)), dim3(256), 0, st, op->nx, op->nz * (int64_t)op->nparam, op->half,
-                       op->w, x, tx);
-    hipLaunchKernelGGL(stencil_z, dim3(blocks_for(n)), dim3(256), 0, st, op->nx, op->nz, (int64_t)op->nparam, op->half,
-                       op->w, tx, tz);
-    const int64_t npt = op->nx * op->nz;
-    hipLaunchKernelGGL(couple, dim3(blocks_for(npt)), dim3(256), 0, st, npt, op->nparam, op->coupling, op->D, x, tz, y);
+    // the tiles' LDS holds a half-width of SM_HALF; grid.y and grid.z count up to 65535
+    if (op->half <= SM_HALF && op->nparam <= 65535 && ceil_div(op->nz, SM_T) <= 65535) {
+        hipLaunchKernelGGL(smooth_tile<T>, dim3((unsigned)ceil_div(op->nx, SM_T), ceil_div(op->nz, SM_T), op->nparam),
+                           dim3(SM_T * SM_T), 0, st, op->nx, op->nz, op->half, op->w, x, tz);
+    } else {
+        double* tx = op->tmp;
+        hipLaunchKernelGGL(stencil_x<T>, dim3(blocks_for(n)), dim3(256), 0, st, op->nx, op->nz * (int64_t)op->nparam,
+                           op->half, op->w, x, tx);
+        hipLaunchKernelGGL(stencil_z, dim3(blocks_for(n)), dim3(256), 0, st, op->nx, op->nz, (int64_t)op->nparam,
+                           op->half, op->w, tx, tz);
+    }
+    if (r)
+        hipLaunchKernelGGL((couple<T, true>), dim3(kRedBlocks), dim3(256), 0, st, npt, op->nparam, op->coupling, op->D,
+                           x, tz, y, r, dots);
+    else
+        hipLaunchKernelGGL((couple<T, false>), dim3(blocks_for(npt)), dim3(256), 0, st, npt, op->nparam, op->coupling,
+                           op->D, x, tz, y, nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
-}
-
-void launch_dot(int64_t n, const double* a, const double* b, double* part, double* out, hipStream_t st) {
-    hipLaunchKernelGGL(dot_partial, dim3(kRedBlocks), dim3(256), 0, st, n, a, b, part);
-    hipLaunchKernelGGL(dot_final, dim3(1), dim3(256), 0, st, kRedBlocks, part, out);
 }
 
 }  // namespace
@@ -224,59 +341,80 @@ int bfgs_minimize_quadratic_ex(bfgs_t h, bfgs_gridop_t op, const double* b, int3
     const int64_t n = h->n;
     hipStream_t st = h->stream;
     const bool f32 = h->storage == BFGS_F32;
-    // g, p, Ap, s, y (float64), the float32 copies of g and p, partial sums and scalars
+    // g, q, Aq (float64), the float32 copies of g and q, a streamed history's pair, the
+    // parts of the dot products
     void* ws = nullptr;
-    const size_t bytes = (size_t)5 * n * 8 + (f32 ? 2 * (size_t)n * 4 : 0) + (kRedBlocks + 8) * 8;
+    const size_t pair_bytes = h->streamed ? 2 * (size_t)n * 8 : 0;
+    const size_t bytes = (size_t)3 * n * 8 + pair_bytes + (f32 ? 2 * (size_t)n * 4 : 0) + 4 * kRedBlocks * 8;
     if (hipMalloc(&ws, bytes) != hipSuccess) return BFGS_ERR_ALLOC;
     double* g = (double*)ws;
-    double* p = g + n;
-    double* Ap = p + n;
-    double* s = Ap + n;
-    double* y = s + n;
-    float* g32 = f32 ? (float*)(y + n) : nullptr;
-    float* p32 = f32 ? g32 + n : nullptr;
-    double* part = f32 ? (double*)(p32 + n) : y + n;
-    double* sc = part + kRedBlocks;   // [0] g^T p, [1] p^T A p, [2] g^T g
+    double* q = g + n;
+    double* Aq = q + n;
+    double* s64 = Aq + n;                 // a streamed history's s and y
+    float* g32 = (float*)((char*)s64 + pair_bytes);
+    float* q32 = g32 + n;
+    double* dots = (double*)((char*)g32 + (f32 ? 2 * (size_t)n * 4 : 0));   // g^T q, q^T A q
+    double* gg = dots + 2 * kRedBlocks;
+    volatile double* gg_host = h->host_sc + 4;   // written by the device, read after a wait
     int rc = BFGS_OK;
-    double host[3];
-    auto gg = [&](double* out) -> int {
-        launch_dot(n, g, g, part, sc + 2, st);
-        if (hipMemcpyAsync(host + 2, sc + 2, 8, hipMemcpyDeviceToHost, st) != hipSuccess) return BFGS_ERR_HIP;
-        if (hipStreamSynchronize(st) != hipSuccess) return BFGS_ERR_HIP;
-        *out = std::sqrt(host[2]);
+    auto norm = [&](double* out) -> int {
+        *out = std::sqrt(*gg_host);
         return std::isfinite(*out) ? BFGS_OK : BFGS_ERR_NONFINITE;
     };
     hipLaunchKernelGGL(negate_to, dim3(blocks_for(n)), dim3(256), 0, st, n, b, g);   // g_0 = A 0 - b
-    if (hipMemsetAsync(m, 0, n * 8, st) != hipSuccess) rc = BFGS_ERR_HIP;
+    hipLaunchKernelGGL(dot_partial, dim3(kRedBlocks), dim3(256), 0, st, n, g, g, gg);
+    hipLaunchKernelGGL(sum_to_host, dim3(1), dim3(256), 0, st, kRedBlocks, gg, h->host_sc + 4);
+    if (hipMemsetAsync(m, 0, n * 8, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess) rc = BFGS_ERR_HIP;
     double gn0 = 0.0;
-    if (rc == BFGS_OK) rc = gg(&gn0);
+    if (rc == BFGS_OK) rc = norm(&gn0);
     if (rc == BFGS_OK && gnorm) gnorm[0] = gn0;
     int it = 0;
     while (rc == BFGS_OK && it < max_iter && (memory > 0 || h->k < h->kmax)) {
-        if (h->k == 0 && h->gamma_mode) {
-            hipLaunchKernelGGL(negate_to, dim3(blocks_for(n)), dim3(256), 0, st, n, g, p);   // gamma unknown: p = -g
+        const bool first = h->k == 0 && h->gamma_mode;   // gamma unknown: p = -g
+        if (first) {
+            rc = gridop_apply_impl(op, g, Aq, st, g, dots);
         } else if (f32) {
-            hipLaunchKernelGGL((convert<double, float>), dim3(blocks_for(n)), dim3(256), 0, st, n, g, g32, 1.0);
-            if ((rc = apply_block(h, g32, 1, p32, false)) != BFGS_OK) break;
-            hipLaunchKernelGGL((convert<float, double>), dim3(blocks_for(n)), dim3(256), 0, st, n, p32, p, -1.0);
+            hipLaunchKernelGGL(to_f32, dim3(blocks_for(n)), dim3(256), 0, st, n, g, g32);
+            if ((rc = apply_block(h, g32, 1, q32, false)) != BFGS_OK) break;
+            rc = gridop_apply_impl(op, q32, Aq, st, g, dots);
         } else {
-            if ((rc = apply_block(h, g, 1, p, false)) != BFGS_OK) break;
-            hipLaunchKernelGGL(negate_to, dim3(blocks_for(n)), dim3(256), 0, st, n, p, p);
+            if ((rc = apply_block(h, g, 1, q, false)) != BFGS_OK) break;
+            rc = gridop_apply_impl(op, q, Aq, st, g, dots);
         }
-        if ((rc = gridop_apply_impl(op, p, Ap, st)) != BFGS_OK) break;
-        launch_dot(n, g, p, part, sc + 0, st);
-        launch_dot(n, p, Ap, part, sc + 1, st);
-        hipLaunchKernelGGL(line_step, dim3(blocks_for(n)), dim3(256), 0, st, n, sc, p, Ap, s, y, m, g, damping);
+        if (rc != BFGS_OK) break;
+        // the limited-memory form keeps the last `memory` pairs
+        if (memory > 0 && h->k == memory && (rc = pop_oldest(h)) != BFGS_OK) break;
+        const int64_t col = (int64_t)h->k * h->ld;
+        auto step = [&](const auto* dir, auto* s, auto* y) {
+            typedef std::remove_cv_t<std::remove_pointer_t<decltype(dir)>> T;
+            typedef std::remove_pointer_t<decltype(s)> Ts;
+            hipLaunchKernelGGL((line_step<T, Ts>), dim3(kRedBlocks), dim3(256), 0, st, n, kRedBlocks, dots, damping, dir,
+                               Aq, s, y, m, g, gg);
+        };
+        // a direction that is g itself is copied first: the step updates g
+        if (first && hipMemcpyAsync(q, g, n * 8, hipMemcpyDeviceToDevice, st) != hipSuccess) rc = BFGS_ERR_HIP;
+        if (rc != BFGS_OK) break;
+        if (h->streamed) {
+            if (f32 && !first) step(q32, s64, s64 + n);
+            else step(q, s64, s64 + n);
+        } else if (f32) {
+            float *S = (float*)h->S + col, *Y = (float*)h->Y + col;
+            if (first) step(q, S, Y);
+            else step(q32, S, Y);
+        } else {
+            step(q, (double*)h->S + col, (double*)h->Y + col);
+        }
+        hipLaunchKernelGGL(sum_to_host, dim3(1), dim3(256), 0, st, kRedBlocks, gg, h->host_sc + 4);
         if (hipGetLastError() != hipSuccess) {
             rc = BFGS_ERR_HIP;
             break;
         }
-        // the limited-memory form keeps the last `memory` pairs
-        if (memory > 0 && h->k == memory && (rc = pop_oldest(h)) != BFGS_OK) break;
-        if ((rc = bfgs_push_pair(h, s, y, BFGS_F64)) != BFGS_OK) break;
+        rc = h->streamed ? push_enqueue(h, s64, s64 + n, BFGS_F64) : push_stored(h);
+        if (rc == BFGS_OK) rc = push_finish(h);   // waits
+        if (rc != BFGS_OK) break;
         ++it;
         double gn = 0.0;
-        if ((rc = gg(&gn)) != BFGS_OK) break;
+        if ((rc = norm(&gn)) != BFGS_OK) break;
         if (gnorm) gnorm[it] = gn;
         if (gn <= rel_tol * gn0) break;
     }

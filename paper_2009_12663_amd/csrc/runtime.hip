@@ -137,12 +137,28 @@ __global__ void __launch_bounds__(256) gram_partial_kernel(int64_t n, int64_t ld
     const Tst* yi = Y + (int64_t)i * ld;
     const Tst* yj = Y + (int64_t)j * ld;
     double sy = 0.0, yhy = 0.0;
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
-        const double y = to_f64(yj[r]);
-        sy += to_f64(si[r]) * y;
-        const double w = gamma_mode ? y : to_f64(h0[r]) * y;
-        yhy += to_f64(yi[r]) * w;
+    auto add = [&](Tst s, Tst yv, Tst yw, Th hv) {
+        const double y = to_f64(yw);
+        sy += to_f64(s) * y;
+        const double w = gamma_mode ? y : to_f64(hv) * y;
+        yhy += to_f64(yv) * w;
+    };
+    // eight rows of a thread in flight, added in order
+    int64_t r = r0 + threadIdx.x;
+    for (; r + 7 * 256 < r1; r += 8 * 256) {
+        Tst s[8], y[8], yv[8];
+        Th hv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            s[u] = si[r + 256 * u];
+            yv[u] = yi[r + 256 * u];
+            y[u] = yj[r + 256 * u];
+            hv[u] = gamma_mode ? Th{} : h0[r + 256 * u];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) add(s[u], yv[u], y[u], hv[u]);
     }
+    for (; r < r1; r += 256) add(si[r], yi[r], yj[r], gamma_mode ? Th{} : h0[r]);
     sy = block_sum<256>(sy, sh);
     yhy = block_sum<256>(yhy, sh);
     if (threadIdx.x == 0) {
@@ -156,7 +172,8 @@ __global__ void __launch_bounds__(256) gram_partial_kernel(int64_t n, int64_t ld
 __global__ void __launch_bounds__(SUM_THREADS) gram_finish_kernel(int j, int kmax, int nb,
                                                                   const double* __restrict__ part,
                                                                   double* __restrict__ Rm, double* __restrict__ YHY,
-                                                                  double* __restrict__ scalars, int gamma_mode) {
+                                                                  double* __restrict__ scalars, int gamma_mode,
+                                                                  double* __restrict__ host_sc) {
     __shared__ double sh[SUM_DEPTH][SUM_ENTRIES];
     const int x = threadIdx.x % SUM_ENTRIES, i = blockIdx.x * (SUM_ENTRIES / 2) + x / 2;
     const bool live = i <= j;
@@ -175,9 +192,10 @@ __global__ void __launch_bounds__(SUM_THREADS) gram_finish_kernel(int j, int kma
     }
     YHY[(int64_t)j * kmax + i] = yhy;
     YHY[(int64_t)i * kmax + j] = yhy;
-    if (i == j) {
-        scalars[1] = sy;
-        scalars[2] = yhy;
+    if (i == j) {   // the host's copy (pinned memory) is read after it has waited for the stream
+        host_sc[0] = scalars[0];
+        host_sc[1] = scalars[1] = sy;
+        host_sc[2] = scalars[2] = yhy;
     }
 }
 
@@ -296,8 +314,10 @@ static int gram_streamed(bfgsuq_ctx* h, int j) {
 
 // push_pair in two halves, so that a batch can enqueue the pushes of many handles
 // before it waits for any: push_enqueue stores the pair as column k and queues the
-// Gram updates and the copy of (gamma, s^T y, y^T B_0 y) to pinned host memory;
+// Gram updates, whose last kernel writes (gamma, s^T y, y^T B_0 y) to pinned host memory;
 // push_finish waits for the handle's stream and accepts or drops the pair.
+static int push_small(bfgsuq_ctx* h, int j);
+
 int push_enqueue(bfgsuq_ctx* h, const void* s, const void* y, bfgs_dtype in_dtype) {
     if (!h || !s || !y) return BFGS_ERR_ARG;
     if (in_dtype != BFGS_F64 && in_dtype != BFGS_F32) return BFGS_ERR_ARG;
@@ -332,14 +352,27 @@ int push_enqueue(bfgsuq_ctx* h, const void* s, const void* y, bfgs_dtype in_dtyp
             launch_gram<bf16_t, float>(h, j);
             break;
     }
+    return push_small(h, j);
+}
+
+// The k x k matrices' new column from the Gram partials, and the host's copy of (gamma,
+// s^T y, y^T B_0 y).
+static int push_small(bfgsuq_ctx* h, int j) {
     BFGS_HIP(hipGetLastError());
     hipLaunchKernelGGL(gram_finish_kernel, dim3(ceil_div(j + 1, SUM_ENTRIES / 2)), dim3(SUM_THREADS), 0, h->stream, j, h->kmax,
-                       h->gram_blocks, h->gram_part, h->Rm, h->YHY, h->scalars, h->gamma_mode ? 1 : 0);
+                       h->gram_blocks, h->gram_part, h->Rm, h->YHY, h->scalars, h->gamma_mode ? 1 : 0, h->host_sc);
     BFGS_HIP(hipGetLastError());
     hipLaunchKernelGGL(rinv_update_kernel, dim3(j / SUM_ENTRIES + 1), dim3(SUM_THREADS), 0, h->stream, j, h->kmax, h->Rm, h->Rinv, h->RinvT);
     BFGS_HIP(hipGetLastError());
-    BFGS_HIP(hipMemcpyAsync(h->host_sc, h->scalars, 3 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     return BFGS_OK;
+}
+
+int push_stored(bfgsuq_ctx* h) {
+    if (h->streamed || h->storage == BFGS_BF16) return BFGS_ERR_ARG;
+    if (h->k >= h->kmax) return BFGS_ERR_FULL;
+    if (h->storage == BFGS_F64) launch_gram<double, double>(h, h->k);
+    else launch_gram<float, float>(h, h->k);
+    return push_small(h, h->k);
 }
 
 int push_finish(bfgsuq_ctx* h) {
