@@ -350,21 +350,8 @@ __global__ void __launch_bounds__(256, 2) gemm2_f64mfma(int64_t n, int64_t ld, i
     gemm2_group<TA, TB, false, Ts, Th, To, Tv>(lds, n, ld, k, c, S, Y, h0, V, ldv, M, out, diff, row0, ct, ctiles);
 }
 
-// Calls f(std::integral_constant<int, TB>) for the tile width tb (1 .. 7).
-template <typename F>
-void with_tile_width(int tb, F&& f) {
-    switch (tb) {
-        case 1: f(std::integral_constant<int, 1>()); break;
-        case 2: f(std::integral_constant<int, 2>()); break;
-        case 3: f(std::integral_constant<int, 3>()); break;
-        case 4: f(std::integral_constant<int, 4>()); break;
-        case 5: f(std::integral_constant<int, 5>()); break;
-        case 6: f(std::integral_constant<int, 6>()); break;
-        default: f(std::integral_constant<int, 7>()); break;
-    }
-}
-
-// The same for up to STREAM_COLS columns (1, 2 or 4 of them computed).
+// Calls f(std::integral_constant<int, CC>) for up to STREAM_COLS columns (1, 2 or 4 of them
+// computed).
 template <typename F>
 void with_few_columns(int c, F&& f) {
     if (c == 1) f(std::integral_constant<int, 1>());

@@ -16,7 +16,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "common.h"
+#include "tall_f64.h"
 
 int probes_launch(bfgsuq_ctx* h, uint64_t seed, int32_t c, void* X, hipStream_t stream);
 
@@ -70,189 +70,105 @@ __device__ double wg_sum(double v, double* red) {
 }
 
 // ---------------------------------------------------------------------------
-// Float64 matrix-core kernels (v_mfma_f64_16x16x4f64).  Fragment layout of one
-// 16 x 16 x 4 product C += A B on a wave: lane l holds A(l % 16, l / 16),
-// B(l / 16, l % 16), and C(l / 16 + 4 r, l % 16) in accumulator element r.
+// Float64 matrix-core products with the tall basis (tall_f64.h).
 // ---------------------------------------------------------------------------
-typedef double v4d __attribute__((ext_vector_type(4)));
+constexpr int MT_K = 16;          // rows of a step: chunks are a whole number of them
 
-__device__ __forceinline__ v4d mfma64(double a, double b, v4d c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
-// Both kernels below are 128 x 128 output tiles per workgroup, 2 x 2 waves of
-// 4 x 4 fragments each, with the next operand stage loaded into registers while
-// the current one (in LDS) feeds the matrix cores.
-constexpr int MT_TILE = 128;
-constexpr int MT_LD = MT_TILE + 4;
-constexpr int MT_K = 16;          // reduction depth staged per step
+// Columns of an n x c block, none scaled.
+template <typename T>
+struct BlockCols {
+    const T* base;
+    int64_t ld;
+    __device__ __forceinline__ TnCol<T> operator()(int j) const { return {base + (int64_t)j * ld, false}; }
+};
 
 // part[ch] = Q[rows of chunk ch, :]^T X[rows of chunk ch, :]  (cq x cx, column-major:
 // part[j * cq + i] = sum_r Q(r, i) X(r, j)), Q column-major n x cq, X n x cx (both
-// leading dimension n).  Grid (nchunk, ceil(cq / 128), ceil(cx / 128)): workgroup
-// (ch, bi, bj) owns output rows bi * 128.. and columns bj * 128..
-template <typename TQ, typename TX>
-__global__ void __launch_bounds__(256, 2) qtx_mfma(int64_t n, int cq, int cx, const TQ* __restrict__ Q,
-                                                const TX* __restrict__ X, double* __restrict__ part,
-                                                int64_t rows_per_chunk) {
-    __shared__ double Qs[MT_K][MT_LD];
-    __shared__ double Xs[MT_K][MT_LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wi = wave >> 1, wj = wave & 1;
-    const int ci0 = blockIdx.y * MT_TILE, cj0 = blockIdx.z * MT_TILE;
-    const int64_t rb = (int64_t)blockIdx.x * rows_per_chunk;
-    const int64_t re = min(n, rb + rows_per_chunk);
-    // staging map: element e = tid + 256 q (q < 8): row e % 16, column e / 16
-    TQ qreg[8];
-    TX xreg[8];
-#define QTX_LOAD_STAGE(R0)                                                                 \
-    _Pragma("unroll") for (int q = 0; q < 8; ++q) {                                      \
-        const int e = tid + 256 * q, rr = e % MT_K, cc = e / MT_K;                       \
-        const int64_t r = (R0) + rr;                                                     \
-        const bool rv = r < re;                                                          \
-        qreg[q] = (rv && ci0 + cc < cq) ? Q[(int64_t)(ci0 + cc) * n + r] : TQ{};         \
-        xreg[q] = (rv && cj0 + cc < cx) ? X[(int64_t)(cj0 + cc) * n + r] : TX{};         \
-    }
-    v4d acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0, 0, 0, 0};
-    if (rb < re) { QTX_LOAD_STAGE(rb) }
-    for (int64_t r0 = rb; r0 < re; r0 += MT_K) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int e = tid + 256 * q, rr = e % MT_K, cc = e / MT_K;
-            Qs[rr][cc] = to_f64(qreg[q]);
-            Xs[rr][cc] = to_f64(xreg[q]);
-        }
-        __syncthreads();
-        if (r0 + MT_K < re) { QTX_LOAD_STAGE(r0 + MT_K) }
-#pragma unroll
-        for (int kk = 0; kk < MT_K / 4; ++kk) {
-            const int k = 4 * kk + lane / 16, m = lane % 16;
-            double a[4], b[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                a[t] = Qs[k][(wi * 4 + t) * 16 + m];
-                b[t] = Xs[k][(wj * 4 + t) * 16 + m];
-            }
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-                for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = mfma64(a[ta], b[tb], acc[ta][tb]);
-        }
-        __syncthreads();
-    }
-    double* out = part + (int64_t)blockIdx.x * cq * cx;
-#pragma unroll
-    for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-        for (int tb = 0; tb < 4; ++tb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int gi = ci0 + (wi * 4 + ta) * 16 + lane / 16 + 4 * r;
-                const int gj = cj0 + (wj * 4 + tb) * 16 + lane % 16;
-                if (gi < cq && gj < cx) out[(int64_t)gj * cq + gi] = acc[ta][tb][r];
-            }
+// leading dimension n).  One wave per (chunk, tile), as tall_f64.h describes, and no more
+// than two to a SIMD: 256 chunks of 8 tiles are then one even round, where three to a SIMD
+// left others with one (120 x 120 of 360,000 rows, float64 Q and float32 X: 233 us,
+// 320 with three, 282 in 128 x 128 tiles through LDS).
+template <int TA, int TB, typename TQ, typename TX>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+qtx_mfma(int64_t n, int cq, int cx, const TQ* __restrict__ Q, const TX* __restrict__ X, double* __restrict__ part,
+         int64_t rows_per_chunk, int nchunks, int ptiles, int ctiles) {
+    int chunk, pos;
+    if (!tn_place(blockIdx.x, ptiles * ctiles, nchunks, chunk, pos)) return;
+    tn_tile<TA, TB, false, false, TQ, double>(n, cq, cx, chunk, rows_per_chunk, pos % ptiles, pos / ptiles, ctiles,
+                                              BlockCols<TQ>{Q, n}, nullptr, X, n, part);
 }
 
-// U = Q Us[:, :rank] (n x rank, column-major, TO) from column-major Q (n x c) and
-// Us (column-major, leading dimension c); with SUB (float64 U) U -= Q Us instead.
-// Grid (ceil(n / 128), ceil(rank / 128)).
-template <typename TQ, typename TO, bool SUB = false>
+template <typename TQ, typename TX>
+void launch_qtx(hipStream_t st, int64_t n, int cq, int cx, const TQ* Q, const TX* X, double* part,
+                int64_t rows_per_chunk, int nchunks) {
+    constexpr bool wide = sizeof(TX) == 8;
+    const TnShape s = tn_shape(cq, cx, wide);
+    with_tile_width(s.tb, [&](auto tb) {
+        constexpr int TB = wide && decltype(tb)::value > TN_WIDE_TB ? TN_WIDE_TB : decltype(tb)::value;
+        hipLaunchKernelGGL((qtx_mfma<tile_rows(TB), TB, TQ, TX>), dim3(tn_grid(s.tiles(), nchunks)), dim3(64), 0, st, n,
+                           cq, cx, Q, X, part, rows_per_chunk, nchunks, s.ptiles, s.ctiles);
+    });
+}
+
+// U = Q M (n x rank, column-major, TO) from column-major Q (n x c) and packed M (c x rank);
+// with SUB (float64 U) U -= Q M instead.
+template <int TA, typename TO, bool SUB>
+struct BasisEmit {
+    TO* U;
+    int64_t n;
+    typedef Run<TO, TA> Ahead;
+    __device__ __forceinline__ Ahead ahead(int j, int64_t r, int live) const {
+        Ahead v{};
+        if (SUB) {
+            const TO* p = U + (int64_t)j * n + r;
+            v = live == TA ? load_run<TO, TA>(p) : load_run_part<TO, TA>(p, live);
+        }
+        return v;
+    }
+    __device__ __forceinline__ void store(int j, int64_t r, const double (&o)[TA], const double (&)[TA], const Ahead& v,
+                                          int live) const {
+        TO* p = U + (int64_t)j * n + r;
+        Run<TO, TA> w;
+#pragma unroll
+        for (int f = 0; f < TA; ++f) w.v[f] = SUB ? (TO)(v.v[f] - (TO)o[f]) : (TO)o[f];
+        if (live == TA) {
+            *(Run<TO, TA>*)p = w;
+        } else {
+#pragma unroll
+            for (int f = 0; f < TA; ++f)
+                if (f < live) p[f] = w.v[f];
+        }
+    }
+};
+
+template <int TA, int TB, typename TQ, typename TO, bool SUB>
 __global__ void __launch_bounds__(256, 2) basis_mfma(int64_t n, int c, int rank, const TQ* __restrict__ Q,
-                                                  const double* __restrict__ Us, TO* __restrict__ U) {
-    __shared__ double stage_sh[MT_TILE * (MT_K + 1) + MT_K * MT_LD];
-    double* Qs = stage_sh;                          // [128 rows][MT_K + 1]
-    double* Ms = stage_sh + MT_TILE * (MT_K + 1);   // [MT_K][MT_LD]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wi = wave >> 1, wj = wave & 1;
-    const int64_t row0 = (int64_t)blockIdx.x * MT_TILE;
-    const int col0 = blockIdx.y * MT_TILE;
-    TQ qreg[8];
-    double mreg[8];
-    // Q stage element e = tid + 256 q: row e % 128, k e / 128; Us stage: k e % 16, column e / 16
-#define BASIS_LOAD_STAGE(K0)                                                                         \
-    _Pragma("unroll") for (int q = 0; q < 8; ++q) {                                                \
-        const int e = tid + 256 * q;                                                               \
-        const int rr = e % MT_TILE, kq = e / MT_TILE;                                              \
-        const int64_t r = row0 + rr;                                                               \
-        qreg[q] = (r < n && (K0) + kq < c) ? Q[(int64_t)((K0) + kq) * n + r] : TQ{};               \
-        const int km = e % MT_K, j = e / MT_K;                                                     \
-        mreg[q] = ((K0) + km < c && col0 + j < rank) ? Us[(int64_t)(col0 + j) * c + (K0) + km] : 0.0; \
-    }
-    v4d acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0, 0, 0, 0};
-    BASIS_LOAD_STAGE(0)
-    for (int k0 = 0; k0 < c; k0 += MT_K) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int e = tid + 256 * q;
-            Qs[(e % MT_TILE) * (MT_K + 1) + e / MT_TILE] = to_f64(qreg[q]);
-            Ms[(e % MT_K) * MT_LD + e / MT_K] = mreg[q];
-        }
-        __syncthreads();
-        if (k0 + MT_K < c) { BASIS_LOAD_STAGE(k0 + MT_K) }
-#pragma unroll
-        for (int kk = 0; kk < MT_K / 4; ++kk) {
-            double a[4], b[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                a[t] = Qs[((wi * 4 + t) * 16 + lane % 16) * (MT_K + 1) + 4 * kk + lane / 16];
-                b[t] = Ms[(4 * kk + lane / 16) * MT_LD + (wj * 4 + t) * 16 + lane % 16];
-            }
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-                for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = mfma64(a[ta], b[tb], acc[ta][tb]);
-        }
-        __syncthreads();
-    }
-    if (sizeof(TO) == 4) {
-        // transpose through LDS, one 64-column half at a time (64 x 129 floats fit in
-        // the staging area): Os[column][row], then each column's 128 rows are contiguous
-        float* Os = (float*)stage_sh;
-        static_assert(64 * (MT_TILE + 1) * sizeof(float) <= sizeof(stage_sh), "epilogue tile exceeds LDS");
-        for (int hh = 0; hh < 2; ++hh) {
-            if (wj == hh) {
-#pragma unroll
-                for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-                    for (int tb = 0; tb < 4; ++tb)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int rr = (wi * 4 + ta) * 16 + lane / 16 + 4 * r;
-                            const int jj = tb * 16 + lane % 16;
-                            Os[jj * (MT_TILE + 1) + rr] = (float)acc[ta][tb][r];
-                        }
-            }
-            __syncthreads();
-            for (int e = tid; e < 64 * MT_TILE; e += 256) {
-                const int rr = e % MT_TILE, jj = e / MT_TILE;
-                const int64_t r = row0 + rr;
-                const int j = col0 + hh * 64 + jj;
-                if (r < n && j < rank) U[(int64_t)j * n + r] = (TO)Os[jj * (MT_TILE + 1) + rr];
-            }
-            __syncthreads();
-        }
-    } else {
-#pragma unroll
-        for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-            for (int tb = 0; tb < 4; ++tb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int64_t row = row0 + (wi * 4 + ta) * 16 + lane / 16 + 4 * r;
-                    const int j = col0 + (wj * 4 + tb) * 16 + lane % 16;
-                    if (j < rank && row < n) {
-                        if (SUB) U[(int64_t)j * n + row] -= (TO)acc[ta][tb][r];
-                        else U[(int64_t)j * n + row] = (TO)acc[ta][tb][r];
-                    }
-                }
+                                                     const double* __restrict__ M, TO* __restrict__ U, int ctiles) {
+    __shared__ NnLds<TB> lds;
+    int64_t row0;
+    int ct;
+    if (!nn_place(blockIdx.x, n, 64 * TA, ctiles, row0, ct)) return;
+    const int cblocks = (rank + 15) / 16, cb = ct * cblocks / ctiles, ce = (ct + 1) * cblocks / ctiles;
+    nn_group<TA, TB, false, false, TQ, double>(lds, n, row0, false, c, rank, cblocks, cb, ce - cb, BlockCols<TQ>{Q, n},
+                                               nullptr, M, BasisEmit<TA, TO, SUB>{U, n});
+}
+
+template <bool SUB, typename TQ, typename TO>
+void launch_basis(hipStream_t st, int64_t n, int c, int rank, const TQ* Q, const double* M, TO* U) {
+    const NnShape s = nn_shape(rank);
+    with_tile_width(s.tb, [&](auto tb) {
+        constexpr int TB = decltype(tb)::value;
+        hipLaunchKernelGGL((basis_mfma<tile_rows(TB), TB, TQ, TO, SUB>), dim3(nn_grid(n, s)), dim3(256), 0, st, n, c,
+                           rank, Q, M, U, s.ctiles);
+    });
+}
+
+// M (nq x nc, column-major) in the fragment order that nn_group reads.
+__global__ void pack_nn(int nq, int nc, const double* __restrict__ M, double* __restrict__ packed) {
+    const int cblocks = (nc + 15) / 16, rows = (nq + 3) / 4 * 4;
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < rows * nc; e += gridDim.x * blockDim.x) {
+        const int q = e % rows, j = e / rows;
+        packed[nn_pack_index(q, j, cblocks)] = q < nq ? M[(int64_t)j * nq + q] : 0.0;
     }
 }
 
@@ -837,20 +753,37 @@ __global__ void __launch_bounds__(256) householder_accum(int c, const double* __
     double z[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) z[q] = (lane + 64 * q == col) ? 1.0 : 0.0;
-    for (int kk = c - 3; kk >= 0; --kk) {
-        const double tau = taus[kk];
-        if (tau == 0.0) continue;
-        double v[4];
-        double s = 0.0;
+    // the chain is two dozen instructions a reflector; reflectors are fetched AHEAD steps
+    // before they are applied (fetched on demand, each waited for memory: 115 us at c = 220)
+    constexpr int AHEAD = 4;
+    double v[AHEAD][4], tau[AHEAD];
+    auto fetch = [&](double (&x)[4], double& t, int kk) {
+        const int k1 = max(kk, 0);
+        t = taus[k1];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int r = lane + 64 * q;
-            v[q] = (r > kk && r < c) ? V[(int64_t)kk * c + r] : 0.0;
-            s = fma(v[q], z[q], s);
+        for (int q = 0; q < 4; ++q) x[q] = V[(int64_t)k1 * c + min(lane + 64 * q, c - 1)];
+    };
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) fetch(v[u], tau[u], c - 3 - u);
+    for (int k0 = c - 3; k0 >= 0; k0 -= AHEAD) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int kk = k0 - u;
+            if (kk < 0) break;
+            const double t = tau[u];
+            double x[4], s = 0.0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = lane + 64 * q;
+                x[q] = (r > kk && r < c) ? v[u][q] : 0.0;
+                s = fma(x[q], z[q], s);
+            }
+            fetch(v[u], tau[u], kk - AHEAD);
+            s = t * wave_sum_d(s);
+            if (t == 0.0) continue;   // uniform: the reflector is the identity
+#pragma unroll
+            for (int q = 0; q < 4; ++q) z[q] = fma(-s, x[q], z[q]);
         }
-        s = tau * wave_sum_d(s);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) z[q] = fma(-s, v[q], z[q]);
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -861,35 +794,44 @@ __global__ void __launch_bounds__(256) householder_accum(int c, const double* __
 
 // Order eigenpairs by |lambda| descending (ties: lambda descending, then index),
 // make each eigenvector's largest-magnitude entry positive (lowest index on ties),
-// write lam_out (c) and Us (column-major c x c, sorted).
-__global__ void __launch_bounds__(SMALL_THREADS) order_sign(int c, const double* __restrict__ d, const double* __restrict__ Z,
-                                                            double* __restrict__ lam_out, double* __restrict__ Us) {
-    __shared__ int dest[256];
-    const int tid = threadIdx.x;
-    for (int i = tid; i < c; i += SMALL_THREADS) {
-        const double ai = fabs(d[i]), li = d[i];
-        int rank = 0;
-        for (int j = 0; j < c; ++j) {
-            if (j == i) continue;
-            const double aj = fabs(d[j]), lj = d[j];
-            const bool before = (aj > ai) || (aj == ai && lj > li) || (aj == ai && lj == li && j < i);
-            rank += before ? 1 : 0;
-        }
-        dest[i] = rank;
+// write lam_out (c) and Us (column-major c x c, sorted), and, where packed is given, the
+// first `rank` columns in the fragment order that nn_group reads.  One wave per
+// eigenvector (one workgroup for all of them took 117 us at c = 220).
+__global__ void __launch_bounds__(64) order_sign(int c, int rank, const double* __restrict__ d,
+                                                 const double* __restrict__ Z, double* __restrict__ lam_out,
+                                                 double* __restrict__ Us, double* __restrict__ packed) {
+    const int i = blockIdx.x, lane = threadIdx.x;
+    const double li = d[i], ai = fabs(li);
+    int before = 0;
+    for (int j = lane; j < c; j += 64) {
+        if (j == i) continue;
+        const double lj = d[j], aj = fabs(lj);
+        before += (aj > ai) || (aj == ai && lj > li) || (aj == ai && lj == li && j < i) ? 1 : 0;
     }
-    __syncthreads();
-    for (int i = tid; i < c; i += SMALL_THREADS) {
-        const int o = dest[i];
-        lam_out[o] = d[i];
-        const double* zc = Z + (int64_t)i * c;
-        int arg = 0;
-        double best = -1.0;
-        for (int r = 0; r < c; ++r) {
-            const double v = fabs(zc[r]);
-            if (v > best) { best = v; arg = r; }
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+    const int o = before;
+    const double* zc = Z + (int64_t)i * c;
+    double z[4], best = -1.0;
+    int arg = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = lane + 64 * q;
+        z[q] = r < c ? zc[r] : 0.0;
+        const double v = fabs(z[q]);
+        if (r < c && v > best) {
+            best = v;
+            arg = r;
         }
-        const double sg = zc[arg] < 0.0 ? -1.0 : 1.0;
-        for (int r = 0; r < c; ++r) Us[(int64_t)o * c + r] = sg * zc[r];
+    }
+    wave_argmax(best, arg);
+    const double sg = zc[arg] < 0.0 ? -1.0 : 1.0;
+    if (lane == 0) lam_out[o] = li;
+    const int cblocks = (rank + 15) / 16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = lane + 64 * q;
+        if (r < c) Us[(int64_t)o * c + r] = sg * z[q];
+        if (packed && o < rank && r < (c + 3) / 4 * 4) packed[nn_pack_index(r, o, cblocks)] = r < c ? sg * z[q] : 0.0;
     }
 }
 
@@ -902,7 +844,15 @@ __global__ void posterior_diag_kernel(int64_t n, int rank, const TO* __restrict_
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
         const double hr = to_f64(h0[r]);
         double s = 0.0;
-        for (int i = 0; i < rank; ++i) {
+        int i = 0;
+        for (; i + 8 <= rank; i += 8) {   // eight in flight, added in order
+            TO u[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) u[q] = U[(int64_t)(i + q) * n + r];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s = fma(lam[i + q], to_f64(u[q]) * to_f64(u[q]), s);
+        }
+        for (; i < rank; ++i) {
             const double u = to_f64(U[(int64_t)i * n + r]);
             s = fma(lam[i], u * u, s);
         }
@@ -995,12 +945,11 @@ int qr_two_blocks(bfgsuq_ctx* h, int c, double* E, double* Q, int nchunks, int64
     if ((rc = tsqr_twice(h, c1, E, W, Q, Rk, R11)) != BFGS_OK) return rc;
     const int64_t cnt = (int64_t)c1 * c2;
     for (int pass = 0; pass < 2; ++pass) {
-        hipLaunchKernelGGL((qtx_mfma<double, double>), dim3(nchunks, ceil_div(c1, MT_TILE), ceil_div(c2, MT_TILE)),
-                           dim3(256), 0, h->stream, n, c1, c2, Q, E2, part, rows_per_chunk);
+        launch_qtx(h->stream, n, c1, c2, (const double*)Q, (const double*)E2, part, rows_per_chunk, nchunks);
         double* dst = pass == 0 ? R12 : Rk;
         if ((rc = sum_partials(h->stream, cnt, nchunks, part, dst)) != BFGS_OK) return rc;
-        hipLaunchKernelGGL((basis_mfma<double, double, true>), dim3((unsigned)ceil_div(n, (int64_t)MT_TILE),
-                           ceil_div(c2, MT_TILE)), dim3(256), 0, h->stream, n, c1, c2, Q, dst, E2);
+        hipLaunchKernelGGL(pack_nn, dim3(64), dim3(256), 0, h->stream, c1, c2, dst, part);   // the partials are summed
+        launch_basis<true>(h->stream, n, c1, c2, (const double*)Q, part, E2);
         if (pass == 1) hipLaunchKernelGGL(add_into, dim3(ceil_div(cnt, 256)), dim3(256), 0, h->stream, cnt, Rk, R12);
     }
     if ((rc = tsqr_twice(h, c2, E2, W, Q2, Rk, R22)) != BFGS_OK) return rc;
@@ -1010,11 +959,10 @@ int qr_two_blocks(bfgsuq_ctx* h, int c, double* E, double* Q, int nchunks, int64
     double* P = Rk;
     double* Rn = Rb + 4 * cc;
     double* Rn1 = Rb + 5 * cc;
-    hipLaunchKernelGGL((qtx_mfma<double, double>), dim3(nchunks, ceil_div(c1, MT_TILE), ceil_div(c2, MT_TILE)),
-                       dim3(256), 0, h->stream, n, c1, c2, Q, Q2, part, rows_per_chunk);
+    launch_qtx(h->stream, n, c1, c2, (const double*)Q, (const double*)Q2, part, rows_per_chunk, nchunks);
     if ((rc = sum_partials(h->stream, cnt, nchunks, part, P)) != BFGS_OK) return rc;
-    hipLaunchKernelGGL((basis_mfma<double, double, true>), dim3((unsigned)ceil_div(n, (int64_t)MT_TILE),
-                       ceil_div(c2, MT_TILE)), dim3(256), 0, h->stream, n, c1, c2, Q, P, Q2);
+    hipLaunchKernelGGL(pack_nn, dim3(64), dim3(256), 0, h->stream, c1, c2, P, part);
+    launch_basis<true>(h->stream, n, c1, c2, (const double*)Q, part, Q2);
     hipLaunchKernelGGL(add_p_times_r, dim3(ceil_div(cnt, 256)), dim3(256), 0, h->stream, c1, c2, P, R22, R12);
     if ((rc = tsqr_twice(h, c2, Q2, W, Q2, Rn1, Rn)) != BFGS_OK) return rc;
     hipLaunchKernelGGL(tri_mul, dim3(ceil_div((int64_t)c2 * c2, 256)), dim3(256), 0, h->stream, c2, Rn, R22, Rn1);
@@ -1108,7 +1056,8 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
     const int qx_chunks = qblk ? (int)ceil_div(n, qb_rows) : nchunks;
     const int part_chunks = std::max(nchunks, qx_chunks);
     const size_t cc = (size_t)c * c;
-    if ((rc = ensure_ws(h->small, ((size_t)part_chunks * cc + 14 * cc + 6 * (size_t)c) * 8 + (size_t)c * 4)) !=
+    if ((rc = ensure_ws(h->small, ((size_t)part_chunks * cc + 14 * cc + nn_pack_doubles(c, rank) + 6 * (size_t)c) * 8 +
+                                      (size_t)c * 4)) !=
         BFGS_OK)
         return rc;
     // tridiagonal eigensolver workspace, then Z = Q_H Y (c x c)
@@ -1132,7 +1081,8 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
     double* R1c = lam + c;
     double* Fm = R1c + cc;
     double* Rb = Fm + cc;   // 6 c x c: the column-blocked QR's pieces
-    int* piv = (int*)(Rb + 6 * cc);
+    double* Mpk = Rb + 6 * cc;   // the basis' small operand, packed
+    int* piv = (int*)(Mpk + nn_pack_doubles(c, rank));
     TS* X = (TS*)h->X.ptr;
     TE* E = (TE*)h->E.ptr;
     TQ* Q = (TQ*)h->Q.ptr;
@@ -1185,9 +1135,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
         }
         if ((rc = apply_diff_float_block(h, V2, sizeof(TQ) == 8, c, Efree)) != BFGS_OK) return rc;
         if (precond) scale_rows_launch(h, c, Efree, -1);
-        const int nblk = ceil_div(c, MT_TILE);
-        hipLaunchKernelGGL((qtx_mfma<TQ, TE>), dim3(nchunks, nblk, nblk), dim3(256), 0, h->stream, n, c, c, Q, Efree,
-                           part, rows_per_chunk);
+        launch_qtx(h->stream, n, c, c, (const TQ*)Q, (const TE*)Efree, part, rows_per_chunk, nchunks);
         if ((rc = sum_partials(h->stream, (int64_t)cc, nchunks, part, Tm)) != BFGS_OK) return rc;
         hipLaunchKernelGGL(symmetrise, dim3(ceil_div((int64_t)cc, 256)), dim3(256), 0, h->stream, c, Tm, Om);
     } else {
@@ -1205,9 +1153,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
                                       qb_rows)) != BFGS_OK)
                 return rc;
         } else {
-            const int nblk = ceil_div(c, MT_TILE);
-            hipLaunchKernelGGL((qtx_mfma<TQ, TS>), dim3(nchunks, nblk, nblk), dim3(256), 0, h->stream, n, c, c, Qp, X,
-                               part, rows_per_chunk);
+            launch_qtx(h->stream, n, c, c, Qp, (const TS*)X, part, rows_per_chunk, nchunks);
         }
         if ((rc = sum_partials(h->stream, (int64_t)cc, bf16_path ? qx_chunks : nchunks, part, Tm)) != BFGS_OK)
             return rc;
@@ -1239,7 +1185,8 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
     hipLaunchKernelGGL(householder_accum, dim3(ceil_div(c, 4)), dim3(256), 0, h->stream, c, Bm, tv, Zm);
     double* wv = nullptr;
     if ((rc = tridiag_dc(h->stream, c, dv, ev, Zm, dcwork, &wv, Zt, h->status)) != BFGS_OK) return rc;
-    hipLaunchKernelGGL(order_sign, dim3(1), dim3(SMALL_THREADS), 0, h->stream, c, wv, Zt, lam, Usm);
+    hipLaunchKernelGGL(order_sign, dim3(c), dim3(64), 0, h->stream, c, rank, wv, Zt, lam, Usm,
+                       bf16_path ? nullptr : Mpk);
     if (hipMemcpyAsync(Sigma, lam, (size_t)rank * 8, hipMemcpyDeviceToDevice, h->stream) != hipSuccess)
         return BFGS_ERR_HIP;
     prof_end(h);
@@ -1250,8 +1197,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
                                     h->status, precond, qb_rows)) != BFGS_OK)
             return rc;
     } else {
-        hipLaunchKernelGGL((basis_mfma<TQ, TO>), dim3((unsigned)ceil_div(n, (int64_t)MT_TILE), ceil_div(rank, MT_TILE)),
-                           dim3(256), 0, h->stream, n, c, rank, Q, Usm, U);
+        launch_basis<false>(h->stream, n, c, rank, (const TQ*)Q, (const double*)Mpk, U);
         const int g = (int)std::min<int64_t>(4096, (n + 255) / 256);
         hipLaunchKernelGGL((posterior_diag_kernel<TO, Th>), dim3(g), dim3(256), 0, h->stream, n, rank, U, lam,
                            (const Th*)h->h0, dout, h->status, precond ? 1 : 0);

@@ -18,6 +18,8 @@
 // the 128 x 128 tiles staged through LDS between barriers took 8.1 and 10.3 ms.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -257,7 +259,7 @@ inline TnShape tn_shape(int np, int c, bool wide_v) {
     s.tb = ceil_div(cblocks, s.ctiles);
     s.ta = tile_rows(s.tb);
     s.ptiles = ceil_div(pblocks, s.ta);
-    s.waves = s.tb >= 5 || (wide_v && s.tb != 1) ? 2 : s.tb % 2 ? 4 : 3;
+    s.waves = s.tb >= 5 ? 2 : (s.tb % 2 ? 4 : 3) - (wide_v ? 1 : 0);
     return s;
 }
 
@@ -429,4 +431,18 @@ __device__ __forceinline__ bool nn_place(int id, int64_t n, int rows, int ctiles
     ct = local % ctiles;
     row0 = blk * rows;
     return row0 < n;
+}
+
+// Calls f(std::integral_constant<int, TB>) for the tile width tb (1 .. 7).
+template <typename F>
+void with_tile_width(int tb, F&& f) {
+    switch (tb) {
+        case 1: f(std::integral_constant<int, 1>()); break;
+        case 2: f(std::integral_constant<int, 2>()); break;
+        case 3: f(std::integral_constant<int, 3>()); break;
+        case 4: f(std::integral_constant<int, 4>()); break;
+        case 5: f(std::integral_constant<int, 5>()); break;
+        case 6: f(std::integral_constant<int, 6>()); break;
+        default: f(std::integral_constant<int, 7>()); break;
+    }
 }
