@@ -22,6 +22,7 @@
 // The merges run bottom-up over power-of-two blocks (leaf i starts at d_i - e_{i-1}
 // - e_i, since every adjacent pair is split at some level), one workgroup per merge,
 // all merges of a level in one launch.  Z = Q_H Y then gives the eigenvectors of Omega.
+#include <algorithm>
 #include <cmath>
 
 #include "common.h"
@@ -30,7 +31,17 @@ namespace {
 
 constexpr double EPS = 2.220446049250313e-16;   // 2^-52
 constexpr int DC_MAX = 256;
-constexpr int DC_THREADS = 256;
+constexpr int DC_THREADS = 1024;   // at most: a merge of blocks of h takes 8 h, four to a pole
+
+// The value that lane q of this lane's quad holds (q a constant).
+template <int Q>
+__device__ __forceinline__ double quad_get(double x) {
+    constexpr int CTRL = Q * 0x55;   // quad_perm [Q, Q, Q, Q]
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
 
 // Leaves: lam_i = d_i - e_{i-1} - e_i, Q = I.
 __global__ void dc_leaves(int c, const double* __restrict__ d, const double* __restrict__ e, double* __restrict__ lam,
@@ -47,128 +58,186 @@ __global__ void dc_leaves(int c, const double* __restrict__ d, const double* __r
     }
 }
 
-// One merge of blocks [s, s + h) and [s + h, s + h + hb) per workgroup.  Qin/lam_in hold
-// the blocks' eigenvectors (block-diagonal, column-major c x c) and eigenvalues;
-// Qout/lam_out receive the merged ones.  R and U are c x c scratch (block regions).
-__global__ void __launch_bounds__(DC_THREADS) dc_merge(int c, int h, const double* __restrict__ e,
-                                                       const double* __restrict__ lam_in, const double* __restrict__ Qin,
-                                                       double* __restrict__ lam_out, double* __restrict__ Qout,
-                                                       double* __restrict__ R, double* __restrict__ U,
-                                                       int* __restrict__ Kg, int* __restrict__ ndx_g,
-                                                       int* __restrict__ slot_g) {
-    __shared__ double Dv[DC_MAX], zv[DC_MAX], ds[DC_MAX], zs[DC_MAX];
-    __shared__ int pcol[DC_MAX], ndx[DC_MAX], slot_of[DC_MAX];
-    __shared__ unsigned char defl[DC_MAX];
-    __shared__ double dn[DC_MAX], z2n[DC_MAX], zn[DC_MAX], taun[DC_MAX], zh[DC_MAX], lamn[DC_MAX];
-    __shared__ int orgn[DC_MAX];
-    __shared__ int rot_a[DC_MAX], rot_b[DC_MAX];
-    __shared__ double rot_c[DC_MAX], rot_s[DC_MAX];
-    __shared__ int nrot_sh, K_sh;
-    const int tid = threadIdx.x;
-    const int s = blockIdx.x * 2 * h;
-    if (s >= c) return;                                   // whole workgroup
-    const int ha = min(h, c - s);
-    const int hb = min(h, c - s - ha);
-    const int n = ha + hb;
-    if (hb == 0) {
-        // nothing to merge: copy the block (dc_merge_gemm skips it)
-        if (tid == 0) Kg[blockIdx.x] = -1;
-        for (int t = tid; t < n * n; t += DC_THREADS) {
-            const int col = s + t / n, row = s + t % n;
-            Qout[(int64_t)col * c + row] = Qin[(int64_t)col * c + row];
-        }
-        for (int t = tid; t < n; t += DC_THREADS) lam_out[s + t] = lam_in[s + t];
-        return;
+// What the merges of a workgroup share, by the column's place in the workgroup.
+struct MergeLds {
+    double Dv[DC_MAX], zv[DC_MAX], ds[DC_MAX], zs[DC_MAX];
+    double dn[DC_MAX], z2n[DC_MAX], zn[DC_MAX], taun[DC_MAX], zh[DC_MAX], lamn[DC_MAX];
+    double rot_c[DC_MAX], rot_s[DC_MAX];
+    int pcol[DC_MAX], ndx[DC_MAX], slot_of[DC_MAX], orgn[DC_MAX], rot_a[DC_MAX], rot_b[DC_MAX], nrot[DC_MAX];
+    // a bit a pole: of weight (not deflated by it), turning with the pole before it, kept
+    uint32_t weighty[DC_MAX / 32], turns[DC_MAX / 32], kept[DC_MAX / 32];
+};
+
+// First set bit of [from, end), or end.
+__device__ __forceinline__ int next_bit(const uint32_t* w, int from, int end) {
+    while (from < end) {
+        const uint32_t m = w[from >> 5] >> (from & 31);
+        if (m) return min(end, from + __ffs(m) - 1);
+        from = (from | 31) + 1;
     }
-    const double beta = e[s + ha - 1];
+    return end;
+}
+
+// Last set bit of [first, before), or -1.
+__device__ __forceinline__ int prev_bit(const uint32_t* w, int first, int before) {
+    while (before > first) {
+        const uint32_t m = w[(before - 1) >> 5] << (31 - ((before - 1) & 31));
+        if (m) {
+            const int at = before - 1 - __clz(m);
+            return at >= first ? at : -1;
+        }
+        before = (before - 1) & ~31;
+    }
+    return -1;
+}
+
+// Set bits of [first, before).
+__device__ __forceinline__ int count_bits(const uint32_t* w, int first, int before) {
+    int n = 0;
+    while (first < before) {
+        const int stop = min(before, (first | 31) + 1), len = stop - first;
+        n += __popc((w[first >> 5] >> (first & 31)) & (len == 32 ? ~0u : (1u << len) - 1u));
+        first = stop;
+    }
+    return n;
+}
+
+// One merge of blocks [s, s + h) and [s + h, s + h + hb) by 8 h threads (t of them; 4 to a
+// pole), whose part of the shared arrays begins at `off`; the workgroup's merges of a level
+// run side by side and meet the same barriers (one with nothing to merge has n = 0).
+// Qin/lam_in hold the blocks' eigenvectors (block-diagonal, column-major c x c) and
+// eigenvalues; lam_out receives the merged ones, R and U (c x c scratch, block regions) the
+// rotated basis and the eigenvectors in it, whose product is the merged basis.
+// Returns the number K of poles kept.
+// The time is that of chains: divisions, and at the last level the root whose Newton steps
+// are most (52 at 120 poles).  A pole's or root's sums and products are shared by a quad of
+// lanes: each forms every fourth term, and the terms are added or multiplied in index
+// order, as by one lane.  The scan for close poles walks only those that turn.
+__device__ __forceinline__ int merge_block(MergeLds& m, int c, int h, int s, int off, int n, int ha, int t,
+                                           const double* __restrict__ e, const double* __restrict__ lam_in,
+                                           const double* __restrict__ Qin, double* __restrict__ lam_out,
+                                           double* __restrict__ R, double* __restrict__ U) {
+    const int step = 8 * h, quad = t >> 2, q = t & 3, end = off + n;
+    const double beta = n > 0 ? e[s + ha - 1] : 0.0;
     const bool neg = beta < 0.0;
     const double rho = 2.0 * fabs(beta);
     const double r2 = 0.7071067811865476;   // 1 / sqrt 2
+    double *Dv = m.Dv + off, *zv = m.zv + off, *ds = m.ds + off, *zs = m.zs + off, *dn = m.dn + off;
+    double *z2n = m.z2n + off, *zn = m.zn + off, *taun = m.taun + off, *zh = m.zh + off, *lamn = m.lamn + off;
+    int *pcol = m.pcol + off, *ndx = m.ndx + off, *slot_of = m.slot_of + off, *orgn = m.orgn + off;
     // poles and weights (negated when beta < 0, so that rho > 0)
-    for (int t = tid; t < n; t += DC_THREADS) {
-        const double dv = lam_in[s + t];
-        Dv[t] = neg ? -dv : dv;
-        zv[t] = r2 * (t < ha ? Qin[(int64_t)(s + t) * c + s + ha - 1] : Qin[(int64_t)(s + t) * c + s + ha]);
+    for (int p = t; p < n; p += step) {
+        const double dv = lam_in[s + p];
+        Dv[p] = neg ? -dv : dv;
+        zv[p] = r2 * (p < ha ? Qin[(int64_t)(s + p) * c + s + ha - 1] : Qin[(int64_t)(s + p) * c + s + ha]);
     }
+    for (int w = threadIdx.x; w < DC_MAX / 32; w += (int)blockDim.x) m.weighty[w] = m.turns[w] = 0;
     __syncthreads();
     // sort by rank (ties by index).  The order is total even for NaN (after every
     // number, among themselves by index), so the ranks are a permutation and every
     // pcol entry is written: a non-finite input gives wrong values, never an index
     // out of range.
-    for (int t = tid; t < n; t += DC_THREADS) {
-        const double dt = Dv[t];
+    double tol = 0.0;
+    if (quad < n) {
+        const double dt = Dv[quad];
         const bool nt = isnan(dt);
         int rk = 0;
-        for (int u = 0; u < n; ++u) {
-            const double du = Dv[u];
-            const bool before = isnan(du) ? (nt && u < t) : (nt || du < dt || (du == dt && u < t));
-            rk += before ? 1 : 0;
-        }
-        ds[rk] = dt;
-        zs[rk] = zv[t];
-        pcol[rk] = t;
-    }
-    __syncthreads();
-    // deflation scan (one lane)
-    if (tid == 0) {
         double dmax = rho;
-        for (int p = 0; p < n; ++p) dmax = fmax(dmax, fabs(ds[p]));
-        const double tol = 8.0 * EPS * dmax;
-        int nrot = 0, last = -1, K = 0;
-        for (int p = 0; p < n; ++p) {
-            defl[p] = fabs(rho * zs[p]) <= tol ? 1 : 0;
-            if (defl[p]) continue;
-            if (last >= 0) {
-                const double zl = zs[last], zi = zs[p];
-                const double tau = sqrt(fma(zl, zl, zi * zi));
-                const double cc = zi / tau, sn = -zl / tau;
-                if (fabs((ds[p] - ds[last]) * cc * sn) <= tol) {
-                    zs[p] = tau;
-                    zs[last] = 0.0;
-                    const double dl = ds[last], di = ds[p];
-                    ds[last] = dl * cc * cc + di * sn * sn;
-                    ds[p] = dl * sn * sn + di * cc * cc;
-                    defl[last] = 1;
-                    rot_a[nrot] = last;
-                    rot_b[nrot] = p;
-                    rot_c[nrot] = cc;
-                    rot_s[nrot] = sn;
-                    ++nrot;
-                }
-            }
-            last = p;
+        for (int u = q; u < n; u += 4) {
+            const double du = Dv[u];
+            const bool before = isnan(du) ? (nt && u < quad) : (nt || du < dt || (du == dt && u < quad));
+            rk += before ? 1 : 0;
+            dmax = fmax(dmax, fabs(du));
         }
-        for (int p = 0; p < n; ++p) {
-            if (!defl[p]) {
-                ndx[K] = p;
-                slot_of[p] = K;
-                ++K;
-            } else {
-                slot_of[p] = -1;
-            }
+        rk += __shfl_xor(rk, 1, 4);
+        rk += __shfl_xor(rk, 2, 4);
+        dmax = fmax(fmax(quad_get<0>(dmax), quad_get<1>(dmax)), fmax(quad_get<2>(dmax), quad_get<3>(dmax)));
+        tol = 8.0 * EPS * dmax;
+        const double z = zv[quad];
+        if (q == 0) {
+            ds[rk] = dt;
+            zs[rk] = z;
+            pcol[rk] = quad;
+            if (!(fabs(rho * z) <= tol)) atomicOr(&m.weighty[(off + rk) >> 5], 1u << ((off + rk) & 31));
         }
-        nrot_sh = nrot;
-        K_sh = K;
     }
     __syncthreads();
-    const int K = K_sh, nrot = nrot_sh;
-    for (int j = tid; j < K; j += DC_THREADS) {
-        const double zj = zs[ndx[j]];
-        dn[j] = ds[ndx[j]];
-        zn[j] = zj;
-        z2n[j] = zj * zj;
+    // Deflation of close neighbours among the poles of weight: the pairs that would turn are
+    // found by all threads, and one lane walks from turn to turn (a turn changes the pair
+    // after it, which is tested anew).
+    auto turn_of = [&](int a, int b, double& tau, double& cc, double& sn) {
+        const double zl = zs[a], zi = zs[b];
+        tau = sqrt(fma(zl, zl, zi * zi));
+        cc = zi / tau;
+        sn = -zl / tau;
+        return fabs((ds[b] - ds[a]) * cc * sn) <= tol;
+    };
+    for (int w = threadIdx.x; w < DC_MAX / 32; w += (int)blockDim.x) m.kept[w] = m.weighty[w];
+    if (t < n && (m.weighty[(off + t) >> 5] >> ((off + t) & 31) & 1)) {
+        const int last = prev_bit(m.weighty, off, off + t);
+        double tau, cc, sn;
+        if (last >= 0 && turn_of(last - off, t, tau, cc, sn)) atomicOr(&m.turns[(off + t) >> 5], 1u << ((off + t) & 31));
     }
     __syncthreads();
-    // secular roots: lane j finds root j from its nearer pole (bracket, then Newton)
-    double z2sum = 0.0;
-    for (int i = 0; i < K; ++i) z2sum += z2n[i];
-    for (int j = tid; j < K; j += DC_THREADS) {
+    if (t == 0) {
+        int nrot = 0;
+        int p = next_bit(m.turns, off, end);
+        while (p < end) {
+            int last = prev_bit(m.weighty, off, p);
+            double tau, cc, sn;
+            turn_of(last - off, p - off, tau, cc, sn);
+            do {
+                zs[p - off] = tau;
+                zs[last - off] = 0.0;
+                const double dl = ds[last - off], di = ds[p - off];
+                ds[last - off] = dl * cc * cc + di * sn * sn;
+                ds[p - off] = dl * sn * sn + di * cc * cc;
+                atomicAnd(&m.kept[last >> 5], ~(1u << (last & 31)));
+                m.rot_a[off + nrot] = last - off;
+                m.rot_b[off + nrot] = p - off;
+                m.rot_c[off + nrot] = cc;
+                m.rot_s[off + nrot] = sn;
+                ++nrot;
+                last = p;
+                p = next_bit(m.weighty, p + 1, end);
+            } while (p < end && turn_of(last - off, p - off, tau, cc, sn));
+            if (p < end) p = next_bit(m.turns, p + 1, end);
+        }
+        m.nrot[off] = nrot;
+    }
+    __syncthreads();
+    const int K = count_bits(m.kept, off, end), nrot = n > 0 ? m.nrot[off] : 0;
+    if (t < n) {
+        const bool kept = m.kept[(off + t) >> 5] >> ((off + t) & 31) & 1;
+        const int j = count_bits(m.kept, off, off + t);
+        slot_of[t] = kept ? j : -1;
+        if (kept) {
+            const double zj = zs[t];
+            ndx[j] = t;
+            dn[j] = ds[t];
+            zn[j] = zj;
+            z2n[j] = zj * zj;
+        }
+    }
+    __syncthreads();
+    // secular roots: quad j finds root j from its nearer pole (bracket, then Newton); lane q
+    // of the quad forms the terms i = 4 l + q
+    if (quad < K) {
+        const int j = quad, K4 = K & ~3;
         int o;
         double a, b;
         if (j < K - 1) {
             const double mid = 0.5 * (dn[j] + dn[j + 1]);
             double f = 1.0;
-            for (int i = 0; i < K; ++i) f += rho * z2n[i] / (dn[i] - mid);
+#pragma unroll 2
+            for (int i = 0; i < K; i += 4) {
+                const int iq = min(i + q, K - 1);
+                const double v = rho * z2n[iq] / (dn[iq] - mid);
+                f += quad_get<0>(v);
+                if (i + 1 < K) f += quad_get<1>(v);
+                if (i + 2 < K) f += quad_get<2>(v);
+                if (i + 3 < K) f += quad_get<3>(v);
+            }
             if (f > 0.0) {
                 o = j;
                 a = 0.0;
@@ -179,108 +248,240 @@ __global__ void __launch_bounds__(DC_THREADS) dc_merge(int c, int h, const doubl
                 b = 0.0;
             }
         } else {
+            double z2sum = 0.0;
+            for (int i = 0; i < K; ++i) z2sum += z2n[i];
             o = K - 1;
             a = 0.0;
             b = rho * z2sum;
         }
-        // Newton on h(t) = t f(t), which has the same root but no pole at the origin
-        // (that term of t f is the constant -rho z_o^2; the other pole is at least twice
+        // Newton on h(x) = x f(x), which has the same root but no pole at the origin
+        // (that term of x f is the constant -rho z_o^2; the other pole is at least twice
         // as far as the root).  The iterate stays inside the bracket [a, b] that each
-        // evaluation's sign of f narrows (f increases in t); a step that leaves it is
-        // replaced by the bracket's midpoint.
+        // evaluation's sign of f narrows (f increases in x); a step that leaves it is
+        // replaced by the bracket's midpoint.  Every lane of the quad takes the same steps.
         const double dorg = dn[o];
-        double t = 0.5 * (a + b);
+        double x = 0.5 * (a + b);
         for (int it = 0; it < 256; ++it) {
-            double f0 = 0.0, f1 = 0.0, f2 = 0.0, f3 = 0.0, g0 = 0.0, g1 = 0.0, g2 = 0.0, g3 = 0.0;
-            int i = 0;
-            for (; i + 4 <= K; i += 4) {
-                const double q0 = 1.0 / ((dn[i] - dorg) - t), q1 = 1.0 / ((dn[i + 1] - dorg) - t);
-                const double q2 = 1.0 / ((dn[i + 2] - dorg) - t), q3 = 1.0 / ((dn[i + 3] - dorg) - t);
-                const double w0 = z2n[i] * q0, w1 = z2n[i + 1] * q1, w2 = z2n[i + 2] * q2, w3 = z2n[i + 3] * q3;
-                f0 += w0;
-                f1 += w1;
-                f2 += w2;
-                f3 += w3;
-                g0 = fma(w0, q0, g0);
-                g1 = fma(w1, q1, g1);
-                g2 = fma(w2, q2, g2);
-                g3 = fma(w3, q3, g3);
+            // lane q: the sums over i = 4 l + q below K4; lane 0 also the rest, in order
+            double fq = 0.0, gq = 0.0;
+#pragma unroll 4
+            for (int i = q; i < K4; i += 4) {
+                const double qi = 1.0 / ((dn[i] - dorg) - x), w = z2n[i] * qi;
+                fq += w;
+                gq = fma(w, qi, gq);
             }
-            for (; i < K; ++i) {
-                const double q = 1.0 / ((dn[i] - dorg) - t), w = z2n[i] * q;
-                f0 += w;
-                g0 = fma(w, q, g0);
-            }
-            const double f = fma(rho, (f0 + f1) + (f2 + f3), 1.0);
-            const double fp = rho * ((g0 + g1) + (g2 + g3));
+            if (q == 0)
+                for (int i = K4; i < K; ++i) {
+                    const double qi = 1.0 / ((dn[i] - dorg) - x), w = z2n[i] * qi;
+                    fq += w;
+                    gq = fma(w, qi, gq);
+                }
+            const double fs = (quad_get<0>(fq) + quad_get<1>(fq)) + (quad_get<2>(fq) + quad_get<3>(fq));
+            const double gs = (quad_get<0>(gq) + quad_get<1>(gq)) + (quad_get<2>(gq) + quad_get<3>(gq));
+            const double f = fma(rho, fs, 1.0);
+            const double fp = rho * gs;
             if (f == 0.0) break;
-            if (f > 0.0) b = t;
-            else a = t;
-            const double step = t * f / fma(t, fp, f);
-            double tn = t - step;
-            if (fabs(step) <= 2.0 * EPS * fabs(t)) {
-                t = tn;
+            if (f > 0.0) b = x;
+            else a = x;
+            const double dx = x * f / fma(x, fp, f);
+            double xn = x - dx;
+            if (fabs(dx) <= 2.0 * EPS * fabs(x)) {
+                x = xn;
                 break;
             }
-            if (!(tn > a && tn < b)) tn = 0.5 * (a + b);
-            t = tn;
+            if (!(xn > a && xn < b)) xn = 0.5 * (a + b);
+            x = xn;
             if (b - a <= 2.0 * EPS * fmax(fabs(a), fabs(b))) break;
         }
-        orgn[j] = o;
-        taun[j] = t;
-        lamn[j] = dorg + t;
+        if (q == 0) {
+            orgn[j] = o;
+            taun[j] = x;
+            lamn[j] = dorg + x;
+        }
     }
     __syncthreads();
-    // Loewner: zh_i^2 = prod_j (x_j - d_i) / prod_{j != i} (d_j - d_i) / rho
-    for (int i = tid; i < K; i += DC_THREADS) {
+    // Loewner: zh_i^2 = prod_j (x_j - d_i) / prod_{j != i} (d_j - d_i) / rho; the quad's
+    // lanes form four quotients at a time, multiplied in order
+    if (quad < K) {
+        const int i = quad;
         const double di = dn[i];
         double p = (dn[orgn[K - 1]] - di) + taun[K - 1];
-        for (int j = 0; j < K - 1; ++j) {
+#pragma unroll 2
+        for (int j0 = 0; j0 < K - 1; j0 += 4) {
+            const int j = min(j0 + q, K - 2);
             const double lj = (dn[orgn[j]] - di) + taun[j];
             const double dd = j >= i ? dn[j + 1] - di : dn[j] - di;
-            p *= lj / dd;
+            const double v = lj / dd;
+            p *= quad_get<0>(v);
+            if (j0 + 1 < K - 1) p *= quad_get<1>(v);
+            if (j0 + 2 < K - 1) p *= quad_get<2>(v);
+            if (j0 + 3 < K - 1) p *= quad_get<3>(v);
         }
         p /= rho;
-        zh[i] = copysign(sqrt(fmax(p, 0.0)), zn[i]);
+        if (q == 0) zh[i] = copysign(sqrt(fmax(p, 0.0)), zn[i]);
     }
     __syncthreads();
     // U (K x K, column j = normalised zh / (d - x_j)) in the block region of U
-    for (int j = tid; j < K; j += DC_THREADS) {
+    if (quad < K) {
+        double* Uj = U + (int64_t)(s + quad) * c + s;
+        const double dj = dn[orgn[quad]], tj = taun[quad];
         double ss = 0.0;
-        for (int i = 0; i < K; ++i) {
-            const double v = zh[i] / ((dn[i] - dn[orgn[j]]) - taun[j]);
-            ss = fma(v, v, ss);
+#pragma unroll 2
+        for (int i = 0; i < K; i += 4) {
+            const int iq = min(i + q, K - 1);
+            const double v = zh[iq] / ((dn[iq] - dj) - tj);
+            if (i + q < K) Uj[iq] = v;
+            const double v0 = quad_get<0>(v), v1 = quad_get<1>(v), v2 = quad_get<2>(v), v3 = quad_get<3>(v);
+            ss = fma(v0, v0, ss);
+            if (i + 1 < K) ss = fma(v1, v1, ss);
+            if (i + 2 < K) ss = fma(v2, v2, ss);
+            if (i + 3 < K) ss = fma(v3, v3, ss);
         }
         const double inv = 1.0 / sqrt(ss);
-        for (int i = 0; i < K; ++i) U[(int64_t)(s + j) * c + s + i] = zh[i] / ((dn[i] - dn[orgn[j]]) - taun[j]) * inv;
+        for (int i = q; i < K; i += 32) {   // the lane's own entries, eight in flight
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = Uj[min(i + 4 * u, K - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i + 4 * u < K) Uj[i + 4 * u] = v[u] * inv;
+        }
     }
     // rotated basis R: row r, sorted column p = column pcol[p] of diag(Q_A, Q_B) (only the
-    // diagonal blocks of Qin are current; the rest is zero), then the deflation
-    // rotations in order (one thread per row)
-    for (int r = tid; r < n; r += DC_THREADS) {
-        double* Rr = R + s + r;   // R[(s + p) * c + s + r]
-        for (int p = 0; p < n; ++p) {
-            const int q = pcol[p];
-            Rr[(int64_t)(s + p) * c] = (q < ha) == (r < ha) ? Qin[(int64_t)(s + q) * c + s + r] : 0.0;
-        }
-        for (int q = 0; q < nrot; ++q) {
-            const int pa = rot_a[q], pb = rot_b[q];
-            const double cc = rot_c[q], sn = rot_s[q];
-            const double xa = Rr[(int64_t)(s + pa) * c], xb = Rr[(int64_t)(s + pb) * c];
-            Rr[(int64_t)(s + pa) * c] = cc * xa + sn * xb;
-            Rr[(int64_t)(s + pb) * c] = -sn * xa + cc * xb;
+    // diagonal blocks of Qin are current; the rest is zero), then the deflation rotations in
+    // order (one thread per row).  Row r's operands are columns that no earlier rotation has
+    // written, but for a pair's first one where it is the second of the pair before.
+    const int r = t & (2 * h - 1);
+    double* Rr = R + (int64_t)s * c + s + r;   // Rr[p * c] = R(r, p)
+    if (r < n) {
+        const double* Qr = Qin + (int64_t)s * c + s + r;
+        for (int p0 = t / (2 * h); p0 < n; p0 += 32) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = Qr[(int64_t)pcol[min(p0 + 4 * u, n - 1)] * c];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int p = p0 + 4 * u;
+                if (p < n) Rr[(int64_t)p * c] = (pcol[p] < ha) == (r < ha) ? v[u] : 0.0;
+            }
         }
     }
-    // the merged basis (R[:, ndx] U, deflated columns as rotated) is formed by dc_merge_gemm
-    if (tid == 0) Kg[blockIdx.x] = K;
-    for (int p = tid; p < n; p += DC_THREADS) {
-        slot_g[s + p] = slot_of[p];
-        ndx_g[s + p] = p < K ? ndx[p] : 0;
+    __syncthreads();
+    if (t < n && nrot > 0) {
+        const int* ra = m.rot_a + off;
+        const int* rb = m.rot_b + off;
+        double carried = 0.0;
+        for (int u0 = 0; u0 < nrot; u0 += 4) {
+            double xa4[4], xb4[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int w = min(u0 + u, nrot - 1);
+                xa4[u] = Rr[(int64_t)ra[w] * c];
+                xb4[u] = Rr[(int64_t)rb[w] * c];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int w = u0 + u;
+                if (w >= nrot) break;
+                const int pa = ra[w], pb = rb[w];
+                const double cc = m.rot_c[off + w], sn = m.rot_s[off + w];
+                const double xa = w > 0 && pa == rb[w - 1] ? carried : xa4[u], xb = xb4[u];
+                Rr[(int64_t)pa * c] = cc * xa + sn * xb;
+                carried = -sn * xa + cc * xb;
+                Rr[(int64_t)pb * c] = carried;
+            }
+        }
     }
-    for (int p = tid; p < n; p += DC_THREADS) {
-        const int j = slot_of[p];
-        const double v = j < 0 ? ds[p] : lamn[j];
-        lam_out[s + p] = neg ? -v : v;
+    if (t < n) {
+        const int j = slot_of[t];
+        const double v = j < 0 ? ds[t] : lamn[j];
+        lam_out[s + t] = neg ? -v : v;
+    }
+    return K;
+}
+
+// Merges of one level, a workgroup each; the merged basis (R[:, ndx] U, deflated columns as
+// rotated) is formed by dc_merge_gemm.
+__global__ void __launch_bounds__(DC_THREADS) dc_merge(int c, int h, const double* __restrict__ e,
+                                                       const double* __restrict__ lam_in, const double* __restrict__ Qin,
+                                                       double* __restrict__ lam_out, double* __restrict__ Qout,
+                                                       double* __restrict__ R, double* __restrict__ U,
+                                                       int* __restrict__ Kg, int* __restrict__ ndx_g,
+                                                       int* __restrict__ slot_g) {
+    __shared__ MergeLds m;
+    const int t = threadIdx.x;
+    const int s = blockIdx.x * 2 * h;
+    if (s >= c) return;                                   // whole workgroup
+    const int ha = min(h, c - s);
+    const int hb = min(h, c - s - ha);
+    const int n = ha + hb;
+    if (hb == 0) {
+        // nothing to merge: copy the block (dc_merge_gemm skips it)
+        if (t == 0) Kg[blockIdx.x] = -1;
+        for (int u = t; u < n * n; u += (int)blockDim.x) {
+            const int col = s + u / n, row = s + u % n;
+            Qout[(int64_t)col * c + row] = Qin[(int64_t)col * c + row];
+        }
+        for (int u = t; u < n; u += (int)blockDim.x) lam_out[s + u] = lam_in[s + u];
+        return;
+    }
+    const int K = merge_block(m, c, h, s, 0, n, ha, t, e, lam_in, Qin, lam_out, R, U);
+    if (t == 0) Kg[blockIdx.x] = K;
+    if (t < n) {
+        slot_g[s + t] = m.slot_of[t];
+        ndx_g[s + t] = t < K ? m.ndx[t] : 0;
+    }
+}
+
+// The levels up to blocks of DC_FIRST columns in one launch: a workgroup takes a block's
+// leaves through all of them, its merges side by side, and forms each merged basis.  Ten
+// launches of 5 to 25 us, mostly fetching the same code anew, took 110 us at c = 50,
+// this one 79.  In: d, e; out: lam, Q (in the first of each pair after an even
+// number of levels, else in the second).
+constexpr int DC_FIRST = 32;
+
+__global__ void __launch_bounds__(4 * DC_FIRST) dc_first(int c, const double* __restrict__ e, double* lam_a, double* Qa,
+                                                         double* lam_b, double* Qb, double* R, double* U) {
+    __shared__ MergeLds m;
+    for (int h = 1; h < DC_FIRST && h < c; h *= 2) {
+        const int t = threadIdx.x & (8 * h - 1), off = threadIdx.x / (8 * h) * (2 * h);
+        const int s = blockIdx.x * DC_FIRST + off;
+        const int ha = max(0, min(h, c - s)), hb = max(0, min(h, c - s - ha)), n = hb > 0 ? ha + hb : 0;
+        const int K = merge_block(m, c, h, s, off, n, ha, t, e, lam_a, Qa, lam_b, R, U);
+        __syncthreads();
+        const int r = t & (2 * h - 1);
+        if (hb == 0) {   // nothing to merge: copied
+            for (int p = t / (2 * h); p < ha && r < ha; p += 4) Qb[(int64_t)(s + p) * c + s + r] = Qa[(int64_t)(s + p) * c + s + r];
+            if (t < ha) lam_b[s + t] = lam_a[s + t];
+        }
+        for (int p = t / (2 * h); p < n && r < n; p += 4) {
+            const int j = m.slot_of[off + p];
+            double acc = 0.0;
+            if (j < 0) {
+                acc = R[(int64_t)(s + p) * c + s + r];
+            } else {
+                for (int k0 = 0; k0 < K; k0 += 8) {
+                    double a[8], b[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int k = min(k0 + u, K - 1);
+                        a[u] = R[(int64_t)(s + m.ndx[off + k]) * c + s + r];
+                        b[u] = U[(int64_t)(s + j) * c + s + k];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (k0 + u < K) acc = fma(a[u], b[u], acc);
+                }
+            }
+            Qb[(int64_t)(s + p) * c + s + r] = acc;
+        }
+        __syncthreads();
+        double* x = Qa;
+        Qa = Qb;
+        Qb = x;
+        x = lam_a;
+        lam_a = lam_b;
+        lam_b = x;
     }
 }
 
@@ -347,7 +548,15 @@ __global__ void __launch_bounds__(64) dc_gemm_nn(int c, const double* __restrict
     if (r >= c) return;
     const double* bc = B + (int64_t)col * c;
     double acc = 0.0;
-    for (int k = 0; k < c; ++k) acc = fma(A[(int64_t)k * c + r], bc[k], acc);
+    int k = 0;
+    for (; k + 16 <= c; k += 16) {   // sixteen in flight, added in order
+        double a[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) a[u] = A[(int64_t)(k + u) * c + r];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc = fma(a[u], bc[k + u], acc);
+    }
+    for (; k < c; ++k) acc = fma(A[(int64_t)k * c + r], bc[k], acc);
     C[(int64_t)col * c + r] = acc;
 }
 
@@ -369,11 +578,16 @@ int tridiag_dc(hipStream_t st, int c, const double* d, const double* e, const do
     int* ndx_g = Kg + c;
     int* slot_g = ndx_g + c;
     hipLaunchKernelGGL(dc_leaves, dim3(ceil_div((int64_t)cc, 256)), dim3(256), 0, st, c, d, e, la, Qa, status);
-    for (int h = 1; h < c; h *= 2) {
+    hipLaunchKernelGGL(dc_first, dim3(ceil_div(c, DC_FIRST)), dim3(4 * DC_FIRST), 0, st, c, e, la, Qa, lb, Qb, R, U);
+    int h = 1;
+    for (; h < DC_FIRST && h < c; h *= 2) {
+        std::swap(Qa, Qb);
+        std::swap(la, lb);
+    }
+    for (; h < c; h *= 2) {
         const int nb = ceil_div(c, 2 * h);
         const int tpd = ceil_div(2 * h, MG_T);
-        hipLaunchKernelGGL(dc_merge, dim3(nb), dim3(DC_THREADS), 0, st, c, h, e, la, Qa, lb, Qb, R, U, Kg, ndx_g,
-                           slot_g);
+        hipLaunchKernelGGL(dc_merge, dim3(nb), dim3(8 * h), 0, st, c, h, e, la, Qa, lb, Qb, R, U, Kg, ndx_g, slot_g);
         hipLaunchKernelGGL(dc_merge_gemm, dim3(nb, tpd * tpd), dim3(256), 0, st, c, h, R, U, Kg, ndx_g, slot_g, Qb);
         std::swap(Qa, Qb);
         std::swap(la, lb);
