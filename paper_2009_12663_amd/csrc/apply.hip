@@ -38,16 +38,31 @@ __global__ void __launch_bounds__(SUM_THREADS) reduce_partials(int64_t count, in
 }
 
 // Where a small solve writes column j of P and T: column-major k x c each, or the packed
-// [T ; -P] that pass 2 reads (with the zero rows that fill its last step).
+// [T ; -P] that the float64 pass 2 reads (with the zero rows that fill its last step), or the
+// two bfloat16 halves of [-P ; T] that the bfloat16 pass 2 reads.
 struct SolveOut {
     double *P, *T, *M;
     int k, cblocks;
+    uint16_t *hi, *lo;   // column j from j * 2 * rows: -P, then T, each k entries and zeros up to rows
+    int rows;
+    __device__ __forceinline__ void put_halves(int q, int j, double v) const {
+        const bf16_t h = float_to_bf16((float)v);
+        hi[(int64_t)j * 2 * rows + q] = h.bits;
+        lo[(int64_t)j * 2 * rows + q] = float_to_bf16((float)(v - (double)bf16_to_float(h))).bits;
+    }
     __device__ __forceinline__ void put(int i, int j, double pv, double tv) const {
         if (M) {
             M[nn_pack_index(i, j, cblocks)] = tv;
             M[nn_pack_index(k + i, j, cblocks)] = -pv;
             if (i == 0)
                 for (int q = 2 * k; q % 4; ++q) M[nn_pack_index(q, j, cblocks)] = 0.0;
+        } else if (hi) {
+            put_halves(i, j, -pv);
+            put_halves(rows + i, j, tv);
+            for (int q = k + i; q < rows; q += k) {
+                put_halves(q, j, 0.0);
+                put_halves(rows + q, j, 0.0);
+            }
         } else {
             P[(int64_t)j * k + i] = pv;
             T[(int64_t)j * k + i] = tv;
@@ -470,8 +485,8 @@ int apply_few(bfgsuq_ctx* h, const Tv* V, int c, To* out, bool diff, const Apply
     if (k <= 256) {
         ProfScope ps(h, "apply_solve");
         hipLaunchKernelGGL(small_solve_few, dim3(c), dim3((unsigned)(FEW_SEGS * round_up(k, 64))), 0, h->stream, k,
-                           h->kmax, h->Rm, h->Rinv, h->RinvT, h->YHY, Z, SolveOut{P, T, nullptr, k, 0}, h->status);
-    } else if (int rc = apply_small_solve(h, c, Z, P, T)) {
+                           h->kmax, h->Rm, h->Rinv, h->RinvT, h->YHY, Z, SolveOut{P, T, nullptr, k, 0, nullptr, nullptr, 0}, h->status);
+    } else if (int rc = small_solve_launch(h, c, Z, SolveOut{P, T, nullptr, k, 0, nullptr, nullptr, 0})) {
         return rc;
     }
     ProfScope ps(h, diff ? "hdiff_gemm2" : "apply_gemm2");
@@ -535,7 +550,7 @@ int apply_generic(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, c
     prof_begin(h, "apply_reduce");
     if (int rc2 = sum_partials(h->stream, (int64_t)twok * c, plan.nchunks, part, Z)) return rc2;
     prof_end(h);
-    if (int rc2 = small_solve_launch(h, c, Z, SolveOut{nullptr, nullptr, M, k, ceil_div(c, 16)})) return rc2;
+    if (int rc2 = small_solve_launch(h, c, Z, SolveOut{nullptr, nullptr, M, k, ceil_div(c, 16), nullptr, nullptr, 0})) return rc2;
     prof_begin(h, diff ? "hdiff_gemm2" : "apply_gemm2");
     launch_gemm2<Ts, Th, To, Tv>(h->stream, n, h->ld, k, c, (const Ts*)h->S, (const Ts*)h->Y, h0, V, n, M, out, diff);
     prof_end(h);
@@ -582,7 +597,7 @@ int apply_streamed(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff) 
     }
     const int64_t count = (int64_t)twok * c;
     if ((rc = sum_partials(h->stream, count, used, part, Z)) != BFGS_OK) return rc;
-    if ((rc = small_solve_launch(h, c, Z, SolveOut{nullptr, nullptr, M, k, ceil_div(c, 16)})) != BFGS_OK) return rc;
+    if ((rc = small_solve_launch(h, c, Z, SolveOut{nullptr, nullptr, M, k, ceil_div(c, 16), nullptr, nullptr, 0})) != BFGS_OK) return rc;
     ProfScope ps(h, diff ? "hdiff_stream_pass2" : "apply_stream_pass2");
     rc = stream_slices(h, k, [&](int, int64_t r0, int64_t rows, const void* Sst, const void* Yst) {
         launch_gemm2<Ts, Th, To, Tv>(h->stream, rows, h->slice_ld, k, c, (const Ts*)Sst, (const Ts*)Yst, h0 + r0, V + r0,
@@ -807,8 +822,8 @@ int sum_partials(hipStream_t st, int64_t count, int nchunks, const double* part,
     return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
 }
 
-int apply_small_solve(bfgsuq_ctx* h, int c, const double* Z, double* P, double* T) {
-    return small_solve_launch(h, c, Z, SolveOut{P, T, nullptr, h->k, 0});
+int apply_small_solve_halves(bfgsuq_ctx* h, int c, const double* Z, int rows, uint16_t* hi, uint16_t* lo) {
+    return small_solve_launch(h, c, Z, SolveOut{nullptr, nullptr, nullptr, h->k, 0, hi, lo, rows});
 }
 
 bool apply_takes_tiles(int ncols) { return ncols > STREAM_COLS; }

@@ -39,6 +39,12 @@ struct alignas(16) u16x8 {
 
 __device__ __forceinline__ bf16x8 as_bf16x8(const uint4 u) { return __builtin_bit_cast(bf16x8, u); }
 
+// A store that keeps no place in the caches.
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_past(float* p, float4 v) {
+    __builtin_nontemporal_store(floatx4{v.x, v.y, v.z, v.w}, (floatx4*)p);
+}
+
 __device__ __forceinline__ floatx16 mfma32(bf16x8 a, bf16x8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -266,26 +272,14 @@ __global__ void reduce_z(int64_t count, int twok, int k, int nk, const float* __
     Z[e] = s;
 }
 
-// small^T (hi, lo): column j, position q of [Y phase (Gp*16) | S phase (Gp*16)]:
-//   Y phase: -P(p, j), S phase: T(p, j), zero beyond k or c.
-__global__ void pack_small(int k, int c, int cpad, int Gp, const double* __restrict__ P, const double* __restrict__ T,
-                           uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
-    const int K2 = 2 * Gp * 16;
-    const int64_t total = (int64_t)cpad * K2;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const int j = (int)(e / K2), q = (int)(e % K2);
-        const int phase = q / (Gp * 16), pp = q % (Gp * 16);
-        double v = 0.0;
-        if (j < c && pp < k) v = phase == 0 ? -P[(int64_t)j * k + pp] : T[(int64_t)j * k + pp];
-        const float vf = (float)v;
-        const uint16_t h = bf16_bits_rne(vf);
-        hi[e] = h;
-        lo[e] = bf16_bits_rne((float)(v - (double)bits_to_f32(h)));
-    }
-}
-
 // ---------------------------------------------------------------------------
-// Pass 2: eight 32-row groups per workgroup (256 rows), MT2 column tiles.
+// Pass 2: eight 32-row groups per workgroup (256 rows), MT2 column tiles.  Memory bounds it
+// (pairs, V and out: 3.9 GB at n = 1,785,000, k = 200, c = 220).  A workgroup walks its
+// row blocks: the pairs and the small operand of the next block, and V a pass ahead, are
+// on their way while one's output goes out, where a workgroup to a block waited for each
+// in turn (1251 us, 1118 so); and the output, which nothing reads soon, is stored past the
+// caches (1057 us).  Half the rows to a workgroup, two at once, instead: 1384 us (the small
+// operand is read twice as often).
 // ---------------------------------------------------------------------------
 constexpr int G2_ROWS = 256;
 constexpr int SM_LD = 40;        // LDS pitch of a staged small column: 32 pairs + 8 pad
@@ -305,7 +299,7 @@ struct G2Shape {
 };
 
 template <int MT2, bool DIFF>
-__global__ void __launch_bounds__(G2Shape<MT2>::THREADS) gemm2_mfma(int64_t n, int c, int G, int Gp,
+__global__ void __launch_bounds__(G2Shape<MT2>::THREADS, 4) gemm2_mfma(int64_t n, int c, int G, int Gp,
                                                                    const bf16_t* __restrict__ Y2,
                                                                    const bf16_t* __restrict__ S2,
                                                                    const uint16_t* __restrict__ shi,
@@ -313,34 +307,38 @@ __global__ void __launch_bounds__(G2Shape<MT2>::THREADS) gemm2_mfma(int64_t n, i
                                                                    const float* __restrict__ h0,
                                                                    const bf16_t* __restrict__ V, float* __restrict__ out) {
     constexpr int SPLIT = G2Shape<MT2>::SPLIT, MH = G2Shape<MT2>::MH, NTH = G2Shape<MT2>::THREADS;
-    // LDS: two buffers of the staged small operand (hi, lo), [col][SM_LD]
+    // LDS: two buffers of the staged small operand (hi, lo), [col][SM_LD], and the output tiles
     extern __shared__ unsigned char smem_raw[];
     constexpr int BUF = MT2 * 32 * SM_LD;
     uint16_t* sm = (uint16_t*)smem_raw;   // buffer b: hi at sm + 2*b*BUF, lo at sm + (2*b+1)*BUF
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5;
+    float* ep = (float*)(smem_raw + 4 * BUF * sizeof(uint16_t));   // [SPLIT * 32][G2_EP_LD]
     // row group and column share; the share alternates between waves 4 apart, which
     // sit on the same SIMD, so every SIMD gets one wave of each share
-    const int rg = wave / SPLIT, cs = SPLIT == 2 ? ((wave ^ (wave >> 2)) & 1) : 0;
-    const int mt0 = cs * MH;                               // first column tile of this wave
-    const int ntw = min(MH, MT2 - mt0);                    // tiles of this wave (uniform)
-    // Row block: workgroup g runs on XCD g % 8, and each XCD walks a contiguous eighth
-    // of the row blocks in order, so the column-major V reads and output writes of the
-    // workgroups an XCD runs at once form long runs per column.
+    struct Place {
+        int tid, lane, wave, rg, cs, mt0, ntw;
+        // of the calling thread, found anew (not kept in registers across a block's phases)
+        __device__ __forceinline__ Place() {
+            tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));
+            lane = tid & 63;
+            wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+            rg = wave / SPLIT;
+            cs = SPLIT == 2 ? ((wave ^ (wave >> 2)) & 1) : 0;
+            mt0 = cs * MH;                                 // first column tile of this wave
+            ntw = min(MH, MT2 - mt0);                      // tiles of this wave (uniform)
+        }
+    };
+    // Row blocks: workgroup g runs on XCD g % 8, and the workgroups of an XCD walk a
+    // contiguous eighth of the row blocks side by side, so the column-major V reads and
+    // output writes that an XCD has in flight form long runs per column.
     const int nblk = (int)((n + G2_ROWS - 1) / G2_ROWS), per_xcd = (nblk + 7) / 8;
-    const int blk = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (blk >= nblk) return;                              // whole workgroup
-    const int64_t row_base = (int64_t)blk * G2_ROWS + rg * 32;
-    const int64_t rb32 = row_base / 32;
+    const int first = (blockIdx.x % 8) * per_xcd, stop = min(nblk, first + per_xcd), slots = gridDim.x / 8;
+    int blk = first + blockIdx.x / 8;
+    if (blk >= stop) return;                              // whole workgroup
     const int K2 = 2 * Gp * 16;
-    const int nchunks = K2 / 32;
-    const bool row_ok = row_base + (lane & 31) < n;
-    const float h0r = row_ok ? h0[row_base + (lane & 31)] : 0.f;
-
-    floatx16 acc[MH];
-#pragma unroll
-    for (int t = 0; t < MH; ++t)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+    const int nchunks = K2 / 32;                          // even: the chunks' buffers alternate across blocks
+    constexpr int DEPTH = MH >= 4 ? 2 : 4;
+    const int steps = (nchunks + DEPTH - 1) / DEPTH * DEPTH;
 
     constexpr int SCH = MT2 * 32 * 4;        // 16-byte chunks of one array per staged chunk (<= 1024)
     static_assert(SCH <= 1024, "one staging chunk per thread and array");
@@ -348,14 +346,14 @@ __global__ void __launch_bounds__(G2Shape<MT2>::THREADS) gemm2_mfma(int64_t n, i
 #define G2_LOAD_SMALL(T)                                                        \
     {                                                                           \
         if (tid < SCH) {                                                        \
-            const int64_t off = (int64_t)(tid >> 2) * K2 + (T) * 32 + (tid & 3) * 8; \
-            sh0 = *(const uint4*)(shi + off);                                   \
-            sl0 = *(const uint4*)(slo + off);                                   \
+            const uint32_t off = (uint32_t)((tid >> 2) * K2 + (tid & 3) * 8);   \
+            sh0 = *(const uint4*)(shi + (T) * 32 + off);                        \
+            sl0 = *(const uint4*)(slo + (T) * 32 + off);                        \
         }                                                                       \
         if (NTH < SCH && tid + NTH < SCH) {                                     \
-            const int64_t off = (int64_t)((tid + NTH) >> 2) * K2 + (T) * 32 + (tid & 3) * 8; \
-            sh1 = *(const uint4*)(shi + off);                                   \
-            sl1 = *(const uint4*)(slo + off);                                   \
+            const uint32_t off = (uint32_t)(((tid + NTH) >> 2) * K2 + (tid & 3) * 8); \
+            sh1 = *(const uint4*)(shi + (T) * 32 + off);                        \
+            sl1 = *(const uint4*)(slo + (T) * 32 + off);                        \
         }                                                                       \
     }
 #define G2_STORE_SMALL(B)                                                                   \
@@ -371,134 +369,169 @@ __global__ void __launch_bounds__(G2Shape<MT2>::THREADS) gemm2_mfma(int64_t n, i
             *(uint4*)(L_ + ((tid + NTH) >> 2) * SM_LD + (tid & 3) * 8) = sl1;               \
         }                                                                                   \
     }
-    // Every call issues a load: a chunk past the end re-reads the last chunk (unused), and a
-    // padding group past G re-reads group G - 1, whose product with the zero rows of the
-    // small operand is exactly zero.  With no branch or select on the result, each prefetch
-    // slot stays in one register set and the loop carries no copies (nor the wait for all
-    // outstanding loads that such copies would force at the back edge).
-    auto load_b = [&](int t, int sg) -> uint4 {
-        const int gq = 2 * min(t, nchunks - 1) + sg;
+    // Every call issues a load: a step past the last chunk re-reads it (unused), one past
+    // the block's steps reads the next block's, and a padding group past G re-reads group
+    // G - 1, whose product with the zero rows of the small operand is exactly zero.  With no
+    // branch or select on the result, each prefetch slot stays in one register set and the
+    // loop carries no copies (nor the wait for all outstanding loads that such copies would
+    // force at the back edge).
+    auto load_b = [&](int lane, int t, int sg, int64_t rb32, int64_t next32) -> uint4 {
+        const bool over = t >= steps;
+        const int gq = 2 * min(over ? t - steps : t, nchunks - 1) + sg;
         const int phase = gq >= Gp ? 1 : 0;
         const int grp = min(gq - phase * Gp, G - 1);
         const bf16_t* W = phase ? S2 : Y2;
-        return *(const uint4*)(W + rb32 * (int64_t)G * 512 + (int64_t)grp * 512 + (lane & 31) * 16 + half * 8);
+        const bf16_t* at = W + ((over ? next32 : rb32) * G + grp) * 512;   // uniform
+        return *(const uint4*)(at + (uint32_t)((lane & 31) * 16 + (lane >> 5) * 8));
     };
 
     // W fragments run DEPTH chunks ahead of the MFMAs.
-    constexpr int DEPTH = MH >= 4 ? 2 : 4;
     uint4 bq0[DEPTH], bq1[DEPTH];
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-        bq0[d] = load_b(d, 0);
-        bq1[d] = load_b(d, 1);
-    }
-    G2_LOAD_SMALL(0)
-    G2_STORE_SMALL(0)
-    G2_LOAD_SMALL(min(1, nchunks - 1))
-    __syncthreads();
-    for (int t0 = 0; t0 < nchunks; t0 += DEPTH) {
+    int64_t rb32;
+    {
+        const Place w;
+        const int tid = w.tid;
+        rb32 = ((int64_t)blk * G2_ROWS + w.rg * 32) / 32;
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
-            const int t = t0 + d;
-            // The loads run unconditionally (clamped chunk indices) so that the prefetch
-            // registers take the same path on every iteration; only the LDS store and the
-            // MFMAs are skipped for a chunk past the end.
-            const int buf = t & 1;
-            if (t + 1 < nchunks) G2_STORE_SMALL(buf ^ 1)
-            G2_LOAD_SMALL(min(t + 2, nchunks - 1))
-            const uint16_t* H = sm + 2 * buf * BUF;
-            const uint16_t* L = H + BUF;
+            bq0[d] = load_b(w.lane, d, 0, rb32, rb32);
+            bq1[d] = load_b(w.lane, d, 1, rb32, rb32);
+        }
+        G2_LOAD_SMALL(0)
+        G2_STORE_SMALL(0)
+        G2_LOAD_SMALL(1)
+    }
+    const bool vec = (n % 4) == 0 && (((uintptr_t)out) & 15) == 0 && (DIFF || (((uintptr_t)V) & 7) == 0);
+    auto row_scale = [&](int64_t rb) {
+        const int64_t r = rb * 32 + (threadIdx.x & 31);
+        return r < n ? h0[r] : 0.f;
+    };
+    float h0r = row_scale(rb32);
+    __syncthreads();
+    for (; blk < stop; blk += slots) {
+        const int64_t next32 = blk + slots < stop ? rb32 + (int64_t)slots * (G2_ROWS / 32) : rb32;
+        floatx16 acc[MH];
 #pragma unroll
-            for (int sg = 0; sg < 2; ++sg) {
-                if (t < nchunks) {
-                    const bf16x8 b = as_bf16x8(sg ? bq1[d] : bq0[d]);
+        for (int t = 0; t < MH; ++t)
 #pragma unroll
-                    for (int m = 0; m < MH; ++m) {
-                        if (m < ntw) {
-                            const int off = ((mt0 + m) * 32 + (lane & 31)) * SM_LD + sg * 16 + half * 8;
-                            acc[m] = mfma32(as_bf16x8(*(const uint4*)(H + off)), b, acc[m]);
-                            acc[m] = mfma32(as_bf16x8(*(const uint4*)(L + off)), b, acc[m]);
+            for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+        auto group = [&](const Place& w, int t0) {
+            const int tid = w.tid, lane = w.lane, half = lane >> 5, mt0 = w.mt0, ntw = w.ntw;
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                const int t = t0 + d;
+                // The loads run unconditionally so that the prefetch registers take the same
+                // path on every iteration; only the LDS store and the MFMAs are skipped for a
+                // step past the last chunk.  The chunks go round: the last steps stage the
+                // first chunks for the next block.
+                const int buf = t & 1;
+                if (t < nchunks) G2_STORE_SMALL(buf ^ 1)
+                const int ahead = min(t + 2, nchunks + 1);
+                G2_LOAD_SMALL(ahead >= nchunks ? ahead - nchunks : ahead)
+                const uint16_t* H = sm + 2 * buf * BUF;
+                const uint16_t* L = H + BUF;
+#pragma unroll
+                for (int sg = 0; sg < 2; ++sg) {
+                    if (t < nchunks) {
+                        const bf16x8 b = as_bf16x8(sg ? bq1[d] : bq0[d]);
+#pragma unroll
+                        for (int m = 0; m < MH; ++m) {
+                            if (m < ntw) {
+                                const int off = ((mt0 + m) * 32 + (lane & 31)) * SM_LD + sg * 16 + half * 8;
+                                acc[m] = mfma32(as_bf16x8(*(const uint4*)(H + off)), b, acc[m]);
+                                acc[m] = mfma32(as_bf16x8(*(const uint4*)(L + off)), b, acc[m]);
+                            }
                         }
                     }
+                    // refill the slot just consumed: its register is free once the MFMAs
+                    // above have read it, so the loop needs no register copies
+                    if (sg) bq1[d] = load_b(lane, t + DEPTH, 1, rb32, next32);
+                    else bq0[d] = load_b(lane, t + DEPTH, 0, rb32, next32);
                 }
-                // refill the slot just consumed: its register is free once the MFMAs
-                // above have read it, so the loop needs no register copies
-                if (sg) bq1[d] = load_b(t + DEPTH, 1);
-                else bq0[d] = load_b(t + DEPTH, 0);
-            }
-            if (t < nchunks) {
-                if (2 * t + 2 == Gp) {
-                    // end of the Y phase: acc holds -(Y P)^T for this lane's row; scale by h0[row]
+                if (t < nchunks) {
+                    if (2 * t + 2 == Gp) {
+                        // end of the Y phase: acc holds -(Y P)^T for this lane's row; scale by h0[row]
 #pragma unroll
-                    for (int m = 0; m < MH; ++m)
+                        for (int m = 0; m < MH; ++m)
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) acc[m][i] *= h0r;
+                            for (int i = 0; i < 16; ++i) acc[m][i] *= h0r;
+                    }
+                    __syncthreads();
                 }
-                __syncthreads();
             }
+        };
+        {
+            const Place w;
+            for (int t0 = 0; t0 + DEPTH < steps; t0 += DEPTH) group(w, t0);
+        }
+        // Output through LDS.  Pass p stages column tile p of each column share as
+        // [column][row] (256 rows per column), then every wave writes four whole columns:
+        // lane l covers rows 4l .. 4l+3 of the workgroup, so each column is one contiguous
+        // 1 KB store (16 bytes per lane) and its V rows one contiguous 512-byte load, which
+        // is in flight since the pass before (the last group of chunks for the first).
+        const Place w;
+        const int lane = w.lane, half = lane >> 5, wave = w.wave;
+        const int64_t r4 = (int64_t)blk * G2_ROWS + lane * 4;
+        float h4[4] = {0.f, 0.f, 0.f, 0.f};
+        uint2 vq[2][4];
+        auto load_v = [&](uint2 (&v)[4], int p) {
+            if (DIFF) return;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int q = wave * 4 + j, qs = q / 32, col = (qs * MH + p) * 32 + q % 32;
+                v[j] = make_uint2(0, 0);
+                const bool has = p < min(MH, MT2 - qs * MH) && col < c;
+                if (has && vec && r4 + 4 <= n) v[j] = *(const uint2*)(V + (int64_t)col * n + (int64_t)blk * G2_ROWS + (uint32_t)(lane * 4));
+            }
+        };
+        if (!DIFF) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h4[e] = r4 + e < n ? h0[r4 + e] : 0.f;
+        }
+        load_v(vq[0], 0);
+        group(w, steps - DEPTH);
+        rb32 = next32;
+        h0r = row_scale(rb32);
+#pragma unroll
+        for (int p = 0; p < MH; ++p) {
+            if (p < w.ntw) {
+                float* dst = ep + w.cs * 32 * G2_EP_LD + w.rg * 32 + (lane & 31);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) dst[(8 * (i / 4) + 4 * half + (i % 4)) * G2_EP_LD] = acc[p][i];
+            }
+            if (p + 1 < MH) load_v(vq[(p + 1) & 1], p + 1);
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int q = wave * 4 + j, qs = q / 32, col = (qs * MH + p) * 32 + q % 32;
+                if (p >= min(MH, MT2 - qs * MH) || col >= c) continue;
+                const float4 a = *(const float4*)(ep + q * G2_EP_LD + lane * 4);
+                float o[4] = {a.x, a.y, a.z, a.w};
+                float* dst = out + (int64_t)col * n + (int64_t)blk * G2_ROWS + (uint32_t)(lane * 4);
+                if (vec && r4 + 4 <= n) {
+                    if (!DIFF) {
+                        const uint2 v = vq[p & 1][j];
+                        o[0] += h4[0] * bits_to_f32((uint16_t)(v.x & 0xffffu));
+                        o[1] += h4[1] * bits_to_f32((uint16_t)(v.x >> 16));
+                        o[2] += h4[2] * bits_to_f32((uint16_t)(v.y & 0xffffu));
+                        o[3] += h4[3] * bits_to_f32((uint16_t)(v.y >> 16));
+                    }
+                    store_past(dst, make_float4(o[0], o[1], o[2], o[3]));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if (r4 + e >= n) break;
+                        float v = o[e];
+                        if (!DIFF) v += h4[e] * bits_to_f32(V[(int64_t)col * n + r4 + e].bits);
+                        dst[e] = v;
+                    }
+                }
+            }
+            __syncthreads();
         }
     }
 #undef G2_LOAD_SMALL
 #undef G2_STORE_SMALL
-    // Output through LDS.  Pass p stages column tile p of each column share as
-    // [column][row] (256 rows per column), then every wave writes four whole columns:
-    // lane l covers rows 4l .. 4l+3 of the workgroup, so each column is one contiguous
-    // 1 KB store (16 bytes per lane) and its V rows one contiguous 512-byte load.  The
-    // small-operand buffers are free by now (last barrier of the loop).
-    float* ep = (float*)smem_raw;                        // [SPLIT * 32][G2_EP_LD]
-    const int64_t r4 = (int64_t)blk * G2_ROWS + lane * 4;
-    const bool vec = (n % 4) == 0 && (((uintptr_t)out) & 15) == 0 && (DIFF || (((uintptr_t)V) & 7) == 0);
-    float h4[4] = {0.f, 0.f, 0.f, 0.f};
-    if (!DIFF) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) h4[e] = r4 + e < n ? h0[r4 + e] : 0.f;
-    }
-#pragma unroll
-    for (int p = 0; p < MH; ++p) {
-        // V rows of this pass's four columns, issued before the staging barrier
-        uint2 vq[4];
-        if (!DIFF) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int q = wave * 4 + j, qs = q / 32, col = (qs * MH + p) * 32 + q % 32;
-                vq[j] = make_uint2(0, 0);
-                const bool has = p < min(MH, MT2 - qs * MH) && col < c;
-                if (has && vec && r4 + 4 <= n) vq[j] = *(const uint2*)(V + (int64_t)col * n + r4);
-            }
-        }
-        if (p < ntw) {
-            float* dst = ep + cs * 32 * G2_EP_LD + rg * 32 + (lane & 31);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) dst[(8 * (i / 4) + 4 * half + (i % 4)) * G2_EP_LD] = acc[p][i];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int q = wave * 4 + j, qs = q / 32, col = (qs * MH + p) * 32 + q % 32;
-            if (p >= min(MH, MT2 - qs * MH) || col >= c) continue;
-            const float4 a = *(const float4*)(ep + q * G2_EP_LD + lane * 4);
-            float o[4] = {a.x, a.y, a.z, a.w};
-            float* dst = out + (int64_t)col * n + r4;
-            if (vec && r4 + 4 <= n) {
-                if (!DIFF) {
-                    o[0] += h4[0] * bits_to_f32((uint16_t)(vq[j].x & 0xffffu));
-                    o[1] += h4[1] * bits_to_f32((uint16_t)(vq[j].x >> 16));
-                    o[2] += h4[2] * bits_to_f32((uint16_t)(vq[j].y & 0xffffu));
-                    o[3] += h4[3] * bits_to_f32((uint16_t)(vq[j].y >> 16));
-                }
-                *(float4*)dst = make_float4(o[0], o[1], o[2], o[3]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (r4 + e >= n) break;
-                    float v = o[e];
-                    if (!DIFF) v += h4[e] * bits_to_f32(V[(int64_t)col * n + r4 + e].bits);
-                    dst[e] = v;
-                }
-            }
-        }
-        __syncthreads();
-    }
 }
 
 template <int NT, bool DIAG>
@@ -534,8 +567,8 @@ void launch_g2(int grid, hipStream_t st, int64_t n, int c, int G, int Gp, const 
                const uint16_t* shi, const uint16_t* slo, const float* h0, const bf16_t* V, float* out) {
     // small-operand double buffer, reused by the epilogue for SPLIT x 32 output columns
     constexpr int NTH = G2Shape<MT2>::THREADS;
-    const size_t smem = std::max((size_t)4 * MT2 * 32 * SM_LD * sizeof(uint16_t),
-                                 (size_t)G2Shape<MT2>::SPLIT * 32 * G2_EP_LD * sizeof(float));
+    const size_t smem = (size_t)4 * MT2 * 32 * SM_LD * sizeof(uint16_t) +
+                        (size_t)G2Shape<MT2>::SPLIT * 32 * G2_EP_LD * sizeof(float);
     static bool attr = false;
     if (!attr) {
         (void)hipFuncSetAttribute((const void*)gemm2_mfma<MT2, DIFF>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -582,8 +615,6 @@ bool mfma_apply_supported(const bfgsuq_ctx* h, int c) {
     return h->storage == BFGS_BF16 && h->S1 != nullptr && h->k >= 1 && h->k <= 256 && c >= 1 && c <= 256;
 }
 
-int apply_small_solve(bfgsuq_ctx* h, int c, const double* Z, double* P, double* T);
-
 size_t apply_small16_bytes(int kmax) { return (size_t)2 * 256 * 2 * (mfma_groups(kmax) + 1) * 16 * 2; }
 
 int mfma_apply(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, const ApplyWs* fixed) {
@@ -602,7 +633,7 @@ int mfma_apply(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, cons
     const int cpad = NT * 32;
     int rc;
     float* part;
-    double *Z, *P;
+    double* Z;
     uint16_t* shi;
     const size_t slot_bytes = (size_t)twok * c * sizeof(float);
     if (fixed) {
@@ -611,19 +642,15 @@ int mfma_apply(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, cons
         nk = std::min(nk, cap);
         part = (float*)fixed->part;
         Z = fixed->Z;
-        P = fixed->PT;
         shi = fixed->small16;
     } else {
         if ((rc = ensure_ws(h->part, (size_t)nk * slot_bytes)) != BFGS_OK) return rc;
         if ((rc = ensure_ws(h->Z, (size_t)2 * h->kmax * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
-        if ((rc = ensure_ws(h->PT, (size_t)2 * h->kmax * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
         if ((rc = ensure_ws(h->small16, apply_small16_bytes(h->kmax))) != BFGS_OK) return rc;
         part = (float*)h->part.ptr;
         Z = (double*)h->Z.ptr;
-        P = (double*)h->PT.ptr;
         shi = (uint16_t*)h->small16.ptr;
     }
-    double* T = P + (size_t)k * c;
     uint16_t* slo = shi + (size_t)cpad * 2 * Gp * 16;
     const bool diag = !h->gamma_mode;
     {
@@ -640,16 +667,13 @@ int mfma_apply(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, cons
         hipLaunchKernelGGL(reduce_z, dim3(ceil_div(count, 256)), dim3(256), 0, h->stream, count, twok, k, nk, part,
                            h->scalars, h->gamma_mode ? 1 : 0, Z);
     }
-    if ((rc = apply_small_solve(h, c, Z, P, T)) != BFGS_OK) return rc;
-    {
-        ProfScope ps(h, "apply_pack");
-        const int64_t total = (int64_t)cpad * 2 * Gp * 16;
-        hipLaunchKernelGGL(pack_small, dim3((int)std::min<int64_t>(2048, (total + 255) / 256)), dim3(256), 0, h->stream,
-                           k, c, cpad, Gp, P, T, shi, slo);
-    }
+    // columns past c of the last tile stay as they are: their products are not stored
+    if ((rc = apply_small_solve_halves(h, c, Z, Gp * 16, shi, slo)) != BFGS_OK) return rc;
     {
         ProfScope ps(h, diff ? "hdiff_gemm2" : "apply_gemm2");
-        const int grid = 8 * ceil_div(ceil_div(n, G2_ROWS), 8);   // whole number of blocks per XCD
+        // a whole number of workgroups per XCD, as many as run at once: one of 16 waves to
+        // a compute unit, or two of 8
+        const int grid = 8 * (int)std::min<int64_t>(ceil_div(ceil_div(n, G2_ROWS), 8), NT > 4 ? 32 : 64);
         pick_g2(NT, diff)(grid, h->stream, n, c, G, Gp, (const bf16_t*)h->Y2, (const bf16_t*)h->S2, shi, slo,
                           (const float*)h->h0, V, out);
     }

@@ -310,7 +310,7 @@ int mfma_groups(int kmax);
 int mfma_scatter_pair(bfgsuq_ctx* h, int j);
 bool mfma_apply_supported(const bfgsuq_ctx* h, int c);
 int mfma_apply(bfgsuq_ctx* h, const void* V, int c, void* out, bool diff, const ApplyWs* fixed);
-int apply_small_solve(bfgsuq_ctx* h, int c, const double* Z, double* P, double* T);
+int apply_small_solve_halves(bfgsuq_ctx* h, int c, const double* Z, int rows, uint16_t* hi, uint16_t* lo);
 
 // One problem of a persistent batched apply (device copy read by the pass kernels).
 struct PersistProblem {
