@@ -219,7 +219,9 @@ __global__ void __launch_bounds__(256) small_solve_blocks(int k, int kmax, const
 // chip otherwise idle the length of a chain is all that counts: one column at k = 100
 // takes 19 us as above, 15 in this form.  (More threads lose it again to the instructions
 // they all issue on one CU; touching the matrices ahead changes nothing.)
-constexpr int FEW_SEGS = 4;
+// From about 150 pairs the waves of a workgroup are too many for that (one column at
+// k = 200: 31 us, 26 as above).
+constexpr int FEW_SEGS = 4, FEW_MAXK = 128;
 
 __global__ void __launch_bounds__(256 * FEW_SEGS) small_solve_few(int k, int kmax, const double* __restrict__ Rm,
                                                                   const double* __restrict__ Rinv,
@@ -482,7 +484,7 @@ int apply_few(bfgsuq_ctx* h, const Tv* V, int c, To* out, bool diff, const Apply
         ProfScope ps(h, "apply_reduce");
         if (int rc = sum_partials(h->stream, (int64_t)2 * k * c, nchunks, part, Z)) return rc;
     }
-    if (k <= 256) {
+    if (k <= FEW_MAXK) {
         ProfScope ps(h, "apply_solve");
         hipLaunchKernelGGL(small_solve_few, dim3(c), dim3((unsigned)(FEW_SEGS * round_up(k, 64))), 0, h->stream, k,
                            h->kmax, h->Rm, h->Rinv, h->RinvT, h->YHY, Z, SolveOut{P, T, nullptr, k, 0, nullptr, nullptr, 0}, h->status);
@@ -858,7 +860,14 @@ int apply_block(bfgsuq_ctx* h, const void* V, int32_t ncols, void* out, bool dif
         if (h->storage != BFGS_F32) return BFGS_ERR_ARG;
         return apply_generic<float, float, double>(h, V, ncols, out, diff, fixed);
     }
-    if (mfma_apply_supported(h, ncols)) return mfma_apply(h, V, ncols, out, diff, fixed);
+    // bfloat16 pairs: B_k V of a few columns streams the pairs too (one column, k = 60: 17 us
+    // at n = 900 and 173 at 1,785,000, 24 and 301 as a tile of 32), but not from 128 pairs on
+    // small blocks or three columns, where a workgroup's chain over the pairs (at n = 9,000 and
+    // k = 200, 49 us, 43 as a tile) or the float64 products (at 1,785,000, 646 and 599) cost
+    // more.  The difference form stays on the matrix cores, as the rSVD's other blocks are.
+    const bool few = !diff && ncols <= STREAM_COLS && (h->k <= FEW_MAXK || (ncols <= 2 && h->n >= 65536));
+    if (mfma_apply_supported(h, ncols) && !few)
+        return mfma_apply(h, V, ncols, out, diff, fixed);
     switch (h->storage) {
         case BFGS_F64: return apply_generic<double, double, double>(h, V, ncols, out, diff, fixed);
         case BFGS_F32: return apply_generic<float, float, float>(h, V, ncols, out, diff, fixed);

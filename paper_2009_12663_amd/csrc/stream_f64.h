@@ -16,11 +16,25 @@ constexpr int stream_rows() {
     return sizeof(T) == 8 ? 2 : 4;
 }
 
-// Sum over the wave, in every lane.
-__device__ __forceinline__ double stream_wave_sum(double v) {
+// Sums of E values over the wave's lanes (E a power of two up to 64): lane l is left with
+// that of value l / (64 / E).  Each step halves the values a lane still carries, so 32
+// sums cost 32 exchanges (192 one at a time, 7 of pass 1's 13 us where it has nothing to read).
+template <int LEFT, int OFF, int E>
+__device__ __forceinline__ double stream_wave_sums(double (&a)[E]) {
+    if constexpr (OFF == 0) {
+        return a[0];
+    } else if constexpr (LEFT > 1) {
+        const bool up = threadIdx.x & OFF;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+        for (int i = 0; i < LEFT / 2; ++i) {
+            const double mine = up ? a[i + LEFT / 2] : a[i], other = up ? a[i] : a[i + LEFT / 2];
+            a[i] = mine + __shfl_xor(other, OFF, 64);
+        }
+        return stream_wave_sums<LEFT / 2, OFF / 2>(a);
+    } else {
+        a[0] += __shfl_xor(a[0], OFF, 64);
+        return stream_wave_sums<1, OFF / 2>(a);
+    }
 }
 
 // Pass 1: part[chunk][j * 2k + p] = sum over the chunk's rows of W(r, p) V(r, j).  A
@@ -39,7 +53,7 @@ __global__ void __launch_bounds__(64, CC > 2 ? 2 : 4) stream_pass1(int64_t n, in
     const int lane = threadIdx.x;
     const int64_t rb = (int64_t)chunk * rows_per_chunk, re = min(n, rb + rows_per_chunk);
     const Ts* W = y ? Y : S;
-    double acc[STREAM_PAIRS][CC] = {};
+    double acc[STREAM_PAIRS * CC] = {};
     for (int64_t r0 = rb; r0 < re; r0 += 64 * VR) {
         const int64_t r = r0 + VR * lane;
         const int live = (int)max((int64_t)0, min((int64_t)VR, re - r));
@@ -73,18 +87,15 @@ __global__ void __launch_bounds__(64, CC > 2 ? 2 : 4) stream_pass1(int64_t n, in
             for (int u = 0; u < STREAM_PAIRS; ++u) {
                 const double we = to_f64(w[u].v[e]);
 #pragma unroll
-                for (int j = 0; j < CC; ++j) acc[u][j] = fma(we, x[j], acc[u][j]);
+                for (int j = 0; j < CC; ++j) acc[u * CC + j] = fma(we, x[j], acc[u * CC + j]);
             }
         }
     }
     double* dst = part + (int64_t)chunk * 2 * k * c + (y ? k : 0);
-#pragma unroll
-    for (int u = 0; u < STREAM_PAIRS; ++u)
-#pragma unroll
-        for (int j = 0; j < CC; ++j) {
-            const double s = stream_wave_sum(acc[u][j]);
-            if (lane == 0 && p0 + u < k && j < c) dst[(int64_t)j * 2 * k + p0 + u] = s;
-        }
+    constexpr int LANES = 64 / (STREAM_PAIRS * CC);   // to a sum
+    const double s = stream_wave_sums<STREAM_PAIRS * CC, 32>(acc);
+    const int u = lane / LANES / CC, j = lane / LANES % CC;
+    if (lane % LANES == 0 && p0 + u < k && j < c) dst[(int64_t)j * 2 * k + p0 + u] = s;
 }
 
 // Pass 2: out = h0 o (V - Y P) + S T (without h0 o V for B_k - B_0); P, T column-major k x c.
