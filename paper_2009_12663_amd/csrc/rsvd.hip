@@ -173,15 +173,14 @@ __global__ void pack_nn(int nq, int nc, const double* __restrict__ M, double* __
 }
 
 // Omega = F T^-1, symmetrised.  T column-major c x c (T[j*c + i] = T(i, j)).
-// F = R, row-major c x c upper triangular.  Work: M = T^T (row-major M[i*c + j] =
-// T(j, i) = T[i*c + j], i.e. the same array), B = F^T; solve M X = B, Omega = X^T.
+// F = R, row-major c x c upper triangular.  M = T^T (row-major M[i*c + j] = T(j, i) =
+// T[i*c + j], i.e. the same array), B = F^T; M X = B, Omega = X^T.
 //
-// Blocked right-looking LU with partial pivoting in one workgroup: a panel of
-// LU_NB columns is factored in LDS; each column of the rest of [M | B] then
-// takes the panel's row swaps and the forward substitution with the panel's
-// unit-lower block (one thread per column); the trailing rows are updated from
-// the panel (L21) and the new U row block, both in LDS.  The backward
-// substitution with U is blocked the same way.
+// Three launches, all chains of small steps whose latency is the cost: lu_factor, a blocked
+// right-looking LU of M with partial pivoting in one workgroup; lu_solve, both substitutions,
+// a workgroup per 16 columns of B held in LDS; omega_symmetric.  (One workgroup for
+// all of it, with the rows swapped in memory one by one: 341 us at c = 120 and 911 at 220,
+// now 221 and 489.)
 // (value, index) of the largest value over a wave, ties to the lower index, in every
 // lane (all lanes active).  Quad and 16-lane row steps by DPP, then the rows by the
 // permlane swaps; each swap returns the lane's own pair and its partner's, and both
@@ -227,222 +226,352 @@ __device__ __forceinline__ void wave_argmax(double& best, int& bi) {
     argmax_swap<true>(best, bi);   // halves
 }
 
+// x combined over the wave, in every lane (all lanes active): quad and 16-lane rows by DPP
+// (quad permutations, row rotations by 4 and 8), then the four rows by the permlane swaps,
+// which return across their two results each lane's own value and that of the same lane
+// in the partner row.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+
+template <typename Op>
+__device__ __forceinline__ double swap16_f64(double x, Op op) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+    return op(__builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]),
+              __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+template <typename Op>
+__device__ __forceinline__ double swap32_f64(double x, Op op) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+    return op(__builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]),
+              __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+template <typename Op>
+__device__ __forceinline__ double wave_reduce_d(double x, Op op) {
+    x = op(x, dpp_f64<0xB1>(x));    // quad_perm [1, 0, 3, 2]
+    x = op(x, dpp_f64<0x4E>(x));    // quad_perm [2, 3, 0, 1]
+    x = op(x, dpp_f64<0x124>(x));   // row_ror:4
+    x = op(x, dpp_f64<0x128>(x));   // row_ror:8
+    return swap32_f64(swap16_f64(x, op), op);
+}
+
+__device__ __forceinline__ double wave_sum_d(double x) {
+    return wave_reduce_d(x, [](double a, double b) { return a + b; });
+}
+
 constexpr int LU_NB = 16;
 constexpr int LU_THREADS = 1024;
 constexpr int LU_PLD = LU_NB + 1;        // panel row stride (doubles)
-constexpr int LU_ULD = 2 * 256 + 1;      // row-block stride: M's right columns then B's columns
+constexpr int LU_ULD = 256 + 1;          // row-block stride: M's right columns
+constexpr int LU_TILES = 4;              // tiles of the trailing update that a wave has in flight
 
-size_t omega_smem_bytes() { return ((size_t)256 * LU_PLD + (size_t)LU_NB * LU_ULD + LU_NB + 8) * sizeof(double); }
+size_t lu_smem_bytes() { return ((size_t)256 * LU_PLD + (size_t)LU_NB * LU_ULD) * sizeof(double); }
 
-__global__ void __launch_bounds__(LU_THREADS) omega_solve(int c, double* __restrict__ M, const double* __restrict__ F,
-                                                          double* __restrict__ B, double* __restrict__ Omega,
-                                                          int* __restrict__ piv, int32_t* __restrict__ status) {
+// M = P^T L U in place: panel by panel, the rows of a panel's L as they lie when it is done
+// (later panels swap only what is right of them).  piv[i]: the row that step i swapped with
+// row i; from[16 panels][256]: the row before the panel's swaps of each row after them,
+// both counted from the panel's first.
+//
+// A panel's rows are held a thread each and stay there: a swap changes only which row a
+// thread stands for (pos).  The step's column is always a[0]; the step shifts the row by
+// one and puts the finished entry (the multiplier, or U's where the row was a pivot) at its end,
+// so that one copy of the code does for all steps.  One barrier a step: every wave offers its
+// largest entry and that row.
+__global__ void __launch_bounds__(LU_THREADS) lu_factor(int c, double* __restrict__ M, int* __restrict__ piv,
+                                                        uint8_t* __restrict__ from, int32_t* __restrict__ status) {
     extern __shared__ double lu_sh[];
-    double* P = lu_sh;                              // panel rows kb..c-1: P[(r - kb) * LU_PLD + j]
-    double* Ub = P + 256 * LU_PLD;                  // row block: Ub[i * LU_ULD + ec]
-    double* red = Ub + LU_NB * LU_ULD;              // pivot value / index exchange
-    __shared__ int pivl[LU_NB];
-    __shared__ int bad;
-    const int tid = threadIdx.x;
-    if (tid == 0) bad = 0;
-    // B(i, j) = F(j, i), row-major B[i*c + j]
-    for (int e = tid; e < c * c; e += LU_THREADS) {
-        const int i = e / c, j = e % c;
-        B[e] = F[(int64_t)j * c + i];
-    }
-    __syncthreads();
+    double* P = lu_sh;                              // panel rows kb..c-1 in their places: P[(r - kb) * LU_PLD + j]
+    double* Ub = P + 256 * LU_PLD;                  // row block: Ub[i * LU_ULD + column right of the panel]
+    __shared__ double cand[2][4][LU_NB], cand_best[2][4];
+    __shared__ int cand_row[2][4];
+    __shared__ int src[256], pivl[LU_NB];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    bool bad = false;
     for (int kb = 0; kb < c; kb += LU_NB) {
         const int nb = min(LU_NB, c - kb);
         const int rows = c - kb;
-        for (int e = tid; e < rows * nb; e += LU_THREADS) {
-            const int r = e / nb, j = e % nb;
-            P[r * LU_PLD + j] = M[(int64_t)(kb + r) * c + kb + j];
-        }
-        __syncthreads();
-        // --- panel factorisation in LDS ---
-        for (int j = 0; j < nb; ++j) {
-            if (tid < 64) {
-                double best = -1.0;
-                int bi = j;
-                for (int r = j + tid; r < rows; r += 64) {
-                    const double v = fabs(P[r * LU_PLD + j]);
-                    if (v > best) { best = v; bi = r; }
-                }
-                wave_argmax(best, bi);
-                if (tid == 0) {
-                    pivl[j] = bi;
-                    piv[kb + j] = kb + bi;
-                    if (!(best > 0.0) || !isfinite(best)) bad = 1;
-                }
-            }
-            __syncthreads();
-            const int p = pivl[j];
-            if (p != j && tid < nb) {
-                const double t = P[j * LU_PLD + tid];
-                P[j * LU_PLD + tid] = P[p * LU_PLD + tid];
-                P[p * LU_PLD + tid] = t;
-            }
-            __syncthreads();
-            const double d = P[j * LU_PLD + j];
-            for (int r = j + 1 + tid; r < rows; r += LU_THREADS) {
-                const double l = d != 0.0 ? P[r * LU_PLD + j] / d : 0.0;
-                P[r * LU_PLD + j] = l;
-                for (int jj = j + 1; jj < nb; ++jj) P[r * LU_PLD + jj] = fma(-l, P[j * LU_PLD + jj], P[r * LU_PLD + jj]);
-            }
-            __syncthreads();
-        }
-        for (int e = tid; e < rows * nb; e += LU_THREADS) {
-            const int r = e / nb, j = e % nb;
-            M[(int64_t)(kb + r) * c + kb + j] = P[r * LU_PLD + j];
-        }
-        // --- swaps and forward substitution, one thread per column outside the panel ---
-        // extended column ec: [0, kb) M left columns (swaps only); [kb + nb, c) M right
-        // columns; then c columns of B
-        const int right = c - kb - nb;
-        for (int ec = tid; ec < kb + right + c; ec += LU_THREADS) {
-            double* col;
-            int stride = c;
-            int ub = -1;
-            if (ec < kb) {
-                col = M + ec;
-            } else if (ec < kb + right) {
-                col = M + (kb + nb + (ec - kb));
-                ub = ec - kb;
-            } else {
-                col = B + (ec - kb - right);
-                ub = right + (ec - kb - right);
-            }
-            for (int j = 0; j < nb; ++j) {
-                const int p = pivl[j];
-                if (p != j) {
-                    const double t = col[(int64_t)(kb + j) * stride];
-                    col[(int64_t)(kb + j) * stride] = col[(int64_t)(kb + p) * stride];
-                    col[(int64_t)(kb + p) * stride] = t;
-                }
-            }
-            if (ub >= 0) {
-                double x[LU_NB];
+        double a[LU_NB];
+        int pos = tid;
+        bool active = tid < rows;
 #pragma unroll
-                for (int i = 0; i < LU_NB; ++i) {
-                    if (i < nb) {
-                        double v = col[(int64_t)(kb + i) * stride];
+        for (int j = 0; j < LU_NB; ++j) a[j] = active && j < nb ? M[(int64_t)(kb + tid) * c + kb + j] : 0.0;
+        for (int j = 0; j < LU_NB; ++j) {
+            double u[LU_NB] = {};
+            bool pivot = false;
+            if (j < nb) {
+                const int buf = j & 1;
+                if (wave < 4) {
+                    // the largest value (NaN and rows that are done: -1), then the rows that
+                    // have it: the lowest of several
+                    const double v = active && fabs(a[0]) >= 0.0 ? fabs(a[0]) : -1.0;
+                    const double best = wave_reduce_d(v, [](double x, double y) { return fmax(x, y); });
+                    bool mine = active && v == best;
+                    unsigned long long tied = __ballot(mine);
+                    if (__popcll(tied) > 1) {
+                        int bi = 256;
+                        for (; tied; tied &= tied - 1) bi = min(bi, __shfl(pos, __ffsll(tied) - 1, 64));
+                        mine = mine && pos == bi;
+                    }
+                    if (mine) {
+                        cand_row[buf][wave] = pos;
 #pragma unroll
-                        for (int l = 0; l < LU_NB; ++l)
-                            if (l < i) v = fma(-P[i * LU_PLD + l], x[l], v);
-                        x[i] = v;
-                        col[(int64_t)(kb + i) * stride] = v;
-                        Ub[i * LU_ULD + ub] = v;
+                        for (int q = 0; q < LU_NB; ++q) cand[buf][wave][q] = a[q];
+                    }
+                    if (lane == 0) {
+                        cand_best[buf][wave] = best;
+                        if (best < 0.0) cand_row[buf][wave] = j;
+                    }
+                }
+                __syncthreads();
+                if (wave < 4) {
+                    double b4[4];
+                    int r4[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        b4[q] = cand_best[buf][q];
+                        r4[q] = cand_row[buf][q];
+                    }
+                    double best = b4[0];
+                    int p = r4[0], w = 0;
+#pragma unroll
+                    for (int q = 1; q < 4; ++q) {
+                        const bool take = (b4[q] > best) | ((b4[q] == best) & (r4[q] < p));
+                        best = take ? b4[q] : best;
+                        p = take ? r4[q] : p;
+                        w = take ? q : w;
+                    }
+#pragma unroll
+                    for (int q = 0; q < LU_NB; ++q) u[q] = cand[buf][w][q];
+#pragma unroll
+                    for (int q = 0; q < LU_NB; ++q) u[q] = q + j < LU_NB ? u[q] : 0.0;
+                    if (tid == 0) pivl[j] = p;   // (to memory later: a barrier waits for stores)
+                    bad |= !(best > 0.0) || !isfinite(best);
+                    pivot = active && pos == p;
+                    if (pivot) {
+                        pos = j;
+                        active = false;
+                    } else if (pos == j) {
+                        pos = p;
                     }
                 }
             }
+            if (wave < 4) {
+                const double d = u[0];
+                const double r = a[0] / d;
+                const bool update = active && j < nb;
+                const double l = update ? (d != 0.0 ? r : 0.0) : a[0];
+#pragma unroll
+                for (int q = 1; q < LU_NB; ++q) a[q - 1] = update ? fma(-l, u[q], a[q]) : a[q];
+                a[LU_NB - 1] = l;
+            }
+        }
+        if (tid < rows) {
+#pragma unroll
+            for (int j = 0; j < LU_NB; ++j)
+                if (j < nb) {
+                    P[pos * LU_PLD + j] = a[j];
+                    M[(int64_t)(kb + pos) * c + kb + j] = a[j];
+                }
+            src[pos] = tid;
+            from[kb * 16 + pos] = (uint8_t)tid;
         }
         __syncthreads();
-        // --- trailing update of rows kb + nb .. c-1 over M's right columns and B:
-        // C -= L21 U12, a rank-nb product on the float64 matrix cores, one wave per
-        // 16 x 16 tile of C (A = L21 rows from the panel, B = U12 from the row block;
-        // loads from clamped indices, stores only inside C) ---
-        {
-            const int trows = rows - nb;
-            const int wcols = right + c;
-            const int ntr = (trows + 15) / 16, ntc = (wcols + 15) / 16;
-            const int lane = tid & 63, lm = lane & 15, lk = lane >> 4;
-            for (int tile = tid >> 6; tile < ntr * ntc; tile += LU_THREADS / 64) {
-                const int ti = tile / ntc, tj = tile % ntc;
-                const int ec = tj * 16 + lm, ecc = min(ec, wcols - 1);
-                double* colp = ecc < right ? M + (int64_t)(kb + nb) * c + kb + nb + ecc
-                                           : B + (int64_t)(kb + nb) * c + (ecc - right);
-                v4d acc;
+        if (tid < nb) piv[kb + tid] = kb + pivl[tid];
+        // swaps and forward substitution of the columns right of the panel, one thread each
+        // (there are some only where nb = LU_NB)
+        const int right = rows - nb;
+        if (tid < right) {
+            double* col = M + (int64_t)kb * c + kb + nb + tid;
+            double top[LU_NB], low[LU_NB];
+            int at[LU_NB];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q] = colp[(int64_t)min(ti * 16 + lk + 4 * q, trows - 1) * c];
-                const int ar = min(ti * 16 + lm, trows - 1);
+            for (int i = 0; i < LU_NB; ++i) at[i] = pivl[i];
+#pragma unroll
+            for (int i = 0; i < LU_NB; ++i) {
+                top[i] = col[(int64_t)src[i] * c];
+                low[i] = col[(int64_t)src[at[i]] * c];
+            }
+#pragma unroll
+            for (int i = 0; i < LU_NB; ++i)
+                if (at[i] >= LU_NB) col[(int64_t)at[i] * c] = low[i];
+#pragma unroll
+            for (int i = 0; i < LU_NB; ++i) {
+#pragma unroll
+                for (int l = 0; l < i; ++l) top[i] = fma(-P[i * LU_PLD + l], top[l], top[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < LU_NB; ++i) {
+                col[(int64_t)i * c] = top[i];
+                Ub[i * LU_ULD + tid] = top[i];
+            }
+        }
+        __syncthreads();
+        // trailing update of M's rows and columns past the panel: C -= L21 U12, a rank-16
+        // product on the float64 matrix cores, one wave per 16 x 16 tile of C
+        // (A = L21 rows from the panel, B = U12 from the row block; loads from clamped
+        // indices, stores only inside C)
+        const int nt = (right + 15) / 16, lm = lane & 15, lk = lane >> 4;
+        double* C = M + (int64_t)(kb + nb) * c + kb + nb;
+        for (int t0 = wave; t0 < nt * nt; t0 += LU_TILES * (LU_THREADS / 64)) {
+            v4d acc[LU_TILES];
+            int ti[LU_TILES], tj[LU_TILES];
+#pragma unroll
+            for (int u = 0; u < LU_TILES; ++u) {
+                const int tile = min(t0 + u * (LU_THREADS / 64), nt * nt - 1);
+                ti[u] = tile / nt * 16;
+                tj[u] = tile % nt * 16;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    acc[u][q] = C[(int64_t)min(ti[u] + lk + 4 * q, right - 1) * c + min(tj[u] + lm, right - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < LU_TILES; ++u) {
+                if (t0 + u * (LU_THREADS / 64) >= nt * nt) break;
+                const int ar = min(ti[u] + lm, right - 1), ec = min(tj[u] + lm, right - 1);
 #pragma unroll
                 for (int ks = 0; ks < LU_NB / 4; ++ks) {
                     const int k = 4 * ks + lk;
-                    const double a = k < nb ? -P[(nb + ar) * LU_PLD + k] : 0.0;
-                    const double b = k < nb ? Ub[k * LU_ULD + ecc] : 0.0;
-                    acc = mfma64(a, b, acc);
+                    acc[u] = mfma64(-P[(LU_NB + ar) * LU_PLD + k], Ub[k * LU_ULD + ec], acc[u]);
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int rr = ti * 16 + lk + 4 * q;
-                    if (rr < trows && ec < wcols) colp[(int64_t)rr * c] = acc[q];
+                    const int r = ti[u] + lk + 4 * q;
+                    if (r < right && tj[u] + lm < right) C[(int64_t)r * c + tj[u] + lm] = acc[u][q];
                 }
             }
         }
         __syncthreads();
     }
-    // --- backward substitution U X = B, blocks from the bottom ---
-    const int nblk = (c + LU_NB - 1) / LU_NB;
-    for (int bidx = nblk - 1; bidx >= 0; --bidx) {
-        const int kb = bidx * LU_NB;
+    if (tid == 0 && bad) set_status(status, BFGS_ERR_NUMERIC);
+}
+
+// Columns 16 blockIdx.x .. + 15 of X = M^-1 B, B(i, j) = F(j, i), by the factors, pivots and
+// row orders of lu_factor; X column-major.  The columns stay in LDS; a panel's factors
+// are fetched into registers before the steps that need them.
+__global__ void __launch_bounds__(256) lu_solve(int c, const double* __restrict__ M, const int* __restrict__ piv,
+                                                const uint8_t* __restrict__ from, const double* __restrict__ F,
+                                                double* __restrict__ X) {
+    __shared__ double Bs[256][LU_PLD], Ls[LU_NB][LU_PLD];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lm = lane & 15, lk = lane >> 4;
+    const int j0 = blockIdx.x * 16, i16 = tid >> 4, j16 = tid & 15;
+    for (int e = tid; e < 16 * c; e += 256) {
+        const int j = e / c, i = e % c;
+        Bs[i][j] = j0 + j < c ? F[(int64_t)(j0 + j) * c + i] : 0.0;
+    }
+    if (c + i16 < (c + 15) / 16 * 16) Bs[c + i16][j16] = 0.0;   // the last panel's missing rows
+    __syncthreads();
+    // rows r0 .. r0 + rows - 1 of B lose A times the 16 rows at kb: A(r, k) = M(r0 + r, kb + k)
+    double lf[4][4];
+    auto fetch = [&](int r0, int rows, int kb, int nb) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const int r = (wave + 4 * u) * 16 + lm, k = 4 * ks + lk;
+                lf[u][ks] = r < rows && k < nb ? -M[(int64_t)(r0 + r) * c + kb + k] : 0.0;
+            }
+    };
+    auto update = [&](int r0, int rows, int kb, int nb) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int t = (wave + 4 * u) * 16;
+            if (t >= rows) break;
+            v4d acc;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = Bs[r0 + min(t + lk + 4 * q, rows - 1)][lm];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const int k = 4 * ks + lk;
+                acc = mfma64(lf[u][ks], k < nb ? Bs[kb + k][lm] : 0.0, acc);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (t + lk + 4 * q < rows) Bs[r0 + t + lk + 4 * q][lm] = acc[q];
+        }
+    };
+    auto diagonal = [&](int kb) {   // the panel's own block of the factors
         const int nb = min(LU_NB, c - kb);
-        // U11 (nb x nb) into Ub's first rows; U[0:kb, kb:kb+nb] into P
-        for (int e = tid; e < nb * nb; e += LU_THREADS) {
-            const int i = e / nb, j = e % nb;
-            Ub[i * LU_ULD + j] = M[(int64_t)(kb + i) * c + kb + j];
-        }
-        for (int e = tid; e < kb * nb; e += LU_THREADS) {
-            const int r = e / nb, j = e % nb;
-            P[r * LU_PLD + j] = M[(int64_t)r * c + kb + j];
-        }
+        return i16 < nb && j16 < nb ? M[(int64_t)(kb + i16) * c + kb + j16] : 0.0;
+    };
+    // forward: each panel's swaps, its unit-lower block, the rows below
+    double dg = diagonal(0);
+    for (int kb = 0; kb < c; kb += LU_NB) {
+        const int nb = min(LU_NB, c - kb), below = c - kb - nb;
+        fetch(kb + nb, below, kb, nb);
+        const int q = i16 < nb ? piv[kb + i16] - kb : 0;
+        const double top = Bs[kb + (i16 < nb ? from[kb * 16 + i16] : 0)][j16], low = Bs[kb + from[kb * 16 + q]][j16];
+        Ls[i16][j16] = dg;
         __syncthreads();
-        double* X = Ub + LU_NB;   // X[i * LU_ULD + col] for col < c (offset past U11's columns)
-        for (int col = tid; col < c; col += LU_THREADS) {
+        if (i16 < nb) Bs[kb + i16][j16] = top;
+        if (q >= nb) Bs[kb + q][j16] = low;
+        dg = diagonal(kb + LU_NB < c ? kb + LU_NB : kb);
+        __syncthreads();
+        if (tid < 16) {
             double x[LU_NB];
 #pragma unroll
-            for (int ii = LU_NB - 1; ii >= 0; --ii) {
-                if (ii < nb) {
-                    double v = B[(int64_t)(kb + ii) * c + col];
+            for (int i = 0; i < LU_NB; ++i) x[i] = Bs[kb + i][tid];
 #pragma unroll
-                    for (int l = 0; l < LU_NB; ++l)
-                        if (l > ii && l < nb) v = fma(-Ub[ii * LU_ULD + l], x[l], v);
-                    const double dii = Ub[ii * LU_ULD + ii];
-                    v = dii != 0.0 ? v / dii : 0.0;
-                    x[ii] = v;
-                    B[(int64_t)(kb + ii) * c + col] = v;
-                }
+            for (int i = 0; i < LU_NB; ++i) {
+#pragma unroll
+                for (int l = 0; l < i; ++l) x[i] = fma(-Ls[i][l], x[l], x[i]);
             }
 #pragma unroll
-            for (int ii = 0; ii < LU_NB; ++ii)
-                if (ii < nb) X[ii * LU_ULD + col] = x[ii];
+            for (int i = 0; i < LU_NB; ++i) Bs[kb + i][tid] = x[i];
         }
         __syncthreads();
-        // B[0:kb, :] -= U[0:kb, kb:kb+nb] X on the matrix cores, as above
-        {
-            const int ntr = (kb + 15) / 16, ntc = (c + 15) / 16;
-            const int lane = tid & 63, lm = lane & 15, lk = lane >> 4;
-            for (int tile = tid >> 6; tile < ntr * ntc; tile += LU_THREADS / 64) {
-                const int ti = tile / ntc, tj = tile % ntc;
-                const int col = tj * 16 + lm, colc = min(col, c - 1);
-                v4d acc;
+        update(kb + nb, below, kb, nb);
+        __syncthreads();
+    }
+    // backward: each panel's upper block from the last, the rows above
+    for (int kb = (c - 1) / LU_NB * LU_NB; kb >= 0; kb -= LU_NB) {
+        const int nb = min(LU_NB, c - kb);
+        fetch(0, kb, kb, nb);
+        Ls[i16][j16] = dg;
+        dg = diagonal(max(kb - LU_NB, 0));
+        __syncthreads();
+        if (tid < 16) {
+            double x[LU_NB];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q] = B[(int64_t)min(ti * 16 + lk + 4 * q, kb - 1) * c + colc];
-                const int ar = min(ti * 16 + lm, kb - 1);
+            for (int i = 0; i < LU_NB; ++i) x[i] = Bs[kb + i][tid];
 #pragma unroll
-                for (int ks = 0; ks < LU_NB / 4; ++ks) {
-                    const int k = 4 * ks + lk;
-                    const double a = k < nb ? -P[ar * LU_PLD + k] : 0.0;
-                    const double b = k < nb ? X[k * LU_ULD + colc] : 0.0;
-                    acc = mfma64(a, b, acc);
-                }
+            for (int i = LU_NB - 1; i >= 0; --i) {   // (missing rows: 0, their factors too)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int r = ti * 16 + lk + 4 * q;
-                    if (r < kb && col < c) B[(int64_t)r * c + col] = acc[q];
-                }
+                for (int l = i + 1; l < LU_NB; ++l) x[i] = fma(-Ls[i][l], x[l], x[i]);
+                const double d = Ls[i][i], v = x[i] / d;
+                x[i] = d != 0.0 ? v : 0.0;
             }
+#pragma unroll
+            for (int i = 0; i < LU_NB; ++i) Bs[kb + i][tid] = x[i];
         }
         __syncthreads();
+        update(0, kb, kb, nb);
+        __syncthreads();
     }
-    // X = B (row-major); Omega = X^T; symmetrise.  Omega(i, j) = (X(j, i) + X(i, j)) / 2
-    for (int e = tid; e < c * c; e += LU_THREADS) {
-        const int i = e / c, j = e % c;
-        const double v = 0.5 * (B[(int64_t)j * c + i] + B[(int64_t)i * c + j]);
-        Omega[e] = v;
-        if (!isfinite(v)) bad = 1;
+    for (int e = tid; e < 16 * c; e += 256) {
+        const int j = e / c, i = e % c;
+        if (j0 + j < c) X[(int64_t)(j0 + j) * c + i] = Bs[i][j];
     }
-    __syncthreads();
-    if (tid == 0 && bad) set_status(status, BFGS_ERR_NUMERIC);
+}
+
+// Omega = X^T, symmetrised: Omega(i, j) = (X(j, i) + X(i, j)) / 2
+__global__ void __launch_bounds__(256) omega_symmetric(int c, const double* __restrict__ X, double* __restrict__ Omega,
+                                                       int32_t* __restrict__ status) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= c * c) return;
+    const int i = e / c, j = e % c;
+    const double v = 0.5 * (X[(int64_t)i * c + j] + X[(int64_t)j * c + i]);
+    Omega[e] = v;
+    if (!isfinite(v)) set_status(status, BFGS_ERR_NUMERIC);
 }
 
 // Symmetric eigendecomposition of A (row-major c x c, overwritten):
@@ -454,42 +583,6 @@ __global__ void __launch_bounds__(LU_THREADS) omega_solve(int c, double* __restr
 //                      eigenvectors of A = Z times those of the tridiagonal
 //                      (tridiag_dc.hip)
 // Z: column-major c x c eigenvectors (Z[i*c + r] = component r of vector i).
-// x summed over the wave, in every lane (all lanes active): quad and 16-lane row sums
-// by DPP (quad permutations, row rotations by 4 and 8), then the four rows by the
-// permlane swaps, which return across their two results each lane's own value and
-// that of the same lane in the partner row.
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double x) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, false);
-    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-
-__device__ __forceinline__ double swap_sum16(double x) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
-    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
-           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-}
-
-__device__ __forceinline__ double swap_sum32(double x) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
-    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
-           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-}
-
-__device__ __forceinline__ double wave_sum_d(double x) {
-    x += dpp_f64<0xB1>(x);    // quad_perm [1, 0, 3, 2]
-    x += dpp_f64<0x4E>(x);    // quad_perm [2, 3, 0, 1]
-    x += dpp_f64<0x124>(x);   // row_ror:4
-    x += dpp_f64<0x128>(x);   // row_ror:8
-    return swap_sum32(swap_sum16(x));
-}
-
 constexpr int TRI_THREADS = 1024;
 constexpr int TRI_LDS_MAX = 191;   // trailing matrices up to this size run from LDS (packed lower triangle)
 static_assert(TRI_LDS_MAX <= 193, "LDS-phase rows are covered by three 64-lane passes");
@@ -1047,7 +1140,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
     const int64_t qb_rows = qblk ? tsqr_chain_rows(h) : 0;
     const int64_t q_rows = qblk ? ceil_div(n, qb_rows) * qb_rows : n;
     if ((rc = ensure_ws(h->Q, (size_t)q_rows * c * sizeof(TQ))) != BFGS_OK) return rc;
-    // small: part(nchunks*c*c) + T, M, B, Omega, Z (5 c*c) + d, e, taus, rot, lam (5 c) + piv
+    // small: part(nchunks*c*c) + T, M, B, Omega, Z (5 c*c) + d, e, taus, rot, lam (5 c) + piv, from
     // Q^T X row chunks: about one per CU, each chunk a multiple of the staging depth
     int nchunks = (int)std::min<int64_t>(256, std::max<int64_t>(1, (n + 63) / 64));
     const int64_t rows_per_chunk = round_up((n + nchunks - 1) / nchunks, MT_K);
@@ -1057,7 +1150,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
     const int part_chunks = std::max(nchunks, qx_chunks);
     const size_t cc = (size_t)c * c;
     if ((rc = ensure_ws(h->small, ((size_t)part_chunks * cc + 14 * cc + nn_pack_doubles(c, rank) + 6 * (size_t)c) * 8 +
-                                      (size_t)c * 4)) !=
+                                      (size_t)c * 4 + 16 * 256)) !=
         BFGS_OK)
         return rc;
     // tridiagonal eigensolver workspace, then Z = Q_H Y (c x c)
@@ -1083,6 +1176,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
     double* Rb = Fm + cc;   // 6 c x c: the column-blocked QR's pieces
     double* Mpk = Rb + 6 * cc;   // the basis' small operand, packed
     int* piv = (int*)(Mpk + nn_pack_doubles(c, rank));
+    uint8_t* from = (uint8_t*)(piv + c);   // 16 panels of 256 rows
     TS* X = (TS*)h->X.ptr;
     TE* E = (TE*)h->E.ptr;
     TQ* Q = (TQ*)h->Q.ptr;
@@ -1162,16 +1256,18 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
         ProfScope ps(h, "omega_lu");
         static bool attr = false;
         if (!attr) {
-            if (hipFuncSetAttribute((const void*)omega_solve, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)omega_smem_bytes()) != hipSuccess)
+            if (hipFuncSetAttribute((const void*)lu_factor, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)lu_smem_bytes()) != hipSuccess)
                 return BFGS_ERR_HIP;
             attr = true;
         }
-        hipLaunchKernelGGL(omega_solve, dim3(1), dim3(LU_THREADS), omega_smem_bytes(), h->stream, c, Tm, R, Bm, Om,
-                           piv, h->status);
+        hipLaunchKernelGGL(lu_factor, dim3(1), dim3(LU_THREADS), lu_smem_bytes(), h->stream, c, Tm, piv, from, h->status);
+        hipLaunchKernelGGL(lu_solve, dim3(ceil_div(c, 16)), dim3(256), 0, h->stream, c, Tm, piv, from, R, Bm);
+        hipLaunchKernelGGL(omega_symmetric, dim3(ceil_div((int64_t)cc, 256)), dim3(256), 0, h->stream, c, Bm, Om,
+                           h->status);
     }
     prof_begin(h, "sym_eig");
-    // Bm (the LU right-hand sides) is free after omega_solve: it holds the reflectors
+    // Bm (X) is free after omega_symmetric: it holds the reflectors
     {
         static bool attr = false;
         if (!attr) {
