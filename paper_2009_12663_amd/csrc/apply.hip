@@ -436,7 +436,8 @@ int small_solve_launch(bfgsuq_ctx* h, int c, const double* Z, SolveOut out) {
     ProfScope ps(h, "apply_solve");
     const int k = h->k;
     if (k <= 256)
-        hipLaunchKernelGGL(small_solve_blocks, dim3(c), dim3((unsigned)round_up(k, 64)), 0, h->stream, k, h->kmax, h->Rm, h->Rinv, h->RinvT, h->YHY, Z, out, h->status);
+        hipLaunchKernelGGL(small_solve_blocks, dim3(c), dim3((unsigned)round_up(k, 64)), 0, h->stream, k, h->kmax, h->Rm,
+                           h->Rinv, h->RinvT, h->YHY, Z, out, h->status);
     else
         hipLaunchKernelGGL(small_solve, dim3(c), dim3(64), 3 * k * sizeof(double), h->stream, k, h->kmax, c, h->Rm,
                            h->YHY, Z, out, h->status);
@@ -472,6 +473,7 @@ int apply_few(bfgsuq_ctx* h, const Tv* V, int c, To* out, bool diff, const Apply
         P = (double*)h->PT.ptr;
     }
     double* T = P + (size_t)k * c;
+    const SolveOut plain{P, T, nullptr, k, 0, nullptr, nullptr, 0};
     {
         ProfScope ps(h, diff ? "hdiff_gemm1" : "apply_gemm1");
         with_few_columns(c, [&](auto cc) {
@@ -487,8 +489,8 @@ int apply_few(bfgsuq_ctx* h, const Tv* V, int c, To* out, bool diff, const Apply
     if (k <= FEW_MAXK) {
         ProfScope ps(h, "apply_solve");
         hipLaunchKernelGGL(small_solve_few, dim3(c), dim3((unsigned)(FEW_SEGS * round_up(k, 64))), 0, h->stream, k,
-                           h->kmax, h->Rm, h->Rinv, h->RinvT, h->YHY, Z, SolveOut{P, T, nullptr, k, 0, nullptr, nullptr, 0}, h->status);
-    } else if (int rc = small_solve_launch(h, c, Z, SolveOut{P, T, nullptr, k, 0, nullptr, nullptr, 0})) {
+                           h->kmax, h->Rm, h->Rinv, h->RinvT, h->YHY, Z, plain, h->status);
+    } else if (int rc = small_solve_launch(h, c, Z, plain)) {
         return rc;
     }
     ProfScope ps(h, diff ? "hdiff_gemm2" : "apply_gemm2");
@@ -552,7 +554,8 @@ int apply_generic(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, c
     prof_begin(h, "apply_reduce");
     if (int rc2 = sum_partials(h->stream, (int64_t)twok * c, plan.nchunks, part, Z)) return rc2;
     prof_end(h);
-    if (int rc2 = small_solve_launch(h, c, Z, SolveOut{nullptr, nullptr, M, k, ceil_div(c, 16), nullptr, nullptr, 0})) return rc2;
+    const SolveOut packed{nullptr, nullptr, M, k, ceil_div(c, 16), nullptr, nullptr, 0};
+    if (int rc2 = small_solve_launch(h, c, Z, packed)) return rc2;
     prof_begin(h, diff ? "hdiff_gemm2" : "apply_gemm2");
     launch_gemm2<Ts, Th, To, Tv>(h->stream, n, h->ld, k, c, (const Ts*)h->S, (const Ts*)h->Y, h0, V, n, M, out, diff);
     prof_end(h);
@@ -599,7 +602,8 @@ int apply_streamed(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff) 
     }
     const int64_t count = (int64_t)twok * c;
     if ((rc = sum_partials(h->stream, count, used, part, Z)) != BFGS_OK) return rc;
-    if ((rc = small_solve_launch(h, c, Z, SolveOut{nullptr, nullptr, M, k, ceil_div(c, 16), nullptr, nullptr, 0})) != BFGS_OK) return rc;
+    const SolveOut packed{nullptr, nullptr, M, k, ceil_div(c, 16), nullptr, nullptr, 0};
+    if ((rc = small_solve_launch(h, c, Z, packed)) != BFGS_OK) return rc;
     ProfScope ps(h, diff ? "hdiff_stream_pass2" : "apply_stream_pass2");
     rc = stream_slices(h, k, [&](int, int64_t r0, int64_t rows, const void* Sst, const void* Yst) {
         launch_gemm2<Ts, Th, To, Tv>(h->stream, rows, h->slice_ld, k, c, (const Ts*)Sst, (const Ts*)Yst, h0 + r0, V + r0,
@@ -812,7 +816,8 @@ int batch_apply_persistent(bfgsuq_ctx* const* hs, int nprob, const void* const* 
     if (nprob < 1) return BFGS_ERR_ARG;
     const bfgs_dtype s0 = hs[0]->storage;
     for (int i = 0; i < nprob; ++i)
-        if (ncols[i] <= STREAM_COLS || hs[i]->storage != s0 || hs[i]->streamed || hs[i]->k < 1 || hs[i]->k > 256) return BFGS_ERR_ARG;
+        if (ncols[i] <= STREAM_COLS || hs[i]->storage != s0 || hs[i]->streamed || hs[i]->k < 1 || hs[i]->k > 256)
+            return BFGS_ERR_ARG;
     if (s0 == BFGS_F64) return batch_persistent_impl<double, double>(hs, nprob, V, ncols, out, st, slot, upload, wg_per_cu);
     if (s0 == BFGS_F32) return batch_persistent_impl<float, float>(hs, nprob, V, ncols, out, st, slot, upload, wg_per_cu);
     return BFGS_ERR_ARG;

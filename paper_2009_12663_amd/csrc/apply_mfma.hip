@@ -481,7 +481,8 @@ __global__ void __launch_bounds__(G2Shape<MT2>::THREADS, 4) gemm2_mfma(int64_t n
                 const int q = wave * 4 + j, qs = q / 32, col = (qs * MH + p) * 32 + q % 32;
                 v[j] = make_uint2(0, 0);
                 const bool has = p < min(MH, MT2 - qs * MH) && col < c;
-                if (has && vec && r4 + 4 <= n) v[j] = *(const uint2*)(V + (int64_t)col * n + (int64_t)blk * G2_ROWS + (uint32_t)(lane * 4));
+                if (has && vec && r4 + 4 <= n)
+                    v[j] = *(const uint2*)(V + (int64_t)col * n + (int64_t)blk * G2_ROWS + (uint32_t)(lane * 4));
             }
         };
         if (!DIFF) {

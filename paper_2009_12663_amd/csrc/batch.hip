@@ -1,9 +1,9 @@
 // Batched form: many independent inversions (uneven n and k) driven together.
 //
 // A batch owns one handle per problem.  With float32 or float64 storage (and
-// 1 <= k <= 256 and more than a few columns everywhere) the apply of all problems is five launches in all:
-// persistent pass kernels take (problem, tile) items from a work queue, longest
-// problems first (batch_apply_persistent).  Otherwise, and for the rSVD, problems
+// 1 <= k <= 256 and more than a few columns everywhere) the apply of all problems is
+// five launches in all: persistent pass kernels take (problem, tile) items from a work
+// queue, longest problems first (batch_apply_persistent).  Otherwise, and for the rSVD, problems
 // are spread over a small set of side streams forked from the caller's stream with
 // events and joined back, so their kernels overlap on the device.  Apply + rSVD of
 // every problem can be captured once into a hipGraph and replayed with a single

@@ -362,7 +362,8 @@ static int push_small(bfgsuq_ctx* h, int j) {
     hipLaunchKernelGGL(gram_finish_kernel, dim3(ceil_div(j + 1, SUM_ENTRIES / 2)), dim3(SUM_THREADS), 0, h->stream, j, h->kmax,
                        h->gram_blocks, h->gram_part, h->Rm, h->YHY, h->scalars, h->gamma_mode ? 1 : 0, h->host_sc);
     BFGS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(rinv_update_kernel, dim3(j / SUM_ENTRIES + 1), dim3(SUM_THREADS), 0, h->stream, j, h->kmax, h->Rm, h->Rinv, h->RinvT);
+    hipLaunchKernelGGL(rinv_update_kernel, dim3(j / SUM_ENTRIES + 1), dim3(SUM_THREADS), 0, h->stream, j, h->kmax, h->Rm,
+                       h->Rinv, h->RinvT);
     BFGS_HIP(hipGetLastError());
     return BFGS_OK;
 }
