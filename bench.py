@@ -636,7 +636,7 @@ KERNEL_GROUPS = [
     ("leaf_backward", "tsqr_leaf_bwd"), ("tri_mul", "tsqr_tree"),
     ("qtx_mfma", "proj_QtX"), ("qtx_bf16", "proj_QtX"), ("lu_factor", "omega_lu"), ("lu_solve", "omega_lu"),
     ("omega_symmetric", "omega_lu"),
-    ("sym_tridiag", "sym_eig"), ("householder_accum", "sym_eig"), ("dc_leaves", "sym_eig"), ("dc_first", "sym_eig"),
+    ("sym_tridiag", "sym_eig"), ("householder_accum", "sym_eig"), ("dc_first", "sym_eig"),
     ("dc_merge_gemm", "sym_eig"), ("dc_merge", "sym_eig"), ("order_sign", "sym_eig"), ("basis_mfma", "basis_diag"),
     ("basis_bf16", "basis_diag"), ("split_us", "basis_diag"),
     ("posterior_diag_kernel", "basis_diag"), ("store_pair_kernel", "push_pair"), ("gram_partial_kernel", "push_pair"),

@@ -43,21 +43,6 @@ __device__ __forceinline__ double quad_get(double x) {
     return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// Leaves: lam_i = d_i - e_{i-1} - e_i, Q = I.
-__global__ void dc_leaves(int c, const double* __restrict__ d, const double* __restrict__ e, double* __restrict__ lam,
-                          double* __restrict__ Q, int32_t* __restrict__ status) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < c * c; i += gridDim.x * blockDim.x) {
-        const int col = i / c, row = i % c;
-        Q[i] = col == row ? 1.0 : 0.0;
-        if (row == 0) {
-            const double el = col > 0 ? e[col - 1] : 0.0, er = col + 1 < c ? e[col] : 0.0;
-            const double v = d[col] - el - er;
-            lam[col] = v;
-            if (!isfinite(d[col]) || !isfinite(el) || !isfinite(er)) set_status(status, BFGS_ERR_NUMERIC);
-        }
-    }
-}
-
 // What the merges of a workgroup share, by the column's place in the workgroup.
 struct MergeLds {
     double Dv[DC_MAX], zv[DC_MAX], ds[DC_MAX], zs[DC_MAX];
@@ -433,16 +418,31 @@ __global__ void __launch_bounds__(DC_THREADS) dc_merge(int c, int h, const doubl
     }
 }
 
-// The levels up to blocks of DC_FIRST columns in one launch: a workgroup takes a block's
-// leaves through all of them, its merges side by side, and forms each merged basis.  Ten
-// launches of 5 to 25 us, mostly fetching the same code anew, took 110 us at c = 50,
-// this one 79.  In: d, e; out: lam, Q (in the first of each pair after an even
-// number of levels, else in the second).
+// The leaves (lam_i = d_i - e_{i-1} - e_i, Q = I) and the levels up to blocks of DC_FIRST
+// columns in one launch: a workgroup takes a block through all of them, its merges side
+// by side, and forms each merged basis.  Ten launches of 5 to 25 us, mostly fetching the
+// same code anew, took 110 us at c = 50, this one 79.  In: d, e; out: lam, Q (in the first
+// of each pair after an even number of levels, else in the second; only the diagonal
+// blocks are written).
 constexpr int DC_FIRST = 32;
 
-__global__ void __launch_bounds__(4 * DC_FIRST) dc_first(int c, const double* __restrict__ e, double* lam_a, double* Qa,
-                                                         double* lam_b, double* Qb, double* R, double* U) {
+__global__ void __launch_bounds__(4 * DC_FIRST) dc_first(int c, const double* __restrict__ d,
+                                                         const double* __restrict__ e, double* lam_a, double* Qa,
+                                                         double* lam_b, double* Qb, double* R, double* U,
+                                                         int32_t* __restrict__ status) {
     __shared__ MergeLds m;
+    const int c0 = blockIdx.x * DC_FIRST;
+    for (int x = threadIdx.x; x < DC_FIRST * DC_FIRST; x += 4 * DC_FIRST) {
+        const int col = c0 + x / DC_FIRST, row = c0 + x % DC_FIRST;
+        if (col >= c || row >= c) continue;
+        Qa[(int64_t)col * c + row] = col == row ? 1.0 : 0.0;
+        if (row == c0) {
+            const double el = col > 0 ? e[col - 1] : 0.0, er = col + 1 < c ? e[col] : 0.0;
+            lam_a[col] = d[col] - el - er;
+            if (!isfinite(d[col]) || !isfinite(el) || !isfinite(er)) set_status(status, BFGS_ERR_NUMERIC);
+        }
+    }
+    __syncthreads();
     for (int h = 1; h < DC_FIRST && h < c; h *= 2) {
         const int t = threadIdx.x & (8 * h - 1), off = threadIdx.x / (8 * h) * (2 * h);
         const int s = blockIdx.x * DC_FIRST + off;
@@ -577,8 +577,8 @@ int tridiag_dc(hipStream_t st, int c, const double* d, const double* e, const do
     int* Kg = (int*)(lb + c);
     int* ndx_g = Kg + c;
     int* slot_g = ndx_g + c;
-    hipLaunchKernelGGL(dc_leaves, dim3(ceil_div((int64_t)cc, 256)), dim3(256), 0, st, c, d, e, la, Qa, status);
-    hipLaunchKernelGGL(dc_first, dim3(ceil_div(c, DC_FIRST)), dim3(4 * DC_FIRST), 0, st, c, e, la, Qa, lb, Qb, R, U);
+    hipLaunchKernelGGL(dc_first, dim3(ceil_div(c, DC_FIRST)), dim3(4 * DC_FIRST), 0, st, c, d, e, la, Qa, lb, Qb, R, U,
+                       status);
     int h = 1;
     for (; h < DC_FIRST && h < c; h *= 2) {
         std::swap(Qa, Qb);

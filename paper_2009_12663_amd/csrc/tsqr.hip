@@ -178,6 +178,14 @@ __device__ void slot_load(SlotT* slot, const double* M, int c) {
     __syncthreads();
 }
 
+// The identity, where the backward pass starts.
+template <typename SlotT>
+__device__ void slot_identity(SlotT* slot, int c) {
+    slot_zero(slot, c);
+    for (int j = threadIdx.x; j < c; j += blockDim.x) slot[tri_index(j, j, c)] = (SlotT)1;
+    __syncthreads();
+}
+
 template <typename SlotT>
 __device__ void slot_store(const SlotT* slot, double* M, int c) {
     for (int col = threadIdx.x; col < c; col += blockDim.x) {
@@ -870,7 +878,8 @@ __global__ void __launch_bounds__(1024) leaf_backward(int64_t n, int c, int64_t 
     // dimension rows_per_chain)
     TQ* Qc = qblk ? Q + (int64_t)ch * rows_per_chain * c - r_begin : Q;
     const int64_t ldq = qblk ? rows_per_chain : n;
-    slot_load(slot, Qtop + (int64_t)ch * c * c, c);
+    if (gridDim.x == 1) slot_identity(slot, c);   // one chain: no tree
+    else slot_load(slot, Qtop + (int64_t)ch * c * c, c);
     for (int tile = ntiles - 1; tile >= 0; --tile) {
         const int64_t r0 = r_begin + (int64_t)tile * BT;
         const int64_t gtile = (int64_t)ch * tiles_per_chain + tile;
@@ -903,7 +912,8 @@ __global__ void __launch_bounds__(1024) tree_backward(int c, int stride, int64_t
     const int col = qf_group(perm) * PW + jl;
     const int a_idx = i * 2 * stride, b_idx = a_idx + stride;
     double* Qb = Qtop + (int64_t)b_idx * c * c;
-    slot_load(slot, Qtop + (int64_t)a_idx * c * c, c);
+    if (gridDim.x == 1) slot_identity(slot, c);   // the root
+    else slot_load(slot, Qtop + (int64_t)a_idx * c * c, c);
     for (int t = ntt - 1; t >= 0; --t) {
         v4d A[RT];
 #pragma unroll
@@ -920,11 +930,6 @@ __global__ void __launch_bounds__(1024) tree_backward(int c, int stride, int64_t
         }
     }
     slot_store(slot, Qtop + (int64_t)a_idx * c * c, c);
-}
-
-__global__ void set_identity_kernel(double* __restrict__ M, int c) {
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < c * c; e += gridDim.x * blockDim.x)
-        M[e] = (e / c == e % c) ? 1.0 : 0.0;
 }
 
 inline int floor_pow2(int64_t x) {
@@ -990,7 +995,6 @@ int tsqr_impl(bfgsuq_ctx* h, int c, const TE* E, TQ* Q, double** R_out, bool q_b
                            h->stream, c, stride, off, Rs, tree, tring, h->status, perm);
         off += ncomb;
     }
-    hipLaunchKernelGGL(set_identity_kernel, dim3(64), dim3(256), 0, h->stream, Qtop, c);
     for (int stride = nchains / 2; stride >= 1; stride /= 2) {
         const int ncomb = nchains / (2 * stride);
         off -= ncomb;
