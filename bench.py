@@ -645,18 +645,21 @@ KERNEL_GROUPS = [
 ]
 
 
-# Groups with a kernel that runs once per launch while others run less often.
-GROUP_ANCHORS = {"push_pair": "store_pair_kernel"}
+# Groups with a kernel that runs once per launch while others run less often, or whose
+# kernels all run several times per launch (the tree's levels: one leaf pass per tree).
+GROUP_ANCHORS = {"push_pair": "store_pair_kernel", "tsqr_tree": "leaf_backward"}
 
 
-def group_launches(group, calls_by_kernel):
+def group_launches(group, groups):
     """Launches of a group in a trace: the anchor kernel's calls, else the fewest calls
-    of any of its kernels (each launch runs every kernel of the group at least once)."""
+    of any of its kernels (each launch runs every kernel of the group at least once).
+    groups: {group: [(kernel, calls, ...)]} of the whole trace."""
     anchor = GROUP_ANCHORS.get(group)
-    for k, cn in calls_by_kernel:
-        if anchor and anchor in k:
-            return cn
-    return min(cn for _, cn in calls_by_kernel)
+    if anchor:
+        for k, cn, *_ in (v for vs in groups.values() for v in vs):
+            if anchor in k:
+                return cn
+    return min(cn for _, cn, *_ in groups[group])
 
 
 def group_of(kernel_name):
@@ -707,7 +710,7 @@ def summarize_profiles(d, out_dir, digest, cmd_prefix):
               "HIP-event timing of the same group measures):", "",
               "| group | kernels | launches | ms per launch |", "|---|---|---|---|"]
     for g, v in sorted(groups.items(), key=lambda kv: -sum(t for _, _, t in kv[1])):
-        launches = group_launches(g, [(k, cn) for k, cn, _ in v])
+        launches = group_launches(g, groups)
         lines.append(f"| {g} | {len(v)} | {launches} | {sum(t for _, _, t in v) / launches / 1e6:.4f} |")
     open(os.path.join(out_dir, "kernels_grid3_bf16.md"), "w").write("\n".join(lines) + "\n")
 
@@ -762,7 +765,7 @@ def summarize_profiles(d, out_dir, digest, cmd_prefix):
     lines += ["", "Per group launch (sum over the group's kernels):", "",
               "| group | launches | HBM bytes per launch |", "|---|---|---|"]
     for g, v in sorted(per_group.items(), key=lambda kv: -sum(b for _, _, b in kv[1])):
-        launches = group_launches(g, [(k, cn) for k, cn, _ in v])
+        launches = group_launches(g, per_group)
         per_launch = sum(b for _, _, b in v) / launches
         lines.append(f"| {g} | {launches} | {per_launch:.4g} |")
         traffic[g] = {"hbm_bytes_per_launch": per_launch, "source_digest": digest,
