@@ -364,11 +364,12 @@ int bfgs_batch_graph_build(bfgs_batch_t b, const void* const* V, const int32_t* 
                            const int32_t* rank, int32_t oversample, uint64_t seed, void* const* U,
                            double* const* Sigma) {
     if (!b) return BFGS_ERR_ARG;
-    // One eager pass sizes every workspace (and fills the graph's persistent
-    // descriptors), so nothing is allocated or copied while capturing.
+    // One eager pass sizes every workspace, so nothing is allocated or copied while
+    // capturing.  The graph's persistent descriptors hold workspace addresses, and an rSVD of
+    // more columns than the apply replaces a workspace: they are filled after it.
     int rc = bfgs_batch_apply_Hinv(b, V, ncols, out);
-    if (rc == BFGS_OK && persistent_ok(b, ncols)) rc = batch_apply(b, b->main, V, ncols, out, 1, true);
     if (rc == BFGS_OK) rc = bfgs_batch_rsvd(b, rank, oversample, seed, U, Sigma);
+    if (rc == BFGS_OK && persistent_ok(b, ncols)) rc = batch_apply(b, b->main, V, ncols, out, 1, true);
     if (rc != BFGS_OK) return rc;
     BFGS_HIP(hipStreamSynchronize(b->main));
     destroy_graph(b);
