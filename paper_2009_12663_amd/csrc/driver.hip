@@ -76,9 +76,9 @@ __global__ void stencil_z(int64_t nx, int64_t nz, int64_t nparam, int half, cons
 // Both passes of the smoother on one field through LDS: a tile of 32 x 32 points with its
 // half-width halo (zero outside the grid), four neighbouring outputs to a thread in the x
 // pass and one in the z pass.  Sums run over the taps in order, as in stencil_x and
-// stencil_z, which serve wider smoothers.  A small grid's tiles are far fewer than the CUs,
-// so a tile's own latency counts: 300 x 100 x 3 points, half 20: 9 us, 19 for
-// the two stencils.
+// stencil_z, which serve wider smoothers and thin grids (smooth_in_tiles).  A small grid's
+// tiles are far fewer than the CUs, so a tile's own latency counts: 300 x 100 x 3 points,
+// half 20: 9 us, 19 for the two stencils.
 constexpr int SM_T = 32, SM_HALF = 20, SM_IN = SM_T + 2 * SM_HALF, SM_PITCH = SM_IN + 1;
 
 template <typename T>
@@ -127,6 +127,22 @@ __global__ void __launch_bounds__(SM_T* SM_T) smooth_tile(int64_t nx, int64_t nz
 #pragma unroll 8
     for (int t = 0; t < taps; ++t) sum = fma(ws[t], xs[iz + t][ix], sum);
     if (x0 + ix < nx && z0 + iz < nz) out[(int64_t)blockIdx.z * nz * nx + (z0 + iz) * nx + x0 + ix] = sum;
+}
+
+// Whether the tiles are the faster smoother.  A tile costs the same however many of its
+// points exist, the stencils only what exists, so the tiles have to be filled: with half 20,
+// 1700 x 350 x 3 points (98 %) take 48 us in tiles and 156 as stencils, 111,562 x 16 (50 %)
+// 73 and 115, 74,375 x 8 x 3 (25 %) 139 and 104, 1,785,000 x 1 929 and 91.  With hardly any
+// taps that is closer (half 0, 50 %: 30 and 24 us; half 2: 33 and 34).  Up to 256 tiles run
+// at once, one to a CU, and take 9 us where the two launches of the stencils take 10, full or
+// not; two to a CU do so up to half 5 (8 us; 13 with half 20).  A launch holds fewer than 2^32
+// threads along x, and 65535 blocks along y and z.
+bool smooth_in_tiles(int64_t nx, int64_t nz, int32_t nparam, int32_t half) {
+    const int64_t tx = (nx + SM_T - 1) / SM_T, tz = (nz + SM_T - 1) / SM_T;
+    if (half > SM_HALF || nparam > 65535 || tz > 65535 || tx * SM_T * SM_T >= (int64_t)1 << 32) return false;
+    if (tx * tz * nparam <= (half <= 5 ? 512 : 256)) return true;
+    const double filled = (double)nx * nz / ((double)tx * tz * SM_T * SM_T);
+    return filled >= (half < 2 ? 0.875 : 0.5);
 }
 
 // Sum of v over a workgroup of 256, in thread 0.
@@ -247,8 +263,7 @@ int gridop_apply_impl(bfgsuq_gridop* op, const T* x, double* y, hipStream_t st, 
                       double* dots = nullptr) {
     const int64_t n = op->n, npt = op->nx * op->nz;
     double* tz = op->tmp + n;
-    // the tiles' LDS holds a half-width of SM_HALF; grid.y and grid.z count up to 65535
-    if (op->half <= SM_HALF && op->nparam <= 65535 && ceil_div(op->nz, SM_T) <= 65535) {
+    if (smooth_in_tiles(op->nx, op->nz, op->nparam, op->half)) {
         hipLaunchKernelGGL(smooth_tile<T>, dim3((unsigned)ceil_div(op->nx, SM_T), ceil_div(op->nz, SM_T), op->nparam),
                            dim3(SM_T * SM_T), 0, st, op->nx, op->nz, op->half, op->w, x, tz);
     } else {
