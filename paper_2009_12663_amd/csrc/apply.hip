@@ -59,14 +59,17 @@ struct SolveOut {
         } else if (hi) {
             put_halves(i, j, -pv);
             put_halves(rows + i, j, tv);
-            for (int q = k + i; q < rows; q += k) {
-                put_halves(q, j, 0.0);
-                put_halves(rows + q, j, 0.0);
-            }
         } else {
             P[(int64_t)j * k + i] = pv;
             T[(int64_t)j * k + i] = tv;
         }
+    }
+    // The zeros of the halves of column j, fewer than 32, by as many of the calling threads.
+    __device__ __forceinline__ void pad(int i, int j) const {
+        const int q = k + i;
+        if (!hi || q >= rows) return;
+        put_halves(q, j, 0.0);
+        put_halves(rows + q, j, 0.0);
     }
 };
 
@@ -136,43 +139,58 @@ __global__ void __launch_bounds__(64) small_solve(int k, int kmax, int c, const 
 // Same solve through the stored R^-1, for k <= 256: one workgroup per probe column, one
 // thread per pair index.
 //   P = R^-1 Z_s;  W = (D + YHY) P - Z_y;  T = R^-T W
-// A result is one chain of sums over the pairs, in order; what bounds it is the latency of
-// the matrix entries, so SOLVE_DEPTH of them are fetched at a time, and the lanes of a wave
-// walk the same pair, so that they come as whole lines.  The loop is kept short on purpose:
-// unrolled further, fetching its instructions took longer than the sums (44 us at k = 200,
-// c = 220).  Before, with eight in flight, four columns to a thread and every lane starting
-// at its own diagonal: 47 us at k = 200, c = 220 and 28 us for one column at k = 100; now
-// 34 and 19 us.
+// A result is one chain of sums over the pairs, in order, SOLVE_DEPTH matrix entries of it
+// fetched while as many are added; the lanes of a wave walk the same pair, so that they come
+// as whole lines.  What bounds it is the instructions of one wave and fetching them: so a
+// pair is a load and a product and little else (R^-1 and its transpose hold zeros outside
+// their triangles, x is padded with zeros, addresses are those of the pair before plus a
+// column), and the three chains go through one copy of the code.  One column at k = 200 takes
+// 25 us, 220 columns 26; with clamped indices, a select at each pair and three copies 27 and
+// 29, and a bfloat16 block of one column at n = 9,000 46 us in all where it now takes 41.
+// (More entries in flight lose: 32 fetched ahead, 48.)
 constexpr int SOLVE_DEPTH = 16;
 
 struct SolveLds {
-    alignas(16) double a[256];
-    alignas(16) double b[256];
+    alignas(16) double x[256 + SOLVE_DEPTH];
 };
 
-// acc + sum of A(i, l) x[l] over l in [lo, hi) in order, taking only first <= l <= last;
-// A column-major, lo and hi the same in a whole wave, lo a multiple of 2.
+// acc + sum of A(i, l) x[l] over l in [lo, hi) in order; A column-major, lo and hi the same in
+// a whole wave; x is zero from hi on to the end of the last batch.
 __device__ __forceinline__ double solve_chain(double acc, const double* __restrict__ A, int kmax, int i, int lo, int hi,
-                                              int first, int last, const double* x) {
-    double cur[SOLVE_DEPTH], nxt[SOLVE_DEPTH];
+                                              const double* x) {
+    double b0[SOLVE_DEPTH], b1[SOLVE_DEPTH];
+    const double* at = A + (int64_t)lo * kmax;   // column of the next entry to fetch
+    auto fetch = [&](double (&b)[SOLVE_DEPTH], int l0) {
+        if (l0 + SOLVE_DEPTH <= hi) {
 #pragma unroll
-    for (int u = 0; u < SOLVE_DEPTH; ++u) cur[u] = A[(int64_t)min(lo + u, hi - 1) * kmax + i];
-#pragma unroll 1
-    for (int l0 = lo; l0 < hi; l0 += SOLVE_DEPTH) {
+            for (int u = 0; u < SOLVE_DEPTH; ++u) {
+                b[u] = at[i];
+                at += kmax;
+            }
+        } else if (l0 < hi) {
 #pragma unroll
-        for (int u = 0; u < SOLVE_DEPTH; ++u)
-            nxt[u] = A[(int64_t)min(l0 + SOLVE_DEPTH + u, hi - 1) * kmax + i];
+            for (int u = 0; u < SOLVE_DEPTH; ++u) {
+                b[u] = at[i];
+                if (l0 + u + 1 < hi) at += kmax;
+            }
+        }
+    };
+    auto sum = [&](const double (&b)[SOLVE_DEPTH], int l0) {
         double xv[SOLVE_DEPTH];
 #pragma unroll
-        for (int u = 0; u < SOLVE_DEPTH; ++u) xv[u] = x[l0 + u];   // past hi: not used
+        for (int u = 0; u < SOLVE_DEPTH; ++u) xv[u] = x[l0 + u];
         __builtin_amdgcn_sched_barrier(0);   // all fetched before the first is added
 #pragma unroll
-        for (int u = 0; u < SOLVE_DEPTH; ++u) {
-            const int l = l0 + u;
-            const double t = fma(cur[u], xv[u], acc);
-            acc = l < hi && l >= first && l <= last ? t : acc;
-            cur[u] = nxt[u];
-        }
+        for (int u = 0; u < SOLVE_DEPTH; ++u) acc = fma(b[u], xv[u], acc);
+    };
+    fetch(b0, lo);
+#pragma unroll 1
+    for (int l0 = lo; l0 < hi; l0 += 2 * SOLVE_DEPTH) {
+        fetch(b1, l0 + SOLVE_DEPTH);
+        sum(b0, l0);
+        if (l0 + SOLVE_DEPTH >= hi) break;
+        fetch(b0, l0 + 2 * SOLVE_DEPTH);
+        sum(b1, l0 + SOLVE_DEPTH);
     }
     return acc;
 }
@@ -186,21 +204,24 @@ __device__ __forceinline__ void small_solve_block(SolveLds& s, int k, int kmax, 
     const int ic = min(i, k - 1);
     const int w0 = __builtin_amdgcn_readfirstlane(i / 64 * 64);   // this wave's rows: w0 .. w1 - 1
     const int w1 = min(k, w0 + 64);
-    const bool work = w0 < k;
     const double zs = live ? Z[(int64_t)j * 2 * k + i] : 0.0, zy = live ? Z[(int64_t)j * 2 * k + k + i] : 0.0;
     const double dii = Rm[(int64_t)ic * kmax + ic];
-    s.a[i] = zs;
-    __syncthreads();
-    const double pv = work ? solve_chain(0.0, Rinv, kmax, ic, w0, k, i, k, s.a) : 0.0;
-    __syncthreads();
-    s.a[i] = pv;   // P
-    __syncthreads();
-    if (work) s.b[i] = solve_chain(dii * pv - zy, YHY, kmax, ic, 0, k, 0, k, s.a);   // W
-    __syncthreads();
-    const double tv = work ? solve_chain(0.0, RinvT, kmax, ic, 0, w1, 0, i, s.b) : 0.0;
+    double v = zs, pv = 0.0;
+#pragma unroll 1
+    for (int step = 0; step < 3; ++step) {
+        __syncthreads();
+        s.x[i] = live ? v : 0.0;
+        __syncthreads();
+        const double* A = step == 0 ? Rinv : step == 1 ? YHY : RinvT;
+        const int lo = step == 0 ? w0 : 0, hi = step == 2 ? w1 : k;
+        const double first = step == 1 ? dii * v - zy : 0.0;
+        v = w0 < k ? solve_chain(first, A, kmax, ic, lo, hi, s.x) : 0.0;
+        if (step == 0) pv = v;
+    }
+    out.pad(i, j);
     if (live) {
-        out.put(i, j, pv, tv);
-        if (!isfinite(pv) || !isfinite(tv)) set_status(status, BFGS_ERR_NONFINITE);
+        out.put(i, j, pv, v);
+        if (!isfinite(pv) || !isfinite(v)) set_status(status, BFGS_ERR_NONFINITE);
     }
 }
 
@@ -215,44 +236,44 @@ __global__ void __launch_bounds__(256) small_solve_blocks(int k, int kmax, const
 }
 
 // The solve of a few columns: as above, with each sum dealt to FEW_SEGS waves per 64 rows
-// (contiguous quarters of the pairs) and added through LDS in a fixed order, since with the
-// chip otherwise idle the length of a chain is all that counts: one column at k = 100
-// takes 19 us as above, 15 in this form.  (More threads lose it again to the instructions
-// they all issue on one CU; touching the matrices ahead changes nothing.)
-// From about 150 pairs the waves of a workgroup are too many for that (one column at
-// k = 200: 31 us, 26 as above).
+// (contiguous quarters of the pairs, each padded in x) and added through LDS in a fixed order,
+// since with the chip otherwise idle the length of a chain is all that counts: one column at
+// k = 100 takes 10 us, 12.5 as above.  More threads lose it again to the instructions they
+// all issue on one CU: from about 150 pairs the form above is faster (one column at k = 200:
+// 31 and 26 us, both with selects).
 constexpr int FEW_SEGS = 4, FEW_MAXK = 128;
 
-__global__ void __launch_bounds__(256 * FEW_SEGS) small_solve_few(int k, int kmax, const double* __restrict__ Rm,
+__global__ void __launch_bounds__(FEW_MAXK * FEW_SEGS) small_solve_few(int k, int kmax, const double* __restrict__ Rm,
                                                                   const double* __restrict__ Rinv,
                                                                   const double* __restrict__ RinvT,
                                                                   const double* __restrict__ YHY,
                                                                   const double* __restrict__ Z, SolveOut out,
                                                                   int32_t* __restrict__ status) {
-    __shared__ double red[FEW_SEGS][256], x[256 + 64];
+    __shared__ double red[FEW_SEGS][FEW_MAXK], x[FEW_MAXK + FEW_SEGS * SOLVE_DEPTH];
     const int rows = blockDim.x / FEW_SEGS;                        // k rounded up to 64
     const int seg = __builtin_amdgcn_readfirstlane(threadIdx.x / rows), i = threadIdx.x - seg * rows;
     const int j = blockIdx.x, ic = min(i, k - 1);
     const int q = (k + 2 * FEW_SEGS - 1) / (2 * FEW_SEGS) * 2;     // pairs of a segment, even
-    const int lo = min(k, seg * q), hi = min(k, lo + q);
+    const int pitch = (q + SOLVE_DEPTH - 1) / SOLVE_DEPTH * SOLVE_DEPTH;   // in x, zeros between
+    const int lo = min(k, seg * q), hi = min(k, lo + q), pos = ic / q * pitch + ic % q;
     const double zy = Z[(int64_t)j * 2 * k + k + ic], dii = Rm[(int64_t)ic * kmax + ic];
-    if (seg == 0) x[i] = i < k ? Z[(int64_t)j * 2 * k + i] : 0.0;
-    __syncthreads();
-    auto step = [&](const double* A, int first, int last) {
-        red[seg][i] = lo < hi ? solve_chain(0.0, A, kmax, ic, lo, hi, first, last, x) : 0.0;
+    double v = Z[(int64_t)j * 2 * k + ic], pv = 0.0;
+    for (int t = threadIdx.x; t < FEW_SEGS * pitch; t += blockDim.x) x[t] = 0.0;
+#pragma unroll 1
+    for (int step = 0; step < 3; ++step) {
         __syncthreads();
-        return (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
-    };
-    const double pv = step(Rinv, i, k);          // P
-    if (seg == 0) x[i] = pv;
-    __syncthreads();
-    const double wv = step(YHY, 0, k) + fma(dii, pv, -zy);   // W
-    if (seg == 0) x[i] = wv;
-    __syncthreads();
-    const double tv = step(RinvT, 0, i);         // T
+        if (seg == 0 && i < k) x[pos] = v;
+        __syncthreads();
+        const double* A = step == 0 ? Rinv : step == 1 ? YHY : RinvT;
+        red[seg][i] = lo < hi ? solve_chain(0.0, A, kmax, ic, lo, hi, x + seg * pitch - lo) : 0.0;
+        __syncthreads();
+        v = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
+        if (step == 0) pv = v;
+        if (step == 1) v += fma(dii, pv, -zy);
+    }
     if (seg == 0 && i < k) {
-        out.put(i, j, pv, tv);
-        if (!isfinite(pv) || !isfinite(tv)) set_status(status, BFGS_ERR_NONFINITE);
+        out.put(i, j, pv, v);
+        if (!isfinite(pv) || !isfinite(v)) set_status(status, BFGS_ERR_NONFINITE);
     }
 }
 
