@@ -230,7 +230,8 @@ int bfgs_get_status(bfgs_t h);
  *   stream and keeps the fastest in the handle.  V (device, n x ncols, storage
  *   type) and out (device, n x ncols) are scratch inputs/outputs it may
  *   overwrite; U (n x rank) and Sigma (rank) likewise, or NULL to tune the
- *   apply only.  Synchronous; results are unchanged by tuning except for the
+ *   apply only.  A block whose apply does not take the MFMA passes (float32 and
+ *   float64 storage; a few bfloat16 columns) leaves their choice as it is.  Synchronous; results are unchanged by tuning except for the
  *   summation order of the split-K reduction and of the TSQR tree.
  * bfgs_tuning — reads the current choices (host pointers, either may be NULL).
  * bfgs_set_tuning — sets them: g1_rows in 8 .. 1024 row slots, qr_chains a power

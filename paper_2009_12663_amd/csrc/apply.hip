@@ -856,6 +856,29 @@ int apply_small_solve_halves(bfgsuq_ctx* h, int c, const double* Z, int rows, ui
 
 bool apply_takes_tiles(int ncols) { return ncols > STREAM_COLS; }
 
+// B_k V of a few columns from bfloat16 pairs streams them, as other storage does, rather than
+// fill a matrix-core tile of 32; the difference form stays on the matrix cores, as the rSVD's
+// other blocks are.  Streaming against the tile (the difference form's time, which reads V once
+// less), us:
+//     k     n        1 column      2            3            4
+//    60     9,000    20 | 23      22 | 24      26 | 24      26 | 24
+//   100       900    23 | 28      25 | 28      31 | 28      33 | 29
+//   100     9,000    27 | 28      29 | 28      34 | 29      35 | 29
+//   128    65,536    31 | 38      34 | 39      41 | 39      41 | 39
+//   128   200,000    51 | 62      53 | 63      62 | 64      63 | 64
+//   128 1,785,000   354 | 363    361 | 379    410 | 386    416 | 392
+//   150   200,000    66 | 77      68 | 77      as a tile
+//   200    65,536    55 | 58      57 | 58      as a tile
+//   200 1,785,000   565 | 537    569 | 557     as a tile
+// Three and four columns of small blocks lose up to 6 us that way (the tile as it was took 32
+// at k = 100, n = 9,000), but the results are the more exact: float64 sums rounded once, where
+// the tile's products are bfloat16 pairs in float32.  Beyond 128 pairs the solve of a few
+// columns ends, and small blocks and three columns go as a tile.
+bool apply_takes_mfma(const bfgsuq_ctx* h, int ncols, bool diff) {
+    const bool few = !diff && ncols <= STREAM_COLS && (h->k <= FEW_MAXK || (ncols <= 2 && h->n >= 65536));
+    return mfma_apply_supported(h, ncols) && !few;
+}
+
 int apply_diff_float_block(bfgsuq_ctx* h, const void* V, bool f64, int32_t ncols, void* out) {
     // (B_k - B_0) V for a block of the type in which the rSVD keeps Q, not a probe block in the
     // storage type (float64 for float32 and float64 storage, float32 for bfloat16), on the
@@ -886,14 +909,7 @@ int apply_block(bfgsuq_ctx* h, const void* V, int32_t ncols, void* out, bool dif
         if (h->storage != BFGS_F32) return BFGS_ERR_ARG;
         return apply_generic<float, float, double>(h, V, ncols, out, diff, fixed);
     }
-    // bfloat16 pairs: B_k V of a few columns streams the pairs too (one column, k = 60: 17 us
-    // at n = 900 and 173 at 1,785,000, 24 and 301 as a tile of 32), but not from 128 pairs on
-    // small blocks or three columns, where a workgroup's chain over the pairs (at n = 9,000 and
-    // k = 200, 49 us, 43 as a tile) or the float64 products (at 1,785,000, 646 and 599) cost
-    // more.  The difference form stays on the matrix cores, as the rSVD's other blocks are.
-    const bool few = !diff && ncols <= STREAM_COLS && (h->k <= FEW_MAXK || (ncols <= 2 && h->n >= 65536));
-    if (mfma_apply_supported(h, ncols) && !few)
-        return mfma_apply(h, V, ncols, out, diff, fixed);
+    if (apply_takes_mfma(h, ncols, diff)) return mfma_apply(h, V, ncols, out, diff, fixed);
     switch (h->storage) {
         case BFGS_F64: return apply_generic<double, double, double>(h, V, ncols, out, diff, fixed);
         case BFGS_F32: return apply_generic<float, float, float>(h, V, ncols, out, diff, fixed);

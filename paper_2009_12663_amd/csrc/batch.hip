@@ -130,7 +130,7 @@ extern "C" {
 int bfgs_autotune(bfgs_t h, int32_t ncols, int32_t rank, int32_t oversample, void* V, void* out, void* U,
                   double* Sigma) {
     if (!h || !V || !out || ncols < 1 || ncols > BFGS_MAX_COLS || h->k < 1) return BFGS_ERR_ARG;
-    if (mfma_apply_supported(h, ncols)) {
+    if (apply_takes_mfma(h, ncols, false)) {   // only its pass 1 reads the slots
         const int cand[] = {64, 128, 256, 512};
         float best = 1e30f;
         int best_nk = h->g1_nk;

@@ -335,6 +335,8 @@ struct PersistSlot {
 // Whether the float64 apply of that many columns runs in tiles (which the persistent form
 // deals out), not on the few-column path.
 bool apply_takes_tiles(int ncols);
+// Whether the bfloat16 matrix-core passes (mfma_apply) form that product.
+bool apply_takes_mfma(const bfgsuq_ctx* h, int ncols, bool diff);
 // Apply B_k of every problem to its block (float32 or float64 storage, all of one
 // type, 1 <= k <= 256, blocks that run in tiles): five launches on st in all (queue reset, pass 1 of every
 // problem, the sums of its partials, the small solves, pass 2).  upload = false reuses the slot's descriptors
