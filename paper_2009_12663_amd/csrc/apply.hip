@@ -243,16 +243,21 @@ __global__ void __launch_bounds__(256) small_solve_blocks(int k, int kmax, const
 // 31 and 26 us, both with selects).
 constexpr int FEW_SEGS = 4, FEW_MAXK = 128;
 
-__global__ void __launch_bounds__(FEW_MAXK * FEW_SEGS) small_solve_few(int k, int kmax, const double* __restrict__ Rm,
-                                                                  const double* __restrict__ Rinv,
-                                                                  const double* __restrict__ RinvT,
-                                                                  const double* __restrict__ YHY,
-                                                                  const double* __restrict__ Z, SolveOut out,
-                                                                  int32_t* __restrict__ status) {
-    __shared__ double red[FEW_SEGS][FEW_MAXK], x[FEW_MAXK + FEW_SEGS * SOLVE_DEPTH];
-    const int rows = blockDim.x / FEW_SEGS;                        // k rounded up to 64
+struct FewLds {
+    double red[FEW_SEGS][FEW_MAXK], x[FEW_MAXK + FEW_SEGS * SOLVE_DEPTH];
+};
+
+// Column j by a workgroup of FEW_SEGS times k rounded up to 64, or more threads.
+__device__ __forceinline__ void small_solve_segments(FewLds& s, int k, int kmax, const double* __restrict__ Rm,
+                                                     const double* __restrict__ Rinv,
+                                                     const double* __restrict__ RinvT,
+                                                     const double* __restrict__ YHY, const double* __restrict__ Z,
+                                                     SolveOut out, int32_t* __restrict__ status, int j) {
+    auto& red = s.red;
+    auto& x = s.x;
+    const int rows = (k + 63) / 64 * 64;
     const int seg = __builtin_amdgcn_readfirstlane(threadIdx.x / rows), i = threadIdx.x - seg * rows;
-    const int j = blockIdx.x, ic = min(i, k - 1);
+    const int ic = min(i, k - 1);
     const int q = (k + 2 * FEW_SEGS - 1) / (2 * FEW_SEGS) * 2;     // pairs of a segment, even
     const int pitch = (q + SOLVE_DEPTH - 1) / SOLVE_DEPTH * SOLVE_DEPTH;   // in x, zeros between
     const int lo = min(k, seg * q), hi = min(k, lo + q), pos = ic / q * pitch + ic % q;
@@ -265,7 +270,7 @@ __global__ void __launch_bounds__(FEW_MAXK * FEW_SEGS) small_solve_few(int k, in
         if (seg == 0 && i < k) x[pos] = v;
         __syncthreads();
         const double* A = step == 0 ? Rinv : step == 1 ? YHY : RinvT;
-        red[seg][i] = lo < hi ? solve_chain(0.0, A, kmax, ic, lo, hi, x + seg * pitch - lo) : 0.0;
+        if (seg < FEW_SEGS) red[seg][i] = lo < hi ? solve_chain(0.0, A, kmax, ic, lo, hi, x + seg * pitch - lo) : 0.0;
         __syncthreads();
         v = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
         if (step == 0) pv = v;
@@ -275,6 +280,16 @@ __global__ void __launch_bounds__(FEW_MAXK * FEW_SEGS) small_solve_few(int k, in
         out.put(i, j, pv, v);
         if (!isfinite(pv) || !isfinite(v)) set_status(status, BFGS_ERR_NONFINITE);
     }
+}
+
+__global__ void __launch_bounds__(FEW_MAXK * FEW_SEGS) small_solve_few(int k, int kmax, const double* __restrict__ Rm,
+                                                                  const double* __restrict__ Rinv,
+                                                                  const double* __restrict__ RinvT,
+                                                                  const double* __restrict__ YHY,
+                                                                  const double* __restrict__ Z, SolveOut out,
+                                                                  int32_t* __restrict__ status) {
+    __shared__ FewLds lds;
+    small_solve_segments(lds, k, kmax, Rm, Rinv, RinvT, YHY, Z, out, status, blockIdx.x);
 }
 
 // k = 0: B_0 V (or zero for B_k - B_0); a non-finite input sets the deferred status.
@@ -388,15 +403,6 @@ __global__ void __launch_bounds__(256, 2) gemm2_f64mfma(int64_t n, int64_t ld, i
     gemm2_group<TA, TB, false, Ts, Th, To, Tv>(lds, n, ld, k, c, S, Y, h0, V, ldv, M, out, diff, row0, ct, ctiles);
 }
 
-// Calls f(std::integral_constant<int, CC>) for up to STREAM_COLS columns (1, 2 or 4 of them
-// computed).
-template <typename F>
-void with_few_columns(int c, F&& f) {
-    if (c == 1) f(std::integral_constant<int, 1>());
-    else if (c == 2) f(std::integral_constant<int, 2>());
-    else f(std::integral_constant<int, STREAM_COLS>());
-}
-
 template <typename Ts, typename Th, typename Tv>
 void launch_gemm1(hipStream_t st, int64_t n, int64_t ld, int k, int c, const Ts* S, const Ts* Y, const Th* h0,
                   const Tv* V, int64_t ldv, double* part, int64_t rows_per_chunk, int nchunks) {
@@ -465,20 +471,17 @@ int small_solve_launch(bfgsuq_ctx* h, int c, const double* Z, SolveOut out) {
     return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
 }
 
-// A few columns (c <= STREAM_COLS): both passes on the vector unit (stream_f64.h).  Row
-// chunks of pass 1: as many as keep 16 waves a CU busy, of at least 1024 rows, so that the
-// sum of the partials stays short; a single chunk writes Z itself.
+// A few columns (c <= STREAM_COLS): both passes on the vector unit (stream_f64.h).
 template <typename Ts, typename Th, typename To, typename Tv>
 int apply_few(bfgsuq_ctx* h, const Tv* V, int c, To* out, bool diff, const ApplyWs* fixed) {
     const int64_t n = h->n;
-    const int k = h->k, groups = ceil_div(k, STREAM_PAIRS);
+    const int k = h->k;
     const Th* h0 = (const Th*)h->h0;
     const Ts *S = (const Ts*)h->S, *Y = (const Ts*)h->Y;
     const size_t chunk_bytes = (size_t)2 * k * c * 8;
-    int64_t nch = std::min<int64_t>(8 * std::max(1, 512 / (2 * groups)), (n + 1023) / 1024);
-    if (fixed) nch = std::min<int64_t>(nch, (int64_t)(fixed->part_bytes / chunk_bytes));
-    const int64_t rows = round_up((n + nch - 1) / nch, 256);
-    const int nchunks = (int)((n + rows - 1) / rows);
+    const StreamPlan plan = stream_plan(n, k, fixed ? (int64_t)(fixed->part_bytes / chunk_bytes) : 1 << 20);
+    const int groups = plan.groups, nchunks = plan.nchunks;
+    const int64_t rows = plan.rows_per_chunk;
     double *part, *Z, *P;
     if (fixed) {
         part = (double*)fixed->part;
@@ -650,7 +653,9 @@ __device__ __forceinline__ T* global_ptr(const void* p) {
     return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
 }
 
-template <int TB, typename Ts, typename Th, typename Tv>
+// FEW: some problem has few columns, whose items are those of the streaming passes (a kernel of
+// its own, as their registers would spill the tiles').
+template <int TB, bool FEW, typename Ts, typename Th, typename Tv>
 __global__ void __launch_bounds__(64, 2) batch_pass1(const PersistProblem* __restrict__ pr, int nprob, int total,
                                                      unsigned* __restrict__ head) {
     for (;;) {
@@ -667,6 +672,15 @@ __global__ void __launch_bounds__(64, 2) batch_pass1(const PersistProblem* __res
         const PersistProblem& q = pr[lo];
         const int local = item - q.first1, per = q.ptiles * q.ctiles1;
         const int chunk = local / per, pos = local % per;
+        if (FEW && q.few) {
+            with_few_columns(q.c, [&](auto cc) {
+                stream_chunk<decltype(cc)::value, Ts, Th, Tv>(
+                    q.n, q.ld, q.k, q.c, global_ptr<const Ts>(q.S), global_ptr<const Ts>(q.Y), global_ptr<const Th>(q.h0),
+                    global_ptr<const Tv>(q.V), global_ptr<double>(q.nchunks > 1 ? q.part : q.Z), q.rows_per_chunk,
+                    q.ptiles / 2, chunk, pos);
+            });
+            continue;
+        }
         tn_tile<2, TB, true, true, Ts>(q.n, 2 * q.k, q.c, chunk, q.rows_per_chunk, pos % q.ptiles, pos / q.ptiles,
                                        q.ctiles1, PairCols<Ts>{global_ptr<const Ts>(q.S), global_ptr<const Ts>(q.Y), q.ld, q.k},
                                        global_ptr<const Th>(q.h0), global_ptr<const Tv>(q.V), q.n, global_ptr<double>(q.part));
@@ -694,24 +708,39 @@ __global__ void __launch_bounds__(SUM_THREADS) batch_sum(const PersistProblem* _
     if (threadIdx.x < SUM_ENTRIES && e < count) q.Z[e] = t;
 }
 
-// One workgroup per (problem, column): its small solve.
-__global__ void __launch_bounds__(256) batch_solve(const PersistProblem* __restrict__ pr, int nprob) {
+// One workgroup per (problem, column): its small solve, by the kernel of its form.
+template <bool SEGMENTS>
+__global__ void __launch_bounds__(SEGMENTS ? FEW_MAXK * FEW_SEGS : 256) batch_solve(
+    const PersistProblem* __restrict__ pr, int nprob) {
     int j = blockIdx.x, p = 0;
     while (p < nprob && j >= pr[p].c) j -= pr[p++].c;
     if (p >= nprob) return;   // whole workgroup
     const PersistProblem& q = pr[p];
-    __shared__ SolveLds lds;
-    small_solve_block(lds, q.k, q.kmax, global_ptr<double>(q.Rm), global_ptr<double>(q.Rinv),
-                      global_ptr<double>(q.RinvT), global_ptr<double>(q.YHY), global_ptr<double>(q.Z),
-                      SolveOut{nullptr, nullptr, global_ptr<double>(q.M), q.k, (q.c + 15) / 16}, q.status,
-                      j);
+    if (SEGMENTS != (q.few && q.k <= FEW_MAXK)) return;   // whole workgroup
+    __shared__ std::conditional_t<SEGMENTS, FewLds, SolveLds> lds;
+    double* M = global_ptr<double>(q.M);
+    const SolveOut out = q.few ? SolveOut{M, M + (int64_t)q.k * q.c, nullptr, q.k, 0, nullptr, nullptr, 0}
+                               : SolveOut{nullptr, nullptr, M, q.k, (q.c + 15) / 16, nullptr, nullptr, 0};
+    if constexpr (SEGMENTS)
+        small_solve_segments(lds, q.k, q.kmax, global_ptr<double>(q.Rm), global_ptr<double>(q.Rinv),
+                             global_ptr<double>(q.RinvT), global_ptr<double>(q.YHY), global_ptr<double>(q.Z), out,
+                             q.status, j);
+    else
+        small_solve_block(lds, q.k, q.kmax, global_ptr<double>(q.Rm), global_ptr<double>(q.Rinv),
+                          global_ptr<double>(q.RinvT), global_ptr<double>(q.YHY), global_ptr<double>(q.Z), out,
+                          q.status, j);
 }
 
-template <typename Ts, typename Th, typename To, typename Tv>
+template <bool FEW, typename Ts, typename Th, typename To, typename Tv>
 __global__ void __launch_bounds__(256, 2) batch_pass2(const PersistProblem* __restrict__ pr, int nprob, int total,
                                                     unsigned* __restrict__ head) {
     __shared__ int item_sh;
-    __shared__ NnLds<NN_TB> lds;
+    __shared__ union {
+        NnLds<NN_TB> tile;
+        StreamLds<1, Ts> s1;
+        StreamLds<2, Ts> s2;
+        StreamLds<STREAM_COLS, Ts> s4;
+    } lds;
     for (;;) {
         if (threadIdx.x == 0) item_sh = (int)atomicAdd(head, 1u);
         __syncthreads();
@@ -726,8 +755,19 @@ __global__ void __launch_bounds__(256, 2) batch_pass2(const PersistProblem* __re
         }
         const PersistProblem& q = pr[lo];
         const int local = item - q.first2;
+        if (FEW && q.few) {
+            with_few_columns(q.c, [&](auto cc) {
+                constexpr int CC = decltype(cc)::value;
+                double* M = global_ptr<double>(q.M);
+                stream_block<CC, Ts, Th, To, Tv>(
+                    (StreamLds<CC, Ts>&)lds, q.n, q.ld, q.k, q.c, global_ptr<const Ts>(q.S), global_ptr<const Ts>(q.Y),
+                    global_ptr<const Th>(q.h0), global_ptr<const Tv>(q.V), M, M + (int64_t)q.k * q.c,
+                    global_ptr<To>(q.out), 0, local);
+            });
+            continue;
+        }
         gemm2_group<2, NN_TB, true, Ts, Th, To, Tv>(
-            lds, q.n, q.ld, q.k, q.c, global_ptr<const Ts>(q.S), global_ptr<const Ts>(q.Y), global_ptr<const Th>(q.h0),
+            lds.tile, q.n, q.ld, q.k, q.c, global_ptr<const Ts>(q.S), global_ptr<const Ts>(q.Y), global_ptr<const Th>(q.h0),
             global_ptr<const Tv>(q.V), q.n, global_ptr<double>(q.M), global_ptr<To>(q.out), 0,
             (int64_t)(local / q.ctiles2) * 128, local % q.ctiles2, q.ctiles2);
     }
@@ -751,6 +791,7 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
         });
         std::vector<PersistProblem> host(nprob);
         int t1 = 0, tsum = 0, t2 = 0, tsolve = 0;
+        bool few = false, segments = false, chains = false;
         for (int r = 0; r < nprob; ++r) {
             const int i = order[r];
             bfgsuq_ctx* h = hs[i];
@@ -767,15 +808,29 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
             q.h0 = h->h0;
             q.V = V[i];
             q.out = out[i];
-            q.ptiles = ceil_div(ceil_div(twok, 16), 2);
-            q.ctiles1 = ceil_div(ceil_div(c, 16), TB1);
-            q.ctiles2 = ceil_div(ceil_div(c, 16), NN_TB);
-            // the per-problem path's chunking, so that the partial sums match it
-            const ChunkPlan plan = chunk_plan(q.n, k, c, false, sizeof(Ts) == 8);
-            q.rows_per_chunk = plan.rows_per_chunk;
-            q.nchunks = plan.nchunks;
+            // the per-problem path's form and chunking, so that the partial sums match it
+            q.few = c <= STREAM_COLS;
+            size_t need;
+            if (q.few) {
+                const StreamPlan plan = stream_plan(q.n, k);
+                q.ptiles = 2 * plan.groups;
+                q.ctiles1 = q.ctiles2 = 1;
+                q.rows_per_chunk = plan.rows_per_chunk;
+                q.nchunks = plan.nchunks;
+                need = (size_t)plan.nchunks * twok * c * 8;
+            } else {
+                q.ptiles = ceil_div(ceil_div(twok, 16), 2);
+                q.ctiles1 = ceil_div(ceil_div(c, 16), TB1);
+                q.ctiles2 = ceil_div(ceil_div(c, 16), NN_TB);
+                const ChunkPlan plan = chunk_plan(q.n, k, c, false, sizeof(Ts) == 8);
+                q.rows_per_chunk = plan.rows_per_chunk;
+                q.nchunks = plan.nchunks;
+                need = part_bytes(q.n, k, c, sizeof(Ts) == 8);
+            }
+            few |= q.few != 0;
+            (q.few && k <= FEW_MAXK ? segments : chains) = true;
             int rc;
-            if ((rc = ensure_ws(h->part, part_bytes(q.n, k, c, sizeof(Ts) == 8))) != BFGS_OK) return rc;
+            if ((rc = ensure_ws(h->part, need)) != BFGS_OK) return rc;
             if ((rc = ensure_ws(h->Z, (size_t)twok * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
             if ((rc = ensure_ws(h->PT, pt_doubles(h->kmax) * 8)) != BFGS_OK) return rc;
             q.part = (double*)h->part.ptr;
@@ -790,8 +845,8 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
             q.firstsum = tsum;
             q.first2 = t2;
             t1 += q.nchunks * q.ptiles * q.ctiles1;
-            tsum += ceil_div((int64_t)twok * c, SUM_ENTRIES);
-            t2 += ceil_div(q.n, 128) * q.ctiles2;
+            if (!q.few || q.nchunks > 1) tsum += ceil_div((int64_t)twok * c, SUM_ENTRIES);
+            t2 += ceil_div(q.n, q.few ? 64 * stream_rows<Ts>() : 128) * q.ctiles2;
             tsolve += c;
         }
         if (slot->cap < (size_t)nprob) {
@@ -814,6 +869,9 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
         slot->sum_blocks = tsum;
         slot->items2 = t2;
         slot->solve_blocks = tsolve;
+        slot->few = few;
+        slot->segments = segments;
+        slot->chains = chains;
     }
     if (slot->nprob != nprob || !slot->prob) return BFGS_ERR_STATE;
     int dev = 0, ncu = 256;
@@ -821,12 +879,25 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
     const int g1 = std::max(1, std::min(slot->items1, 4 * ncu * wg_per_cu));   // single waves
     const int g2 = std::max(1, std::min(slot->items2, ncu * wg_per_cu));
     hipLaunchKernelGGL(batch_reset, dim3(1), dim3(64), 0, st, slot->head);
-    hipLaunchKernelGGL((batch_pass1<TB1, Ts, Th, Ts>), dim3(g1), dim3(64), 0, st, slot->prob, nprob, slot->items1,
-                       slot->head);
-    hipLaunchKernelGGL(batch_sum, dim3(slot->sum_blocks), dim3(SUM_THREADS), 0, st, slot->prob, nprob);
-    hipLaunchKernelGGL(batch_solve, dim3(slot->solve_blocks), dim3(256), 0, st, slot->prob, nprob);
-    hipLaunchKernelGGL((batch_pass2<Ts, Th, Th, Ts>), dim3(g2), dim3(256), 0, st, slot->prob, nprob, slot->items2,
-                       slot->head + 1);
+    if (slot->few)
+        hipLaunchKernelGGL((batch_pass1<TB1, true, Ts, Th, Ts>), dim3(g1), dim3(64), 0, st, slot->prob, nprob,
+                           slot->items1, slot->head);
+    else
+        hipLaunchKernelGGL((batch_pass1<TB1, false, Ts, Th, Ts>), dim3(g1), dim3(64), 0, st, slot->prob, nprob,
+                           slot->items1, slot->head);
+    if (slot->sum_blocks)
+        hipLaunchKernelGGL(batch_sum, dim3(slot->sum_blocks), dim3(SUM_THREADS), 0, st, slot->prob, nprob);
+    if (slot->chains)
+        hipLaunchKernelGGL(batch_solve<false>, dim3(slot->solve_blocks), dim3(256), 0, st, slot->prob, nprob);
+    if (slot->segments)
+        hipLaunchKernelGGL(batch_solve<true>, dim3(slot->solve_blocks), dim3(FEW_MAXK * FEW_SEGS), 0, st, slot->prob,
+                           nprob);
+    if (slot->few)
+        hipLaunchKernelGGL((batch_pass2<true, Ts, Th, Th, Ts>), dim3(g2), dim3(256), 0, st, slot->prob, nprob,
+                           slot->items2, slot->head + 1);
+    else
+        hipLaunchKernelGGL((batch_pass2<false, Ts, Th, Th, Ts>), dim3(g2), dim3(256), 0, st, slot->prob, nprob,
+                           slot->items2, slot->head + 1);
     return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
 }
 
@@ -837,7 +908,7 @@ int batch_apply_persistent(bfgsuq_ctx* const* hs, int nprob, const void* const* 
     if (nprob < 1) return BFGS_ERR_ARG;
     const bfgs_dtype s0 = hs[0]->storage;
     for (int i = 0; i < nprob; ++i)
-        if (ncols[i] <= STREAM_COLS || hs[i]->storage != s0 || hs[i]->streamed || hs[i]->k < 1 || hs[i]->k > 256)
+        if (hs[i]->storage != s0 || hs[i]->streamed || hs[i]->k < 1 || hs[i]->k > 256)
             return BFGS_ERR_ARG;
     if (s0 == BFGS_F64) return batch_persistent_impl<double, double>(hs, nprob, V, ncols, out, st, slot, upload, wg_per_cu);
     if (s0 == BFGS_F32) return batch_persistent_impl<float, float>(hs, nprob, V, ncols, out, st, slot, upload, wg_per_cu);

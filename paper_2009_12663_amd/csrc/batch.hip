@@ -1,8 +1,8 @@
 // Batched form: many independent inversions (uneven n and k) driven together.
 //
 // A batch owns one handle per problem.  With float32 or float64 storage (and
-// 1 <= k <= 256 and more than a few columns everywhere) the apply of all problems is
-// five launches in all: persistent pass kernels take (problem, tile) items from a work
+// 1 <= k <= 256, and where that is the faster way: persistent_ok) the apply of all problems is
+// five or six launches in all: persistent pass kernels take (problem, tile) items from a work
 // queue, longest problems first (batch_apply_persistent).  Otherwise, and for the rSVD, problems
 // are spread over a small set of side streams forked from the caller's stream with
 // events and joined back, so their kernels overlap on the device.  Apply + rSVD of
@@ -10,6 +10,7 @@
 // launch.  The autotuner times the tunable launch shapes of each problem (rows per
 // pass-1 workgroup, TSQR chain count) and the persistent grid (workgroups per
 // compute unit) with HIP events and keeps the fastest.
+#include <algorithm>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -69,14 +70,32 @@ int joined(bfgsuq_batch* b, hipStream_t root, F&& fn) {
     return rc;
 }
 
+// Whether the apply of the batch goes through the persistent kernels.  Blocks that all run in
+// tiles always do.  With few columns a problem's own four launches are short, and the side
+// streams overlap them: what is left is 15 us of launching a problem, against kernels that
+// stream with less in flight and deal small and large items from one queue.  us, persistent |
+// forked, float32 (float64 alike):
+//   one column each:      64 problems of n = 5,000, k = 20: 277 | 952; 20,000, 60: 563 | 967;
+//                         60,000, 100: 1,973 | 1,630; 8 of 20,000, 60: 211 | 219; 60,000, 40:
+//                         261 | 241; 2 of 20,000, 60: 80 | 83; 60,000, 40: 108 | 81; 1: 46 | 38
+//   one column in one,    64 of 20,000, 60: 2,308 | 2,512; 60,000, 40: 3,744 | 3,000;
+//   k + 10 in the others: 32 of 20,000, 60: 1,222 | 1,217; 16 of 20,000, 20: 322 | 358; 60:
+//                         662 | 621; 8 of 5,000, 60: 248 | 260; 20,000, 20: 253 | 224; 2 of
+//                         5,000, 20: 82 | 84; 60: 97 | 84
 bool persistent_ok(const bfgsuq_batch* b, const int32_t* ncols) {
     const bfgs_dtype s0 = b->h[0]->storage;
     if (s0 != BFGS_F32 && s0 != BFGS_F64) return false;
+    int few = 0;
+    double entries = 0.0;   // of S
     for (int i = 0; i < b->nprob; ++i) {
         const bfgsuq_ctx* h = b->h[i];
-        if (h->storage != s0 || h->streamed || h->k < 1 || h->k > 256 || !apply_takes_tiles(ncols[i])) return false;
+        if (h->storage != s0 || h->streamed || h->k < 1 || h->k > 256) return false;
+        if (!apply_takes_tiles(ncols[i])) ++few;
+        entries += (double)h->n * h->k;
     }
-    return true;
+    if (few == 0) return true;
+    const double most = few == b->nprob ? 1.5e6 : std::min(1.5e6, 4e4 * b->nprob);
+    return b->nprob > 1 && entries <= most * b->nprob;
 }
 
 // capture: root is capturing and the apply opens the captured work, so it needs no

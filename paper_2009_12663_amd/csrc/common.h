@@ -315,7 +315,7 @@ int apply_small_solve_halves(bfgsuq_ctx* h, int c, const double* Z, int rows, ui
 // One problem of a persistent batched apply (device copy read by the pass kernels).
 struct PersistProblem {
     int64_t n, ld, rows_per_chunk;
-    int k, kmax, c, ptiles, ctiles1, ctiles2, nchunks, first1, firstsum, first2;
+    int k, kmax, c, few, ptiles, ctiles1, ctiles2, nchunks, first1, firstsum, first2;
     const void *S, *Y, *h0, *V;
     void* out;
     double *part, *Z, *M;
@@ -330,16 +330,16 @@ struct PersistSlot {
     size_t cap = 0;
     unsigned* head = nullptr;
     int nprob = 0, items1 = 0, sum_blocks = 0, items2 = 0, solve_blocks = 0;
+    bool few = false, segments = false, chains = false;   // whether some problem has that form
 };
 
-// Whether the float64 apply of that many columns runs in tiles (which the persistent form
-// deals out), not on the few-column path.
+// Whether the float64 apply of that many columns runs in tiles, not on the few-column path.
 bool apply_takes_tiles(int ncols);
 // Whether the bfloat16 matrix-core passes (mfma_apply) form that product.
 bool apply_takes_mfma(const bfgsuq_ctx* h, int ncols, bool diff);
 // Apply B_k of every problem to its block (float32 or float64 storage, all of one
-// type, 1 <= k <= 256, blocks that run in tiles): five launches on st in all (queue reset, pass 1 of every
-// problem, the sums of its partials, the small solves, pass 2).  upload = false reuses the slot's descriptors
+// type, 1 <= k <= 256): five or six launches on st in all (queue reset, pass 1 of every
+// problem, the sums of its partials, the small solves in each form that occurs, pass 2).  upload = false reuses the slot's descriptors
 // (a graph capture after an eager call with the same arguments).  wg_per_cu sets the
 // persistent grid (workgroups per compute unit).
 int batch_apply_persistent(bfgsuq_ctx* const* hs, int nprob, const void* const* V, const int32_t* ncols,

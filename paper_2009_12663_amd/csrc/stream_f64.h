@@ -5,10 +5,35 @@
 // 47 us (6.2 TB/s), 75 and 69 us with the tiles.
 #pragma once
 
+#include <algorithm>
+
 #include "tall_f64.h"
 
 constexpr int STREAM_COLS = 4;
 constexpr int STREAM_PAIRS = 8;   // pairs a wave of pass 1 takes at a time
+
+// Calls f(std::integral_constant<int, CC>) for up to STREAM_COLS columns (1, 2 or 4 of them
+// computed).
+template <typename F>
+__host__ __device__ __forceinline__ void with_few_columns(int c, F&& f) {
+    if (c == 1) f(std::integral_constant<int, 1>());
+    else if (c == 2) f(std::integral_constant<int, 2>());
+    else f(std::integral_constant<int, STREAM_COLS>());
+}
+
+// Row chunks of pass 1: as many as keep 16 waves a CU busy, of at least 1024 rows, so that the
+// sum of the partials stays short; a single chunk writes Z itself.
+struct StreamPlan {
+    int groups, nchunks;
+    int64_t rows_per_chunk;
+};
+inline StreamPlan stream_plan(int64_t n, int k, int64_t most = 1 << 20) {
+    const int groups = ceil_div(k, STREAM_PAIRS);
+    int64_t nch = std::min<int64_t>(8 * std::max(1, 512 / (2 * groups)), (n + 1023) / 1024);
+    nch = std::min(nch, most);
+    const int64_t rows = round_up((n + nch - 1) / nch, 256);
+    return {groups, (int)((n + rows - 1) / rows), rows};
+}
 
 // Consecutive rows a lane loads at a time: 16 bytes of the pairs' type.
 template <typename T>
@@ -41,13 +66,11 @@ __device__ __forceinline__ double stream_wave_sums(double (&a)[E]) {
 // workgroup is one wave: STREAM_PAIRS columns of S or of Y over one chunk, the sums kept in
 // registers, V (and h0 for Y) read again by each group of pairs, from L2.
 template <int CC, typename Ts, typename Th, typename Tv>
-__global__ void __launch_bounds__(64, CC > 2 ? 2 : 4) stream_pass1(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
-                                                      const Ts* __restrict__ Y, const Th* __restrict__ h0,
-                                                      const Tv* __restrict__ V, double* __restrict__ part,
-                                                      int64_t rows_per_chunk, int nchunks, int groups) {
+__device__ __forceinline__ void stream_chunk(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
+                                             const Ts* __restrict__ Y, const Th* __restrict__ h0,
+                                             const Tv* __restrict__ V, double* __restrict__ part,
+                                             int64_t rows_per_chunk, int groups, int chunk, int pos) {
     constexpr int VR = stream_rows<Ts>();
-    int chunk, pos;
-    if (!tn_place(blockIdx.x, 2 * groups, nchunks, chunk, pos)) return;
     const bool y = pos >= groups;
     const int p0 = (y ? pos - groups : pos) * STREAM_PAIRS;
     const int lane = threadIdx.x;
@@ -98,18 +121,34 @@ __global__ void __launch_bounds__(64, CC > 2 ? 2 : 4) stream_pass1(int64_t n, in
     if (lane % LANES == 0 && p0 + u < k && j < c) dst[(int64_t)j * 2 * k + p0 + u] = s;
 }
 
+template <int CC, typename Ts, typename Th, typename Tv>
+__global__ void __launch_bounds__(64, CC > 2 ? 2 : 4) stream_pass1(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
+                                                      const Ts* __restrict__ Y, const Th* __restrict__ h0,
+                                                      const Tv* __restrict__ V, double* __restrict__ part,
+                                                      int64_t rows_per_chunk, int nchunks, int groups) {
+    int chunk, pos;
+    if (tn_place(blockIdx.x, 2 * groups, nchunks, chunk, pos))
+        stream_chunk<CC, Ts, Th, Tv>(n, ld, k, c, S, Y, h0, V, part, rows_per_chunk, groups, chunk, pos);
+}
+
 // Pass 2: out = h0 o (V - Y P) + S T (without h0 o V for B_k - B_0); P, T column-major k x c.
 // A workgroup's four waves share its rows: two take a half of S's columns each, two a
 // half of Y's, and their sums meet in LDS.
+template <int CC, typename Ts>
+struct StreamLds {
+    double sums[4][CC][64 * stream_rows<Ts>()];
+};
+
 template <int CC, typename Ts, typename Th, typename To, typename Tv>
-__global__ void __launch_bounds__(256) stream_pass2(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
-                                                    const Ts* __restrict__ Y, const Th* __restrict__ h0,
-                                                    const Tv* __restrict__ V, const double* __restrict__ P,
-                                                    const double* __restrict__ T, To* __restrict__ out, int diff) {
+__device__ __forceinline__ void stream_block(StreamLds<CC, Ts>& lds, int64_t n, int64_t ld, int k, int c,
+                                             const Ts* __restrict__ S, const Ts* __restrict__ Y,
+                                             const Th* __restrict__ h0, const Tv* __restrict__ V,
+                                             const double* __restrict__ P, const double* __restrict__ T,
+                                             To* __restrict__ out, int diff, int block) {
     constexpr int VR = stream_rows<Ts>(), ROWS = 64 * VR, DEPTH = 8;
-    __shared__ double sums[4][CC][ROWS];
+    auto& sums = lds.sums;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
+    const int64_t row0 = (int64_t)block * ROWS;
     {
         const Ts* W = (wave < 2 ? S : Y) + row0 + VR * lane;   // columns are ld (a multiple of 128) rows long
         const double* M = wave < 2 ? T : P;
@@ -145,4 +184,13 @@ __global__ void __launch_bounds__(256) stream_pass2(int64_t n, int64_t ld, int k
         const double h = to_f64(h0[r]), v = diff ? 0.0 : to_f64(V[(int64_t)j * n + r]);
         out[(int64_t)j * n + r] = (To)fma(h, v - (sums[2][j][i] + sums[3][j][i]), sums[0][j][i] + sums[1][j][i]);
     }
+}
+
+template <int CC, typename Ts, typename Th, typename To, typename Tv>
+__global__ void __launch_bounds__(256) stream_pass2(int64_t n, int64_t ld, int k, int c, const Ts* __restrict__ S,
+                                                    const Ts* __restrict__ Y, const Th* __restrict__ h0,
+                                                    const Tv* __restrict__ V, const double* __restrict__ P,
+                                                    const double* __restrict__ T, To* __restrict__ out, int diff) {
+    __shared__ StreamLds<CC, Ts> lds;
+    stream_block<CC, Ts, Th, To, Tv>(lds, n, ld, k, c, S, Y, h0, V, P, T, out, diff, blockIdx.x);
 }
