@@ -628,11 +628,11 @@ def bench_learned(args):
 # ---------------------------------------------------------------------------
 KERNEL_GROUPS = [
     ("gemm1_mfma", "apply_gemm1"), ("gemm1_f64mfma", "apply_gemm1"), ("reduce_z", "apply_reduce"),
-    ("reduce_partials", "apply_reduce"), ("small_solve", "apply_solve"),
+    ("ProjectionSum", "proj_QtX"), ("reduce_partials", "apply_reduce"), ("small_solve", "apply_solve"),
     ("gemm2_mfma", "apply_gemm2"), ("gemm2_f64mfma", "apply_gemm2"), ("scale_by_h0", "apply_gemm2"),
     ("stream_pass1", "apply_gemm1"), ("stream_pass2", "apply_gemm2"),
     ("probes_kernel", "probes"), ("leaf_forward_q", "tsqr_leaf_fwd"),
-    ("tree_forward_q", "tsqr_tree"), ("tree_backward", "tsqr_tree"), ("set_identity", "tsqr_tree"),
+    ("tree_forward_q", "tsqr_tree"), ("tree_backward", "tsqr_tree"),
     ("leaf_backward", "tsqr_leaf_bwd"), ("tri_mul", "tsqr_tree"),
     ("qtx_mfma", "proj_QtX"), ("qtx_bf16", "proj_QtX"), ("lu_factor", "omega_lu"), ("lu_solve", "omega_lu"),
     ("omega_symmetric", "omega_lu"),

@@ -25,6 +25,11 @@
 
 namespace {
 
+// What the sum belongs to, so that a trace tells the two apart.
+struct ApplySum;
+struct ProjectionSum;
+
+template <typename Use>
 __global__ void __launch_bounds__(SUM_THREADS) reduce_partials(int64_t count, int nchunks,
                                                                const double* __restrict__ part,
                                                                double* __restrict__ Z) {
@@ -915,9 +920,9 @@ int batch_apply_persistent(bfgsuq_ctx* const* hs, int nprob, const void* const* 
     return BFGS_ERR_ARG;
 }
 
-int sum_partials(hipStream_t st, int64_t count, int nchunks, const double* part, double* out) {
-    hipLaunchKernelGGL(reduce_partials, dim3(ceil_div(count, SUM_ENTRIES)), dim3(SUM_THREADS), 0, st, count, nchunks,
-                       part, out);
+int sum_partials(hipStream_t st, int64_t count, int nchunks, const double* part, double* out, bool projection) {
+    hipLaunchKernelGGL(projection ? reduce_partials<ProjectionSum> : reduce_partials<ApplySum>,
+                       dim3(ceil_div(count, SUM_ENTRIES)), dim3(SUM_THREADS), 0, st, count, nchunks, part, out);
     return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
 }
 

@@ -238,8 +238,9 @@ __device__ __forceinline__ double ordered_sum(int lo, int hi, double (*sh)[SUM_E
     return sum;
 }
 
-// out[e] = sum over ch of part[ch * count + e], e < count (apply.hip).
-int sum_partials(hipStream_t st, int64_t count, int nchunks, const double* part, double* out);
+// out[e] = sum over ch of part[ch * count + e], e < count (apply.hip); projection: of the rSVD's
+// products with the basis, not of the apply's pass 1.
+int sum_partials(hipStream_t st, int64_t count, int nchunks, const double* part, double* out, bool projection = false);
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }

@@ -45,11 +45,6 @@ __global__ void tri_mul(int c, const double* __restrict__ R2, const double* __re
     }
 }
 
-__global__ void set_identity(double* __restrict__ M, int c) {
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < c * c; e += gridDim.x * blockDim.x)
-        M[e] = (e / c == e % c) ? 1.0 : 0.0;
-}
-
 // ---------------------------------------------------------------------------
 // Small float64 steps, one workgroup of 256 threads.  Matrices live in global
 // memory (at most 256 x 256 doubles, cache resident).
@@ -1040,7 +1035,7 @@ int qr_two_blocks(bfgsuq_ctx* h, int c, double* E, double* Q, int nchunks, int64
     for (int pass = 0; pass < 2; ++pass) {
         launch_qtx(h->stream, n, c1, c2, (const double*)Q, (const double*)E2, part, rows_per_chunk, nchunks);
         double* dst = pass == 0 ? R12 : Rk;
-        if ((rc = sum_partials(h->stream, cnt, nchunks, part, dst)) != BFGS_OK) return rc;
+        if ((rc = sum_partials(h->stream, cnt, nchunks, part, dst, true)) != BFGS_OK) return rc;
         hipLaunchKernelGGL(pack_nn, dim3(64), dim3(256), 0, h->stream, c1, c2, dst, part);   // the partials are summed
         launch_basis<true>(h->stream, n, c1, c2, (const double*)Q, part, E2);
         if (pass == 1) hipLaunchKernelGGL(add_into, dim3(ceil_div(cnt, 256)), dim3(256), 0, h->stream, cnt, Rk, R12);
@@ -1053,7 +1048,7 @@ int qr_two_blocks(bfgsuq_ctx* h, int c, double* E, double* Q, int nchunks, int64
     double* Rn = Rb + 4 * cc;
     double* Rn1 = Rb + 5 * cc;
     launch_qtx(h->stream, n, c1, c2, (const double*)Q, (const double*)Q2, part, rows_per_chunk, nchunks);
-    if ((rc = sum_partials(h->stream, cnt, nchunks, part, P)) != BFGS_OK) return rc;
+    if ((rc = sum_partials(h->stream, cnt, nchunks, part, P, true)) != BFGS_OK) return rc;
     hipLaunchKernelGGL(pack_nn, dim3(64), dim3(256), 0, h->stream, c1, c2, P, part);
     launch_basis<true>(h->stream, n, c1, c2, (const double*)Q, part, Q2);
     hipLaunchKernelGGL(add_p_times_r, dim3(ceil_div(cnt, 256)), dim3(256), 0, h->stream, c1, c2, P, R22, R12);
@@ -1230,7 +1225,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
         if ((rc = apply_diff_float_block(h, V2, sizeof(TQ) == 8, c, Efree)) != BFGS_OK) return rc;
         if (precond) scale_rows_launch(h, c, Efree, -1);
         launch_qtx(h->stream, n, c, c, (const TQ*)Q, (const TE*)Efree, part, rows_per_chunk, nchunks);
-        if ((rc = sum_partials(h->stream, (int64_t)cc, nchunks, part, Tm)) != BFGS_OK) return rc;
+        if ((rc = sum_partials(h->stream, (int64_t)cc, nchunks, part, Tm, true)) != BFGS_OK) return rc;
         hipLaunchKernelGGL(symmetrise, dim3(ceil_div((int64_t)cc, 256)), dim3(256), 0, h->stream, c, Tm, Om);
     } else {
         ProfScope ps(h, "proj_QtX");
@@ -1249,7 +1244,7 @@ int rsvd_impl(bfgsuq_ctx* h, int rank, int oversample, uint64_t seed, TO* U, dou
         } else {
             launch_qtx(h->stream, n, c, c, Qp, (const TS*)X, part, rows_per_chunk, nchunks);
         }
-        if ((rc = sum_partials(h->stream, (int64_t)cc, bf16_path ? qx_chunks : nchunks, part, Tm)) != BFGS_OK)
+        if ((rc = sum_partials(h->stream, (int64_t)cc, bf16_path ? qx_chunks : nchunks, part, Tm, true)) != BFGS_OK)
             return rc;
     }
     if (!two_pass) {
