@@ -49,33 +49,35 @@ __device__ __forceinline__ float bfv(const uint16_t* w, int i) {
 // derivative at the exact 2 Q; the coefficients are rounded to float32 from the constant on,
 // the rest fitted anew after each (2.4e-9 with these; rounded all at once, 1.3e-8, and since
 // that is the same for every sample the sum over the samples kept it: 1.9e-8 of a gradient).
-// Beyond 6 the error is under 1e-9.  Beyond 8 the callers take 2 Q(8) = 2e-14.
+// Beyond 6 the error is under 1e-9.  Beyond 8 the callers take 2 Q(8) = 2e-14.  The
+// coefficients here are those of u / 2, the fitted ones times powers of two.
 // In float32 2 Q is within 7e-8 (rms 0.9e-8 over [-6, 6]), 1 + erff within 1.5e-7 (3.4e-8);
 // the GELU within 2.5e-7 (5.9e-8), with erff 4.5e-7 (7.9e-8).
-__device__ __forceinline__ float normal_tail2(float u) {
-    float p = -5.206117634770635e-07f;
-    p = fmaf(p, u, 9.671506632003002e-06f);
-    p = fmaf(p, u, -7.562607788713649e-05f);
-    p = fmaf(p, u, 0.00028636842034757137f);
-    p = fmaf(p, u, -1.8569659005152062e-05f);
-    p = fmaf(p, u, -0.006927464157342911f);
-    p = fmaf(p, u, 0.05243270471692085f);
-    p = fmaf(p, u, 0.4592220187187195f);
-    p = fmaf(p, u, 1.151104211807251f);
-    return __builtin_amdgcn_exp2f(-(p * u));
+__device__ __forceinline__ float normal_tail2(float v) {   // of u = 2 v
+    float p = -0.0002665532229002565f;
+    p = fmaf(p, v, 0.0024759056977927685f);
+    p = fmaf(p, v, -0.00968013796955347f);
+    p = fmaf(p, v, 0.018327578902244568f);
+    p = fmaf(p, v, -0.000594229088164866f);
+    p = fmaf(p, v, -0.11083942651748657f);
+    p = fmaf(p, v, 0.4194616377353668f);
+    p = fmaf(p, v, 1.836888074874878f);
+    p = fmaf(p, v, 2.302208423614502f);
+    return __builtin_amdgcn_exp2f(-(p * v));
 }
-// x Phi(x) = max(x, 0) - |x| Q(|x|); x + |x| is exact and keeps a NaN.
+// x Phi(x) = max(x, 0) - |x| Q(|x|), from v = x / 2: v + |v| is exact, keeps a NaN, and does
+// not overflow where x + |x| would.
 __device__ __forceinline__ float gelu_f(float x) {
-    const float u = fminf(fabsf(x), 8.0f);
-    return 0.5f * fmaf(-u, normal_tail2(u), x + fabsf(x));
+    const float h = 0.5f * x, v = fminf(fabsf(h), 4.0f);
+    return fmaf(-v, normal_tail2(v), h + fabsf(h));
 }
 // gelu(x) and its derivative Phi(x) + x phi(x)
 __device__ __forceinline__ float gelu_with_grad(float x, float& grad) {
-    const float u = fminf(fabsf(x), 8.0f), q = normal_tail2(u);
+    const float h = 0.5f * x, v = fminf(fabsf(h), 4.0f), q = normal_tail2(v);
     const float cdf = x >= 0.0f ? fmaf(-0.5f, q, 1.0f) : 0.5f * q;
     const float e = __builtin_amdgcn_exp2f(x * x * -0.72134752044448170f);   // exp(-x^2 / 2)
     grad = fmaf(x * 0.39894228040143268f, e, cdf);
-    return 0.5f * fmaf(-u, q, x + fabsf(x));
+    return fmaf(-v, q, h + fabsf(h));
 }
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));

@@ -1,0 +1,33 @@
+"""The network's forward pass on finite features near float32's largest, where x + |x| would
+overflow.  At 3e38 the sums stay finite by the choice of weights, within the forward
+pass's 1e-6 of the float64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mlp as omlp
+
+pytestmark = pytest.mark.gpu
+
+
+def network(sign):
+    rng = np.random.default_rng(5)
+    p = np.abs(omlp.init_params(5) + 0.01 * rng.standard_normal(omlp.NPARAM)).astype(np.float32) + np.float32(1e-3)
+    p[4736:] *= sign
+    return p
+
+
+@pytest.mark.parametrize("x", [1e30, 1.5e38, 2.5e38, 3.3e38])
+def test_near_overflow(x):
+    import paper_2009_12663_amd as P
+    p = network(1.0)
+    p[:512].reshape(64, 8)[:] = [1, 0, 0, 0, 0, 0, 0, 0]     # z1 = x, where 2 x may overflow
+    p[576:4672] /= 64 * p[576:4672].max()
+    p[4736:4800] /= 64 * p[4736:4800].max()
+    net = P.Mlp(torch.from_numpy(p))
+    X = np.full((5, 8), x, dtype=np.float32)
+    X[1::2, ::2] = 0.0
+    got = net.forward(torch.from_numpy(X)).double().cpu().numpy()
+    want = omlp.forward(omlp.round_bf16(p), X.astype(np.float64))
+    assert np.isfinite(got).all() and np.abs(got - want).max() <= 1e-6 * np.abs(want).max()
+    net.close()
