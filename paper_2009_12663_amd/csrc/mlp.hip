@@ -93,14 +93,15 @@ __device__ __forceinline__ f32x16 mfma_bf16(uint4 a, uint4 b, f32x16 c) {
 }
 
 // x = hi + mid + lo exactly, each with at most eight significant bits (truncation): term t
-// of eight values, packed.
+// of eight values, packed.  Of an infinite x, hi is x and the others are zero, not the NaN that
+// x - hi is: `infinite` says that the wave may hold one (nothing else needs to look).
 struct Split8 {
     uint4 term[3];
 };
 __device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b) {   // bfloat16 a, then b
     return __builtin_amdgcn_perm(b, a, 0x07060302u);
 }
-__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+__device__ __forceinline__ Split8 split8(const float (&x)[8], bool infinite) {
     uint32_t t[3][8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -111,6 +112,12 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
         t[0][e] = u;
         t[1][e] = v;
         t[2][e] = __builtin_bit_cast(uint32_t, r2);
+    }
+    if (infinite) {
+        asm volatile("" ::: "memory");   // a branch, not a select for every value
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (isinf(x[e])) t[1][e] = t[2][e] = 0u;
     }
     Split8 s;
 #pragma unroll
@@ -204,7 +211,10 @@ __device__ __forceinline__ f32x16 units_of(const float4* v, int t, int half) {
 // (half 1), another lo and zeros.
 __device__ __forceinline__ void layer1(const MlpWeights& w, int lane, const float (&x)[8], f32x16 (&z)[2]) {
     const int half = lane >> 5;
-    const Split8 s = split8(x);
+    uint32_t most = 0u;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) most = max(most, __builtin_bit_cast(uint32_t, x[e]) << 1);
+    const Split8 s = split8(x, __any(most >= 0xff000000u));
     uint4 first, second;
     first.x = half ? s.term[1].x : s.term[0].x;
     first.y = half ? s.term[1].y : s.term[0].y;
@@ -226,6 +236,12 @@ __device__ __forceinline__ void layer1(const MlpWeights& w, int lane, const floa
 __device__ __forceinline__ void layer64(const uint4 (&m)[2][2][2][64], int lane, const f32x16 (&in)[2],
                                         f32x16 (&out)[2]) {
     Split8 s[2][2];
+    int most = 0;   // of the bits: infinities (the GELU's are positive) and NaN are the largest
+#pragma unroll
+    for (int tk = 0; tk < 2; ++tk)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) most = max(most, __builtin_bit_cast(int, in[tk][r]));
+    const bool infinite = __any(most >= 0x7f800000);
 #pragma unroll
     for (int tk = 0; tk < 2; ++tk)
 #pragma unroll
@@ -233,7 +249,7 @@ __device__ __forceinline__ void layer64(const uint4 (&m)[2][2][2][64], int lane,
             float v[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = in[tk][8 * p + e];
-            s[tk][p] = split8(v);
+            s[tk][p] = split8(v, infinite);
         }
 #pragma unroll
     for (int q = 2; q >= 0; --q)

@@ -1,6 +1,12 @@
-"""The network's forward pass on finite features near float32's largest, where x + |x| would
-overflow.  At 3e38 the sums stay finite by the choice of weights, within the forward
+"""The network's forward pass on infinite features and on finite ones near float32's largest:
+the three-term split of an infinity must not make a NaN of it, nor x + |x| overflow.
+
+With all weights positive an infinite feature gives an infinite output (a negative last layer
+the other sign, and 0 and infinity through the exponential); samples beside it in the wave
+keep every bit.  At 3e38 the sums stay finite by the choice of weights, within the forward
 pass's 1e-6 of the float64 oracle."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -15,6 +21,21 @@ def network(sign):
     p = np.abs(omlp.init_params(5) + 0.01 * rng.standard_normal(omlp.NPARAM)).astype(np.float32) + np.float32(1e-3)
     p[4736:] *= sign
     return p
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_infinite_feature(sign):
+    import paper_2009_12663_amd as P
+    net = P.Mlp(torch.from_numpy(network(sign)))
+    X = torch.from_numpy(np.random.default_rng(6).standard_normal((70, 8)).astype(np.float32))
+    clean, bad = X.clone(), [3, 33, 69]
+    for s in bad:
+        X[s, s % 8] = math.inf
+    out, h0 = net.forward(X).cpu(), net.forward(X, exp_out=True).cpu()
+    want, keep = net.forward(clean).cpu(), [s for s in range(70) if s not in bad]
+    assert torch.equal(out[keep], want[keep])
+    assert (out[bad] == sign * math.inf).all() and (h0[bad] == (math.inf if sign > 0 else 0.0)).all()
+    net.close()
 
 
 @pytest.mark.parametrize("x", [1e30, 1.5e38, 2.5e38, 3.3e38])
