@@ -138,8 +138,11 @@ int bfgs_num_pairs(bfgs_t h, int32_t* k_out);
  * 1 <= ncols <= BFGS_MAX_COLS columns at once.
  *   V    (device) n x ncols, storage type
  *   out  (device) n x ncols, float64 (F64 storage) or float32; must not alias V
- * With k = 0 the result is B_0 V.  Never synchronizes; non-finite results set
- * the deferred status (bfgs_get_status).                                      */
+ * With k = 0 the result is B_0 V.  Non-finite results set the deferred status
+ * (bfgs_get_status).  Never synchronizes, but where a workspace has to be made or
+ * replaced, which waits for the device: on the first call, on the first with more
+ * columns, and for blocks of more than four columns on the first after the pairs
+ * have become more.                                                           */
 int bfgs_apply_Hinv(bfgs_t h, const void* V, int32_t ncols, void* out);
 
 /* bfgs_apply_Hdiff — out = (B_k - B_0) V: Alg. 2 including its final

@@ -494,8 +494,8 @@ int apply_few(bfgsuq_ctx* h, const Tv* V, int c, To* out, bool diff, const Apply
         P = fixed->PT;
     } else {
         int rc;
-        if ((rc = ensure_ws(h->part, (size_t)nchunks * chunk_bytes)) != BFGS_OK) return rc;
-        if ((rc = ensure_ws(h->Z, (size_t)2 * k * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
+        if ((rc = ensure_ws(h->part, stream_part_bytes(n, h->kmax))) != BFGS_OK) return rc;
+        if ((rc = ensure_ws(h->Z, (size_t)2 * h->kmax * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
         if ((rc = ensure_ws(h->PT, pt_doubles(h->kmax) * 8)) != BFGS_OK) return rc;
         part = (double*)h->part.ptr;
         Z = (double*)h->Z.ptr;
@@ -570,7 +570,7 @@ int apply_generic(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff, c
     } else {
         int rc;
         if ((rc = ensure_ws(h->part, part_bytes(n, k, c, sizeof(Tv) == 8))) != BFGS_OK) return rc;
-        if ((rc = ensure_ws(h->Z, (size_t)twok * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
+        if ((rc = ensure_ws(h->Z, (size_t)2 * h->kmax * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
         if ((rc = ensure_ws(h->PT, pt_doubles(h->kmax) * 8)) != BFGS_OK) return rc;
         part = (double*)h->part.ptr;
         Z = (double*)h->Z.ptr;
@@ -614,7 +614,7 @@ int apply_streamed(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff) 
     const size_t chunk_bytes = (size_t)twok * c * 8;
     int rc;
     if ((rc = ensure_ws(h->part, (size_t)ns * nsub * chunk_bytes)) != BFGS_OK) return rc;
-    if ((rc = ensure_ws(h->Z, (size_t)twok * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
+    if ((rc = ensure_ws(h->Z, (size_t)2 * h->kmax * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
     if ((rc = ensure_ws(h->PT, pt_doubles(h->kmax) * 8)) != BFGS_OK) return rc;
     double* part = (double*)h->part.ptr;
     double* Z = (double*)h->Z.ptr;
@@ -822,7 +822,7 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
                 q.ctiles1 = q.ctiles2 = 1;
                 q.rows_per_chunk = plan.rows_per_chunk;
                 q.nchunks = plan.nchunks;
-                need = (size_t)plan.nchunks * twok * c * 8;
+                need = stream_part_bytes(q.n, h->kmax);
             } else {
                 q.ptiles = ceil_div(ceil_div(twok, 16), 2);
                 q.ctiles1 = ceil_div(ceil_div(c, 16), TB1);
@@ -836,7 +836,7 @@ int batch_persistent_impl(bfgsuq_ctx* const* hs, int nprob, const void* const* V
             (q.few && k <= FEW_MAXK ? segments : chains) = true;
             int rc;
             if ((rc = ensure_ws(h->part, need)) != BFGS_OK) return rc;
-            if ((rc = ensure_ws(h->Z, (size_t)twok * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
+            if ((rc = ensure_ws(h->Z, (size_t)2 * h->kmax * BFGS_MAX_COLS * 8)) != BFGS_OK) return rc;
             if ((rc = ensure_ws(h->PT, pt_doubles(h->kmax) * 8)) != BFGS_OK) return rc;
             q.part = (double*)h->part.ptr;
             q.Z = (double*)h->Z.ptr;

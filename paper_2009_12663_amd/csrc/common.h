@@ -257,7 +257,7 @@ struct ApplyWs {
     void* part = nullptr;
     size_t part_bytes = 0;
     double* Z = nullptr;        // >= 2 * k_max * BFGS_MAX_COLS doubles
-    double* PT = nullptr;       // >= 2 * k_max * BFGS_MAX_COLS doubles
+    double* PT = nullptr;       // >= (2 * k_max rounded up to 4) * BFGS_MAX_COLS doubles
     uint16_t* small16 = nullptr;// >= apply_small16_bytes(k_max)
 };
 size_t apply_small16_bytes(int kmax);

@@ -34,6 +34,12 @@ inline StreamPlan stream_plan(int64_t n, int k, int64_t most = 1 << 20) {
     const int64_t rows = round_up((n + nch - 1) / nch, 256);
     return {groups, (int)((n + rows - 1) / rows), rows};
 }
+// Bytes of the partial sums, enough for any number of pairs and columns here: at most 1 MB
+// (8 * 256 / groups chunks of 16 groups sums), so that a handle that gains pairs between its
+// calls, as an optimizer's does, never replaces them (which would wait for the device).
+inline size_t stream_part_bytes(int64_t n, int kmax) {
+    return (size_t)std::min<int64_t>(8 * 256 * 16, (n + 1023) / 1024 * 2 * kmax) * STREAM_COLS * 8;
+}
 
 // Consecutive rows a lane loads at a time: 16 bytes of the pairs' type.
 template <typename T>
