@@ -147,12 +147,12 @@ __global__ void __launch_bounds__(64) small_solve(int k, int kmax, int c, const 
 // A result is one chain of sums over the pairs, in order, SOLVE_DEPTH matrix entries of it
 // fetched while as many are added; the lanes of a wave walk the same pair, so that they come
 // as whole lines.  What bounds it is the instructions of one wave and fetching them: so a
-// pair is a load and a product and little else (R^-1 and its transpose hold zeros outside
-// their triangles, x is padded with zeros, addresses are those of the pair before plus a
-// column), and the three chains go through one copy of the code.  One column at k = 200 takes
-// 25 us, 220 columns 26; with clamped indices, a select at each pair and three copies 27 and
-// 29, and a bfloat16 block of one column at n = 9,000 46 us in all where it now takes 41.
-// (More entries in flight lose: 32 fetched ahead, 48.)
+// pair is a load, its address (32 bits from the matrix's start, a column further and not past
+// the last) and a product, and little else: R^-1 and its transpose hold zeros outside their
+// triangles, x is padded with zeros, and the three chains go through one copy of the code.
+// One to 71 columns take 3.3 us at k = 5, 6.8 at 61, 9.8 at 100 and 13.7 at 150; with scalar
+// addresses, a select at each pair and three copies 4.4, 9.5, 15 and 21.  (More entries in
+// flight lose: 32 fetched ahead, 48.)
 constexpr int SOLVE_DEPTH = 16;
 
 struct SolveLds {
@@ -164,20 +164,13 @@ struct SolveLds {
 __device__ __forceinline__ double solve_chain(double acc, const double* __restrict__ A, int kmax, int i, int lo, int hi,
                                               const double* x) {
     double b0[SOLVE_DEPTH], b1[SOLVE_DEPTH];
-    const double* at = A + (int64_t)lo * kmax;   // column of the next entry to fetch
-    auto fetch = [&](double (&b)[SOLVE_DEPTH], int l0) {
-        if (l0 + SOLVE_DEPTH <= hi) {
+    const unsigned step = (unsigned)kmax * 8, last = (unsigned)(hi - 1) * step + (unsigned)i * 8;
+    unsigned at = (unsigned)lo * step + (unsigned)i * 8;   // of the next entry to fetch, in bytes; at most 8 MB
+    auto fetch = [&](double (&b)[SOLVE_DEPTH]) {           // past hi the last entry again
 #pragma unroll
-            for (int u = 0; u < SOLVE_DEPTH; ++u) {
-                b[u] = at[i];
-                at += kmax;
-            }
-        } else if (l0 < hi) {
-#pragma unroll
-            for (int u = 0; u < SOLVE_DEPTH; ++u) {
-                b[u] = at[i];
-                if (l0 + u + 1 < hi) at += kmax;
-            }
+        for (int u = 0; u < SOLVE_DEPTH; ++u) {
+            b[u] = *(const double*)((const char*)A + at);
+            at = min(at + step, last);
         }
     };
     auto sum = [&](const double (&b)[SOLVE_DEPTH], int l0) {
@@ -188,13 +181,13 @@ __device__ __forceinline__ double solve_chain(double acc, const double* __restri
 #pragma unroll
         for (int u = 0; u < SOLVE_DEPTH; ++u) acc = fma(b[u], xv[u], acc);
     };
-    fetch(b0, lo);
+    fetch(b0);
 #pragma unroll 1
     for (int l0 = lo; l0 < hi; l0 += 2 * SOLVE_DEPTH) {
-        fetch(b1, l0 + SOLVE_DEPTH);
+        fetch(b1);
         sum(b0, l0);
         if (l0 + SOLVE_DEPTH >= hi) break;
-        fetch(b0, l0 + 2 * SOLVE_DEPTH);
+        fetch(b0);
         sum(b1, l0 + SOLVE_DEPTH);
     }
     return acc;
@@ -240,13 +233,12 @@ __global__ void __launch_bounds__(256) small_solve_blocks(int k, int kmax, const
     small_solve_block(lds, k, kmax, Rm, Rinv, RinvT, YHY, Z, out, status, blockIdx.x);
 }
 
-// The solve of a few columns: as above, with each sum dealt to FEW_SEGS waves per 64 rows
+// The solve of a few columns and pairs: as above, with each sum dealt to FEW_SEGS waves
 // (contiguous quarters of the pairs, each padded in x) and added through LDS in a fixed order,
 // since with the chip otherwise idle the length of a chain is all that counts: one column at
-// k = 100 takes 10 us, 12.5 as above.  More threads lose it again to the instructions they
-// all issue on one CU: from about 150 pairs the form above is faster (one column at k = 200:
-// 31 and 26 us, both with selects).
-constexpr int FEW_SEGS = 4, FEW_MAXK = 128;
+// k = 61 takes 4.1 us, 5.4 as above.  From 65 pairs, whose rows are two waves, the waves of the
+// segments hinder one another: 9.2 us at k = 65 and 10.9 at 100, 5.8 and 8.2 as above.
+constexpr int FEW_SEGS = 4, FEW_MAXK = 64;
 
 struct FewLds {
     double red[FEW_SEGS][FEW_MAXK], x[FEW_MAXK + FEW_SEGS * SOLVE_DEPTH];
@@ -937,21 +929,22 @@ bool apply_takes_tiles(int ncols) { return ncols > STREAM_COLS; }
 // other blocks are.  Streaming against the tile (the difference form's time, which reads V once
 // less), us:
 //     k     n        1 column      2            3            4
-//    60     9,000    20 | 23      22 | 24      26 | 24      26 | 24
-//   100       900    23 | 28      25 | 28      31 | 28      33 | 29
-//   100     9,000    27 | 28      29 | 28      34 | 29      35 | 29
-//   128    65,536    31 | 38      34 | 39      41 | 39      41 | 39
-//   128   200,000    51 | 62      53 | 63      62 | 64      63 | 64
-//   128 1,785,000   354 | 363    361 | 379    410 | 386    416 | 392
-//   150   200,000    66 | 77      68 | 77      as a tile
-//   200    65,536    55 | 58      57 | 58      as a tile
-//   200 1,785,000   565 | 537    569 | 557     as a tile
-// Three and four columns of small blocks lose up to 6 us that way (the tile as it was took 32
-// at k = 100, n = 9,000), but the results are the more exact: float64 sums rounded once, where
-// the tile's products are bfloat16 pairs in float32.  Beyond 128 pairs the solve of a few
-// columns ends, and small blocks and three columns go as a tile.
+//    60     9,000    18 | 19      20 | 21      24 | 21      25 | 21
+//   100       900    21 | 24      25 | 25      29 | 25      31 | 25
+//   100     9,000    24 | 24      27 | 25      33 | 25      34 | 25
+//   128    65,536    32 | 36      35 | 37      43 | 37      44 | 37
+//   128   200,000    53 | 60      56 | 61      67 | 62      68 | 62
+//   128 1,785,000   359 | 359    365 | 376    415 | 383    422 | 388
+//   150   200,000    60 | 72      64 | 72      as a tile
+//   200    65,536    47 | 50      50 | 50      as a tile
+//   200 1,785,000   557 | 529    564 | 548     as a tile
+// Three and four columns lose up to 9 us of small blocks that way (the tile as it was before
+// took 32 at k = 100, n = 9,000), but the results are the more exact: float64 sums rounded
+// once, where the tile's products are bfloat16 pairs in float32.  Beyond 128 pairs a
+// workgroup's chain over the pairs in pass 2 costs more than that is worth on small blocks and
+// on three columns.
 bool apply_takes_mfma(const bfgsuq_ctx* h, int ncols, bool diff) {
-    const bool few = !diff && ncols <= STREAM_COLS && (h->k <= FEW_MAXK || (ncols <= 2 && h->n >= 65536));
+    const bool few = !diff && ncols <= STREAM_COLS && (h->k <= 128 || (ncols <= 2 && h->n >= 65536));
     return mfma_apply_supported(h, ncols) && !few;
 }
 
