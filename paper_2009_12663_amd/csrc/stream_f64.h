@@ -36,8 +36,10 @@ inline StreamPlan stream_plan(int64_t n, int k, int64_t most = 1 << 20) {
 }
 // Bytes of the partial sums, enough for any number of pairs and columns here: at most 1 MB
 // (8 * 256 / groups chunks of 16 groups sums), so that a handle that gains pairs between its
-// calls, as an optimizer's does, never replaces them (which would wait for the device).
+// calls, as an optimizer's does, never replaces them (which would wait for the device).  None
+// where n is one chunk for any number of pairs.
 inline size_t stream_part_bytes(int64_t n, int kmax) {
+    if (n <= 1024) return 0;
     return (size_t)std::min<int64_t>(8 * 256 * 16, (n + 1023) / 1024 * 2 * kmax) * STREAM_COLS * 8;
 }
 
