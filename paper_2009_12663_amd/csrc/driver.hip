@@ -130,19 +130,23 @@ __global__ void __launch_bounds__(SM_T* SM_T) smooth_tile(int64_t nx, int64_t nz
 }
 
 // Whether the tiles are the faster smoother.  A tile costs the same however many of its
-// points exist, the stencils only what exists, so the tiles have to be filled: with half 20,
-// 1700 x 350 x 3 points (98 %) take 48 us in tiles and 156 as stencils, 111,562 x 16 (50 %)
-// 73 and 115, 74,375 x 8 x 3 (25 %) 139 and 104, 1,785,000 x 1 929 and 91.  With hardly any
-// taps that is closer (half 0, 50 %: 30 and 24 us; half 2: 33 and 34).  Up to 256 tiles run
-// at once, one to a CU, and take 9 us where the two launches of the stencils take 10, full or
-// not; two to a CU do so up to half 5 (8 us; 13 with half 20).  A launch holds fewer than 2^32
-// threads along x, and 65535 blocks along y and z.
+// points exist, the stencils only what exists, so the tiles have to be filled, the more so the
+// fewer taps there are.  us in tiles | as stencils, half 20, 10, 5, 2, 0:
+//   1700 x 350 x 3 (98 %)   48 | 156    35 | 93     28 | 60     26 | 40     25 | 26
+//   111,562 x 16 (50 %)     73 | 115    48 | 78     37 | 52     33 | 34     30 | 24
+//   65 x 65 x 400 (46 %)   294 | 355   265 | 295   254 | 262   249 | 244   243 | 235
+//   74,375 x 8 x 3 (25 %)  139 | 104    88 | 67     65 | 50     56 | 36     48 | 26
+//   1,785,000 x 1 (3 %)    929 | 91    538 | 58    373 | 40    306 | 30    248 | 25
+// Up to 256 tiles run at once, one to a CU, and take 9 us where the two launches of the
+// stencils take 10, full or not; two to a CU do so with fewer taps (384 of them with half 10:
+// 9 us, 13 with half 20; 512 with half 5: 8).  A launch holds fewer than 2^32 threads along x,
+// and 65535 blocks along y and z.
 bool smooth_in_tiles(int64_t nx, int64_t nz, int32_t nparam, int32_t half) {
     const int64_t tx = (nx + SM_T - 1) / SM_T, tz = (nz + SM_T - 1) / SM_T;
     if (half > SM_HALF || nparam > 65535 || tz > 65535 || tx * SM_T * SM_T >= (int64_t)1 << 32) return false;
-    if (tx * tz * nparam <= (half <= 5 ? 512 : 256)) return true;
+    if (tx * tz * nparam <= (half <= 5 ? 512 : half <= 10 ? 384 : 256)) return true;
     const double filled = (double)nx * nz / ((double)tx * tz * SM_T * SM_T);
-    return filled >= (half < 2 ? 0.875 : 0.5);
+    return filled >= (half < 2 ? 0.875 : half < 5 ? 0.45 : 0.35);
 }
 
 // Sum of v over a workgroup of 256, in thread 0.

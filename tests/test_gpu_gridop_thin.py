@@ -1,6 +1,5 @@
 """The grid operator's smoother on both sides of the rule that chooses between its 32 x 32
-tiles and the two stencils (256 or 512 tiles, half or seven eighths of their points filled),
-on thin grids, and on a row of 2^27 points, whose tiles would not fit a launch.
+tiles and the two stencils (how many tiles, how full they are, how many taps), on thin grids, and on a row of 2^27 points, whose tiles would not fit a launch.
 
 Tolerance: as for the tiles' own edges, sums of at most 2 x 41 positive-weight terms in
 float64 and a coupling of up to three: a few dozen roundings of 2^-53 relative to the largest
@@ -29,8 +28,9 @@ def along(f, half, dim):
 
 
 @pytest.mark.parametrize("nx,nz,nparam,half", [(8192, 1, 1, 20), (8193, 1, 1, 20), (1, 8225, 1, 6), (16384, 3, 1, 5),
-                                               (16385, 3, 1, 5), (16416, 16, 1, 2), (16416, 15, 1, 2), (16416, 28, 1, 1),
-                                               (16416, 27, 1, 0), (5, 7, 600, 20), (50000, 1, 3, 20)])
+                                               (16385, 3, 1, 5), (16416, 16, 1, 2), (16416, 15, 1, 2), (16416, 14, 1, 4),
+                                               (16416, 12, 1, 5), (16416, 11, 1, 20), (12288, 2, 1, 10),
+                                               (12289, 2, 1, 10), (16416, 28, 1, 1), (16416, 27, 1, 0), (5, 7, 600, 20), (50000, 1, 3, 20)])
 def test_rule_edges(nx, nz, nparam, half):
     import paper_2009_12663_amd as P
     g = torch.Generator().manual_seed(nx + 100 * nz)
