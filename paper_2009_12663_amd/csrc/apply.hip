@@ -637,7 +637,8 @@ int apply_streamed(bfgsuq_ctx* h, const void* Vv, int c, void* outv, bool diff) 
 // ---------------------------------------------------------------------------
 // Persistent batched apply (float32 and float64 storage): the first pass of every
 // problem, the float64 small steps of every problem and the second pass of every
-// problem are one launch each.  A pass's workgroups take (problem, tile) items from
+// problem are one launch each (the solve two where problems of up to FEW_MAXK pairs and few
+// columns stand beside others).  A pass's workgroups take (problem, tile) items from
 // a work queue (an atomic counter) until it runs dry; the problems are laid out
 // longest first (work n k c), so the last items to be taken are small ones.  Each
 // item is exactly one workgroup of the per-problem kernels (same tiles, same

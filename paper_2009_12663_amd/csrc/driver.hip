@@ -17,9 +17,10 @@
 // What bounds an iteration on all but the largest models is the launches and the one wait
 // for the pair's check, so the kernels between them are few: the smoothing (both passes
 // through LDS), the coupling with both dot products, and one that takes the step, stores
-// the pair and sums g^T g (q = -p is kept instead of p).  30 iterations at
-// n = 90,000, float64: 4.1 ms with 20 launches and two waits an iteration, now 3.0 with 11
-// and one.
+// the pair and sums g^T g (q = -p is kept instead of p).  Nothing is allocated after the first
+// direction: the apply's workspaces are sized for the handle's capacity.  30 iterations at
+// n = 90,000, float64: 4.1 ms with 20 launches and two waits an iteration, 2.9 with 11 and one
+// and two workspaces replaced for every pair, 2.3 now.
 #include <cmath>
 #include <new>
 #include <type_traits>

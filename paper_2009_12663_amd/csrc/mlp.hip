@@ -16,7 +16,8 @@
 // vector unit's multipliers: with them it took the sum of its products' and its GELUs'
 // time.)  Its error against float64 is 1.0e-7, 1.8e-7 before.  The gradient keeps float32
 // products (v_mfma_f32_32x32x2f32): the bfloat16 ones leave an error of one sign in every
-// sample, which the sum over the samples does not average away (4.5e-8 against 3.5e-8).
+// sample, which the sum over the samples does not average away (4.5e-8 against
+// 3.5e-8, both with the GELU as it was then).
 // Its outer products contract over the samples and go through LDS once.  Per-wave gradient
 // partials are summed in a fixed order in float64 (deterministic), followed by Adam on the
 // float32 master weights.
