@@ -392,17 +392,18 @@ __device__ __forceinline__ float sum_samples(float* rows, int lane, const f32x16
     return s0 + s1;
 }
 
-// Half the gradient of the sum of squared residuals over the wave's samples: partial[wave] =
-// the NP gradients, then the sum of squared residuals.  The factor 2 / N comes in float64 with
-// the sum of the partials (rounded to float32 it was an error common to all: 4.8e-8 at
-// N = 1,000).  A wave takes `per` samples at a time, 32 but for the smallest batches
+// `scale` times half the gradient of the sum of squared residuals over the wave's samples:
+// partial[wave] = the NP gradients, then the sum of squared residuals.  The scale is the power
+// of two in 2 / N, so that the sums stay in range where the gradient does; the rest comes in
+// float64 with the sum of the partials (all of 2 / N rounded to float32 was an error common to
+// all: 4.8e-8 at N = 1,000).  A wave takes `per` samples at a time, 32 but for the smallest batches
 // (mlp_grad_impl): it sums them in float32, and with few of them nothing averages that.
 // Relative error of the gradient at N = 64, 1,000, 8,000 and 65,536 (medians and root mean
 // squares over random networks): 7.6e-8, 3.6e-8, 2.7e-8 and 2.4e-8; of the former kernel, one
 // sample per wave at a time, 7.4e-8, 5.6e-8, 4.5e-8 and 2.8e-8.
 __global__ void __launch_bounds__(256, 1) mlp_grad_kernel(const uint16_t* __restrict__ wbf, const float* __restrict__ X,
                                                           const float* __restrict__ target, int64_t N, int per,
-                                                          float* __restrict__ partial) {
+                                                          float scale, float* __restrict__ partial) {
     extern __shared__ unsigned char mlp_sh[];
     MlpGradLds& lds = *(MlpGradLds*)mlp_sh;
     const MlpGradWeights& w = lds.w;
@@ -452,14 +453,15 @@ __global__ void __launch_bounds__(256, 1) mlp_grad_kernel(const uint16_t* __rest
             }
         }
         const float res = valid ? both_halves((o[0] + o[1]) + (o[2] + o[3])) + w.b3 - tgt : 0.f;
+        const float dout = res * scale;
         lsum = fmaf(res, res, lsum);
-        gb3 += res;
+        gb3 += dout;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                gw3[t][r] = fmaf(res, z[t][r], gw3[t][r]);
-                d2[t][r] *= res;                         // dz2
+                gw3[t][r] = fmaf(dout, z[t][r], gw3[t][r]);
+                d2[t][r] *= dout;                        // dz2
                 gb2[t][r] += d2[t][r];
                 sc.d[(32 * t + 8 * (r / 4) + 4 * half + r % 4) * MLP_PITCH + col] = d2[t][r];
             }
@@ -540,7 +542,7 @@ constexpr int RED_ENTRIES = 32, RED_SEGS = 32;
 __global__ void __launch_bounds__(RED_ENTRIES* RED_SEGS) mlp_reduce_adam(
     const float* __restrict__ partial, int nwaves, float* __restrict__ grad, float* __restrict__ loss,
     float* __restrict__ master, float* __restrict__ m1, float* __restrict__ m2, uint16_t* __restrict__ wbf, int step,
-    float lr, double inv_n, int update) {
+    float lr, double inv_n, double factor, int update) {
     __shared__ double sh[RED_SEGS][RED_ENTRIES + 1];
     const int px = threadIdx.x % RED_ENTRIES, seg = threadIdx.x / RED_ENTRIES;
     const int p = blockIdx.x * RED_ENTRIES + px;
@@ -558,7 +560,7 @@ __global__ void __launch_bounds__(RED_ENTRIES* RED_SEGS) mlp_reduce_adam(
         if (loss) loss[0] = (float)(g * inv_n);
         return;
     }
-    const float gf = (float)(g * (2.0 * inv_n));
+    const float gf = (float)(g * factor);
     if (grad) grad[p] = gf;
     if (!update) return;
     const float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
@@ -695,12 +697,14 @@ static int mlp_grad_impl(bfgs_mlp_t m, const float* X, const float* target, int6
     // are as accurate as the former kernel, and 128 partials would take 2 of 20 us more)
     const int per = N <= 512 ? (int)((N + 127) / 128) : 32;
     const int grid = (int)std::min<int64_t>(MLP_BLOCKS, (N + 4 * per - 1) / (4 * per));
+    const double two_over_n = 2.0 / (double)N, scale = std::ldexp(1.0, std::ilogb(two_over_n));
     hipLaunchKernelGGL(mlp_grad_kernel, dim3(grid), dim3(256), sizeof(MlpGradLds), m->stream, m->wbf, X, target, N,
-                       per, m->partial);
+                       per, (float)scale, m->partial);
     if (update) ++m->step;
     hipLaunchKernelGGL(mlp_reduce_adam, dim3(ceil_div(NP + 1, RED_ENTRIES)), dim3(RED_ENTRIES * RED_SEGS), 0,
                        m->stream, m->partial, 4 * grid,
-                       grad, loss, m->master, m->m1, m->m2, m->wbf, m->step, lr, 1.0 / (double)N, update);
+                       grad, loss, m->master, m->m1, m->m2, m->wbf, m->step, lr, 1.0 / (double)N,
+                       two_over_n / scale, update);
     return hipGetLastError() == hipSuccess ? BFGS_OK : BFGS_ERR_HIP;
 }
 

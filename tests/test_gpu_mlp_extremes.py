@@ -52,3 +52,22 @@ def test_near_overflow(x):
     want = omlp.forward(omlp.round_bf16(p), X.astype(np.float64))
     assert np.isfinite(got).all() and np.abs(got - want).max() <= 1e-6 * np.abs(want).max()
     net.close()
+
+
+@pytest.mark.parametrize("N", [64, 1000, 65536])
+def test_large_residuals(N):
+    """Residuals of 1e37 whose mean float32 holds and whose sum it does not: with X = 0 every
+    sample is the same, so db3 = 2 r and dw3 = 2 r h2 up to rounding."""
+    import paper_2009_12663_amd as P
+    p = network(1.0)
+    net = P.Mlp(torch.from_numpy(p))
+    r = 1e37
+    grad, _ = net.grad(torch.zeros(N, 8), torch.full((N,), -r))
+    grad = grad.double().cpu().numpy()
+    w = omlp.round_bf16(p).astype(np.float64)
+    gelu = np.vectorize(lambda z: 0.5 * z * math.erfc(-z / math.sqrt(2.0)))
+    h2 = gelu(w[576:4672].reshape(64, 64) @ gelu(w[512:576]) + w[4672:4736])
+    want = 2 * r * np.append(h2, 1.0)
+    assert np.isfinite(grad).all()
+    assert np.abs(grad[4736:] - want).max() <= 1e-6 * np.abs(want).max()
+    net.close()
